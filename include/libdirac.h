@@ -138,7 +138,9 @@ int dl_step(dl_plan p, void *psi, const double *V, int64_t nsteps, void *stream)
 /* (Several steps are fused into one pass over memory: up to 5 on 1-D and
  * 2-D grids (1-D lines of at most 65536 cells without a vector potential
  * first run passes of 24 steps, each wave writing 16 cells, unless the depth
- * is capped), fewer on
+ * is capped; 2-D planes with FP32 state, and with FP64 state up to 600
+ * thousand cells, run passes of up to 12 lowest-order or 6 second-order steps
+ * in register tiles, unless the depth is capped or the plan retiled), fewer on
  * periodic 2-D boxes of fewer than twice that many rows,
  * and 2 on 3-D grids with rows of fewer than 2^28 cells; the remainder of
  * nsteps runs in shallower passes.  Second-order steps on 3-D grids take one
@@ -350,7 +352,8 @@ int dl_plan_set_depth(dl_plan p, int depth);
  * [9] graph_pairs, [10] fused steps per pass, [11] workgroups of a
  * single-step pass, [12] reverse steps per pass of dl_grad_step, [13] steps
  * per pass of dl_step_field, [14] steps per pass of the deep passes that 1-D
- * lines run first (0 if the plan has none).  Works on DL_DRY plans.  On a
+ * lines run first (0 if the plan has none), [15] steps per register-tile pass
+ * of 2-D planes (0: marching passes).  Works on DL_DRY plans.  On a
  * batch handle every
  * value is 0 but [10], the steps fused per pass of the batch, [14] the
  * instances run whole by the lines kernel, [15] its workgroups (0 on a dry

@@ -78,6 +78,33 @@ struct SweepArgs {
   int nc;              // components stored per cell: 4, or 2 (two-component 1-D line)
 };
 
+// a 2-D pass held in registers (dirac_tile2d_kernels.h): tiles of 64 columns
+struct TileArgs {
+  int64_t nx, ny;
+  int periodic;
+  int steps;           // steps of the pass
+  int halo;            // transports per axis of the pass: cells lost at each tile edge
+  int64_t nstrips;     // ceil(nx / (64 - 2 halo))
+  int64_t ntiles;      // workgroups with work
+  int xcd_remap;       // blocks dealt XCD-contiguously (grid a multiple of 8)
+  int axes_code;
+  PhaseK ph;
+};
+
+// the register tiles: W waves of RW rows.  `big` has fewer halo rows per
+// written row (48 of FP32 state, 32 of FP64 state, two workgroups per CU),
+// the other (32 rows of sixteen waves) the shorter chain of work per step,
+// which counts when the grid is a few tiles per CU.
+constexpr int kMaxTileDepth = 12;
+struct TileShape { int waves, rows; };
+__host__ __device__ constexpr TileShape tile_shape(bool fp64, bool big) {
+  return big ? (fp64 ? TileShape{4, 8} : TileShape{8, 6}) : TileShape{16, 2};
+}
+// waves per SIMD the register tile kernel is compiled for
+__host__ __device__ constexpr int tile2d_waves(bool fp64, int rows) {
+  return fp64 ? (rows > 2 ? 2 : 4) : (rows > 2 ? 4 : 8);
+}
+
 struct ResidentArgs {
   int64_t n;
   int64_t nsteps;
@@ -112,6 +139,10 @@ bool sweep2d_obs_available(bool fp64, int depth, int mode);
 // modes 0-2; tiling made for strip_width(kDeep1D))
 hipError_t launch_sweep1d_deep(bool fp64, const void* src, void* dst, const double* V,
                                const SweepArgs& a, int blocks, hipStream_t st);
+// a.steps full steps src -> dst on a 2-D grid in register tiles (phase modes
+// 0-2; a.nstrips, a.ntiles made for tile_shape(fp64, big) and a.halo)
+hipError_t launch_tile2d(bool fp64, bool strang, bool big, const void* src, void* dst,
+                         const double* V, const TileArgs& a, hipStream_t st);
 // the two-step 3-D pass (phase modes 0-2) that also sums the observables of
 // the cells it stores: 10 doubles per wave (4 per workgroup tile, a.ntiles
 // tiles) at `partials`, reduced by launch_obs_final

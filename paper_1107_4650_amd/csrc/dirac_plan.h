@@ -17,6 +17,24 @@ struct PlanTiling {
   int deep_b = 0;
 };
 
+// a run of equal passes of a call: marching passes or register tiles of
+// `depth` steps, or the deep passes of 1-D lines
+struct PassRun {
+  enum Kind { kMarch, kDeep, kTile, kTileBig } kind;
+  int depth;
+  int64_t count;
+};
+struct PassList {
+  PassRun run[kMaxDepth + 4];
+  int n = 0;
+  int64_t passes = 0;
+  void add(PassRun::Kind kind, int depth, int64_t count) {
+    if (count <= 0) return;
+    run[n++] = PassRun{kind, depth, count};
+    passes += count;
+  }
+};
+
 struct GraphEntry {
   void* psi;
   const double* V;
@@ -52,6 +70,8 @@ struct dl_plan_s {
   int depth = 1;                        // fused steps per pass in use
   int waves_per_cu = 0;        // 0: size the grid from the kernels' occupancy
   int cu_count = 256;
+  int tile_depth = 0;          // 2-D: steps per register-tile pass (0: marching passes)
+  bool tile_big = false;       // ... in the larger tiles
   dirac::PlanTiling tiling[5];  // per phase mode (3: a vector potential, 4: a pulse)
   int depth_field = 1;          // fused steps per pass with a vector potential
   const double* field = nullptr;  // field integrals (mode 3) or profile (mode 4) of the call

@@ -222,6 +222,70 @@ static int64_t resident_waves(dl_plan p, int mode, int depth) {
   return int64_t(occ) * 4 * p->cu_count;
 }
 
+// tiling of a register-tile pass of `steps` steps; false if the tile is too
+// small for them
+static bool tile_args(dl_plan p, bool big, int steps, TileArgs& a) {
+  const TileShape t = tile_shape(p->fp64, big);
+  const int halo = steps * (p->strang ? 2 : 1);
+  const int64_t w = 64 - 2 * halo, h = t.waves * t.rows - 2 * halo;
+  if (w < 16 || h < 8) return false;
+  a.nx = p->g.n[0];
+  a.ny = p->g.n[1];
+  a.periodic = (p->bc == DL_BC_PERIODIC);
+  a.steps = steps;
+  a.halo = halo;
+  a.nstrips = (a.nx + w - 1) / w;
+  a.ntiles = a.nstrips * ((a.ny + h - 1) / h);
+  a.xcd_remap = 1;
+  a.axes_code = axes_code(p->g);
+  return a.ntiles <= INT32_MAX - 8;
+}
+
+// Time of a register-tile pass in us, from fits (rms error 5-8 %) to the
+// passes of 1 to 12 steps on planes of 128^2 to 4096^2 cells: a tile alone on
+// its compute unit takes t0 + t1 per transport pair, every further tile of
+// the compute unit n0 + n1 per transport pair.  Negative: no such pass.
+static double tile_cost(dl_plan p, bool big, int steps) {
+  struct Fit { double t0, t1, n0, n1; };
+  static const Fit fits[2][2][2] = {  // [fp64][strang][big]
+      {{{5.0, 0.74, 4.2, 0.28}, {7.1, 1.07, 6.4, 0.51}},
+       {{5.1, 0.63, 5.2, 0.11}, {6.5, 1.04, 6.0, 0.43}}},
+      {{{9.3, 0.79, 15.5, 0.0}, {11.1, 1.0, 10.9, 0.17}},
+       {{8.8, 0.79, 14.8, 0.0}, {11.8, 0.89, 10.4, 0.18}}}};
+  TileArgs a{};
+  if (!tile_args(p, big, steps, a)) return -1.0;
+  const Fit& f = fits[p->fp64][p->strang][big];
+  const double per_cu = static_cast<double>(a.ntiles) / p->cu_count;
+  const double more = std::max(0.0, (per_cu < 4.0 ? std::ceil(per_cu) : per_cu) - 1.0);
+  return f.t0 + f.t1 * a.halo + more * (f.n0 + f.n1 * a.halo);
+}
+
+// 2-D plans whose passes are not capped or retiled by the caller run in
+// register tiles where those beat the marching passes: with FP32 state on
+// every plane (per step, Lie: 1.2 against 4.1 us at 256^2, 4.6 against 6.7 us
+// at 1024^2, 14.0 against 17.0 us at 2048^2, 49 against 57 us at 4096^2), with
+// FP64 state up to 600 thousand cells (768^2: 5.5 against 6.4 us, second
+// order 11.0 against 11.1 us; 1024^2: 9.1 against 8.7 and 18.4 against 15.5
+// us).  The tile and the depth are those of the least fitted time per step.
+constexpr int64_t kTileMaxCellsF64 = 600000;
+
+static void choose_tile(dl_plan p) {
+  p->tile_depth = 0;
+  if (p->g.ndim != 2 || p->depth_limit < kMaxDepth || p->waves_per_cu > 0 || p->seg_override > 0)
+    return;
+  if (p->fp64 && p->g.n[0] * p->g.n[1] > kTileMaxCellsF64) return;
+  double best = 0.0;
+  for (int big = 0; big < 2; ++big)
+    for (int k = 1; k <= kMaxTileDepth; ++k) {
+      const double t = tile_cost(p, big != 0, k);
+      if (t > 0.0 && (p->tile_depth == 0 || t / k < best)) {
+        best = t / k;
+        p->tile_depth = k;
+        p->tile_big = big != 0;
+      }
+    }
+}
+
 static int plan_tiling(dl_plan p) {
   // fused steps per pass.  A periodic 2-D pass reaches one row per stage (one
   // per lowest-order step, two per second-order step) beyond a segment on each
@@ -273,6 +337,7 @@ static int plan_tiling(dl_plan p) {
     for (int d = 0; d < kMaxDepth; ++d) t.a[d].periodic = (p->bc == DL_BC_PERIODIC);
   }
   select_tiling(p, 2);
+  choose_tile(p);
   // resident 1-D path: the whole line in one workgroup (4 cells per thread)
   // for all steps of a call.  One workgroup issues every step, so it only
   // beats the tiled passes when those pay a launch for every one or two
@@ -486,29 +551,67 @@ static hipError_t launch_pass_deep(dl_plan p, const void* src, void* dst, const 
   return launch_sweep1d_deep(p->fp64, src, dst, V, a, p->bl_deep, st);
 }
 
-// passes of `nsteps` steps at the plan's current depth (deepest first)
-static int64_t pass_count(dl_plan p, int64_t nsteps) {
+// one register-tile pass of `depth` steps src -> dst
+static hipError_t launch_pass_tile(dl_plan p, bool big, int depth, const void* src, void* dst,
+                                   const double* V, hipStream_t st) {
+  TileArgs a{};
+  if (!tile_args(p, big, depth, a)) return hipErrorInvalidValue;
+  a.ph = p->ph;
+  return launch_tile2d(p->fp64, p->strang, big, src, dst, V, a, st);
+}
+
+// The passes of a call of `nsteps` steps with the current phase: deep passes
+// (1-D) or register tiles (2-D) where the plan uses them, marching passes for
+// the rest, deepest first.  obs: the last pass is the marching pass that sums
+// the observables (on 3-D plans a two-step one, after the single step of an
+// odd count).
+static PassList pass_list(dl_plan p, int64_t nsteps, bool obs) {
+  PassList l;
+  int64_t left = nsteps;
   const int dmax = (p->ph.mode >= 3) ? p->depth_field : p->depth;
-  int64_t n = 0, left = nsteps;
   if (deep1d(p)) {
-    n += left / kDeep1D;
+    l.add(PassRun::kDeep, kDeep1D, left / kDeep1D);
     left %= kDeep1D;
   }
+  if (p->tile_depth > 0 && p->ph.mode <= 2) {
+    const int64_t n = obs ? left - std::min<int64_t>(left, dmax) : left;
+    if (n > 0) {
+      const PassRun::Kind kind = p->tile_big ? PassRun::kTileBig : PassRun::kTile;
+      int64_t passes = (n + p->tile_depth - 1) / p->tile_depth;
+      if (passes == 1 && n > 1 && left == n) {
+        // a single pass ends in the plan's buffer: two shallower ones, unless
+        // copying the state back (about 4 us, then 4.5 TB/s) is cheaper
+        const double copy = 4.0 + 2.0 * static_cast<double>(p->state_bytes) / 4.5e6;
+        if (tile_cost(p, p->tile_big, static_cast<int>(n - n / 2)) +
+                tile_cost(p, p->tile_big, static_cast<int>(n / 2)) <
+            tile_cost(p, p->tile_big, static_cast<int>(n)) + copy)
+          passes = 2;
+      }
+      const int d = static_cast<int>(n / passes);  // passes of d + 1 and d steps
+      l.add(kind, d + 1, n % passes);
+      l.add(kind, d, passes - n % passes);
+      left -= n;
+    }
+  }
+  if (obs && p->g.ndim == 3 && p->depth == 2 && left % 2 == 1 && left > 1) {
+    l.add(PassRun::kMarch, 1, 1);
+    --left;
+  }
   for (int d = dmax; d >= 1; --d) {
-    n += left / d;
+    l.add(PassRun::kMarch, d, left / d);
     left %= d;
   }
-  return n;
+  return l;
 }
 
 // The plan's third state buffer: with it, an odd number (>= 3) of passes
 // ends in psi (psi -> tmp -> alt -> tmp ... -> psi) instead of in tmp with a
 // copy back.  Allocated once, by the first call that needs it, and never
-// while the stream is being captured; without it the copy stays.
-static void want_alt(dl_plan p, int64_t nsteps, hipStream_t st) {
+// while the stream is being captured; without it the copy stays.  n: passes
+// of the call.
+static void want_alt(dl_plan p, int64_t n, hipStream_t st) {
   if (p->alt || p->alt_failed) return;
   if (p->g.ndim == 3 && p->strang) return;  // second-order 3-D groups end in psi by themselves
-  const int64_t n = pass_count(p, nsteps);
   if (n < 3 || n % 2 == 0) return;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
@@ -548,42 +651,28 @@ hipError_t enqueue_steps(dl_plan p, void* psi, const double* V, int64_t nsteps, 
     *result = psi;
     return hipSuccess;
   }
-  want_alt(p, nsteps, st);
-  const int64_t passes = pass_count(p, nsteps);
-  void* third = (passes >= 3 && passes % 2 == 1) ? p->alt : nullptr;
+  const PassList list = pass_list(p, nsteps, obs != nullptr);
+  want_alt(p, list.passes, st);
+  void* third = (list.passes >= 3 && list.passes % 2 == 1) ? p->alt : nullptr;
   void* in = psi;
-  int64_t i = 0, left = nsteps;
-  if (obs && p->g.ndim == 3 && p->depth == 2 && left % 2 == 1 && left > 1) {
-    // the single step first, so that the last pass is a two-step one, the
-    // pass that sums the observables
-    void* out = third ? ((i == passes - 1) ? psi : (i % 2 == 0 ? p->tmp : third))
-                      : (in == psi ? p->tmp : psi);
-    hipError_t e = launch_pass(p, 1, in, out, V, st);
-    if (e != hipSuccess) return e;
-    p->pulse.n0 += 1;
-    in = out;
-    ++i;
-    --left;
-  }
-  if (deep1d(p)) {
-    for (; left >= kDeep1D; left -= kDeep1D, ++i) {
-      void* out = third ? ((i == passes - 1) ? psi : (i % 2 == 0 ? p->tmp : third))
+  int64_t i = 0;
+  for (int r = 0; r < list.n; ++r) {
+    const PassRun& run = list.run[r];
+    for (int64_t c = 0; c < run.count; ++c, ++i) {
+      const bool last = i == list.passes - 1;
+      void* out = third ? (last ? psi : (i % 2 == 0 ? p->tmp : third))
                         : (in == psi ? p->tmp : psi);
-      hipError_t e = launch_pass_deep(p, in, out, V, st);
+      hipError_t e;
+      if (run.kind == PassRun::kDeep)
+        e = launch_pass_deep(p, in, out, V, st);
+      else if (run.kind == PassRun::kTile || run.kind == PassRun::kTileBig)
+        e = launch_pass_tile(p, run.kind == PassRun::kTileBig, run.depth, in, out, V, st);
+      else if (obs && last)
+        e = launch_pass_obs(p, run.depth, in, out, V, *obs, st, obs_waves);
+      else
+        e = launch_pass(p, run.depth, in, out, V, st);
       if (e != hipSuccess) return e;
-      p->pulse.n0 += kDeep1D;
-      in = out;
-    }
-  }
-  const int dmax = (p->ph.mode >= 3) ? p->depth_field : p->depth;
-  for (int d = dmax; d >= 1; --d) {
-    for (; left >= d; left -= d, ++i) {
-      void* out = third ? ((i == passes - 1) ? psi : (i % 2 == 0 ? p->tmp : third))
-                        : (in == psi ? p->tmp : psi);
-      hipError_t e = (obs && left == d) ? launch_pass_obs(p, d, in, out, V, *obs, st, obs_waves)
-                                        : launch_pass(p, d, in, out, V, st);
-      if (e != hipSuccess) return e;
-      p->pulse.n0 += d;  // the pulse's step index of the next pass
+      p->pulse.n0 += run.depth;  // the pulse's step index of the next pass
       in = out;
     }
   }
@@ -614,7 +703,7 @@ static hipError_t graph_for(dl_plan p, void* psi, const double* V, int64_t pairs
     hipError_t e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking);
     if (e != hipSuccess) return e;
   }
-  want_alt(p, 2 * pairs, p->cap_stream);  // before the capture begins
+  want_alt(p, pass_list(p, 2 * pairs, false).passes, p->cap_stream);  // before the capture begins
   hipGraph_t graph = nullptr;
   hipError_t e = hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return e;
@@ -1000,7 +1089,8 @@ extern "C" int dl_plan_info(dl_plan p, int64_t* info, int n) {
                           t.xcd_remap,         p->graph_pairs, p->depth,     p->bl[0],
                           reverse_depth(p),    p->depth_field,
                           (p->g.ndim == 1 && !p->strang && p->depth_limit >= kMaxDepth &&
-                           p->bl_deep > 0) ? kDeep1D : 0};
+                           p->bl_deep > 0) ? kDeep1D : 0,
+                          p->tile_depth};
   const int nv = static_cast<int>(sizeof vals / sizeof vals[0]);
   for (int i = 0; i < n && i < nv; ++i) info[i] = vals[i];
   return DL_OK;

@@ -25,6 +25,7 @@
 #include "dirac_launch.h"
 #include "dirac_sweep_impl.h"
 #include "dirac_sweep2d_kernels.h"
+#include "dirac_tile2d_kernels.h"
 
 namespace dirac {
 
@@ -142,6 +143,20 @@ hipError_t launch_sweep1d_deep(bool fp64, const void* src, void* dst, const doub
   SweepArgs args = a;
   void* kargs[] = {const_cast<void**>(&src), &dst, const_cast<double**>(&V), &args};
   return hipLaunchKernel(fn, dim3(blocks), dim3(256), kargs, 0, st);
+}
+
+hipError_t launch_tile2d(bool fp64, bool strang, bool big, const void* src, void* dst,
+                         const double* V, const TileArgs& a, hipStream_t st) {
+  const void* fn = fp64 ? kernel_tile2d_f64(strang, big, a.axes_code, a.ph.mode)
+                        : kernel_tile2d_f32(strang, big, a.axes_code, a.ph.mode);
+  const TileShape t = tile_shape(fp64, big);
+  const int64_t blocks = (a.ntiles + 7) / 8 * 8;
+  if (!fn || a.ntiles < 1 || blocks > INT32_MAX || 2 * a.halo >= 64 ||
+      2 * a.halo >= t.waves * t.rows)
+    return hipErrorInvalidValue;
+  TileArgs args = a;
+  void* kargs[] = {const_cast<void**>(&src), &dst, const_cast<double**>(&V), &args};
+  return hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(64 * t.waves), kargs, 0, st);
 }
 
 bool sweep2d_obs_available(bool fp64, int depth, int mode) {

@@ -1,0 +1,11 @@
+// dirac_tile2d_f32.hip -- register-tile 2-D passes, FP32 state (instances of
+// the kernel in dirac_tile2d_kernels.h)
+#include "dirac_tile2d_kernels.h"
+
+namespace dirac {
+
+const void* kernel_tile2d_f32(bool strang, bool big, int axes_code, int mode) {
+  return kernel_tile2d<float>(strang, big, axes_code, mode);
+}
+
+}  // namespace dirac

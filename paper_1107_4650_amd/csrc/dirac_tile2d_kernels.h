@@ -1,0 +1,196 @@
+// dirac_tile2d_kernels.h -- 2-D passes held in a workgroup's registers.
+// Internal to libdirac.
+//
+// A workgroup of W waves holds a tile of 64 columns by W * RW rows (RW rows
+// per wave, one cell per lane and row) with its phase factors in registers,
+// advances it by K full steps and writes the cells K steps (2K transports per
+// axis with second-order steps) away from the tile's edges.  The x transport
+// is a DPP shift, the y transport passes the movers of a wave's first and
+// last row to its neighbours through LDS (double buffered: one barrier per y
+// transport).  The cells beyond a wave's tile that a transport lacks only
+// reach cells that are not written.  Per cell the arithmetic and its order are
+// those of the marching passes, so the bits are the same.
+//
+// Why beside the marching passes (march2d): a marching wave issues its rows
+// one after the other, 18 iterations of 5 stages however small the plane,
+// and at two waves per SIMD it cannot use the second FP32 issue slot (a wave
+// issues one FP32 instruction in 4.9 cycles, four waves one in 2.4).  Tiles
+// need 16 registers per cell (FP32) and run 4 to 8 waves per SIMD.  Per step
+// with a potential, marching -> tiles: 256^2 FP32 4.06 -> 1.20 us, 1024^2
+// 6.7 -> 4.6 us, 2048^2 17.0 -> 14.0 us; 256^2 FP64 4.9 -> 1.7 us; second
+// order at 2048^2 FP32 28.4 -> 25.7 us.  Large planes are bound by VALU issue
+// (the halo makes a tile of 48 rows and K = 7 do 1.8 times the work it writes)
+// at 4.5 TB/s of reads and writes; small ones by the launch and the first load
+// (about 5 us) and by the barrier and LDS latency of a step (0.7 us).
+#pragma once
+#include "dirac_device.h"
+#include "dirac_launch.h"
+#include "dirac_sweep_impl.h"
+
+namespace dirac {
+
+// one y mover of every lane of a wave, in 16-byte parts (conflict-free
+// 128-bit LDS accesses for both state types)
+template <typename T> struct MovLds {
+  static constexpr int kParts = sizeof(Mov<T>) / 16;
+  uint4 q[kParts][64];
+  __device__ __forceinline__ void put(int lane, const Mov<T>& m) {
+    const uint4* s = reinterpret_cast<const uint4*>(m.v);
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) q[p][lane] = s[p];
+  }
+  __device__ __forceinline__ void get(int lane, Mov<T>& m) const {
+    uint4* d = reinterpret_cast<uint4*>(m.v);
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) d[p] = q[p][lane];
+  }
+};
+
+// r (at most 2^31 + a tile) wrapped around a periodic box, or clamped to the box
+__device__ __forceinline__ int64_t tile_index(int64_t r, int64_t n, int periodic) {
+  if (!periodic) return r < 0 ? 0 : (r >= n ? n - 1 : r);
+  // one wrap reaches the halo of any box of a tile or more; the division
+  // only runs for smaller boxes
+  if (r < 0) r += n;
+  if (r >= n) r -= n;
+  if (r < 0 || r >= n) {
+    const int m = static_cast<int>(r) % static_cast<int>(n);
+    r = m < 0 ? m + static_cast<int>(n) : m;
+  }
+  return r;
+}
+
+template <typename T, class S, int W, int RW, int AX0, int AX1, int MODE>
+__global__ __launch_bounds__(64 * W, tile2d_waves(sizeof(T) == 8, RW)) void k_tile2d(
+    const T* __restrict__ src, T* __restrict__ dst, const double* __restrict__ V, TileArgs a) {
+  constexpr bool TWO = sizeof(T) == 8;
+  __shared__ MovLds<T> sr[2][W], sl[2][W];  // right movers up, left movers down
+  const int lane = threadIdx.x & 63;
+  const int wv = wave_in_block();
+  int64_t blk = blockIdx.x;
+  if (a.xcd_remap) blk = (blk % 8) * (gridDim.x / 8) + blk / 8;
+  if (blk >= a.ntiles) return;  // the whole workgroup
+  const int64_t nx = a.nx, ny = a.ny;
+  const int64_t seg = blk / a.nstrips, strip = blk % a.nstrips;
+  const int X = a.halo;  // transports per axis of the pass
+  const int64_t x = strip * (64 - 2 * X) - X + lane;
+  const int64_t y0 = seg * (W * RW - 2 * X) - X + wv * RW;  // this wave's first row
+  const int64_t col = tile_index(x, nx, a.periodic);
+  const bool xin = x >= 0 && x < nx;
+  // wave-uniform: some cell of the wave lies beyond a zero wall
+  const int64_t xs = strip * (64 - 2 * X) - X;
+  const bool walls = !a.periodic && (xs < 0 || xs + 63 >= nx || y0 < 0 || y0 + RW > ny);
+  Site<T> s[RW];
+  double v[RW];
+  uint32_t yin = 0;  // bit j: row y0 + j lies in the box
+#pragma unroll
+  for (int j = 0; j < RW; ++j) {
+    const int64_t q = tile_index(y0 + j, ny, a.periodic) * nx + col;
+    load_site(src + q * 8, s[j]);
+    v[j] = (MODE == 2) ? V[q] : 0.0;
+    if (y0 + j >= 0 && y0 + j < ny) yin |= 1u << j;
+  }
+  yin = __builtin_amdgcn_readfirstlane(yin);
+  typename Stored<T>::type f[RW];
+#pragma unroll
+  for (int j = 0; j < RW; ++j) {
+    Factors fd = factors_of<MODE, TWO>(v[j], a.ph);
+    factors_fix<MODE, TWO>(fd, v[j], a.ph);
+    f[j] = Stored<T>::of(fd);
+    if (walls && (!((yin >> j) & 1u) || !xin)) zero(s[j]);
+  }
+  const int below = wv > 0 ? wv - 1 : 0, above = wv < W - 1 ? wv + 1 : W - 1;
+  // One transport pair and its local work per stage.  EDGE: zero the cells
+  // beyond a zero wall after every stage, as the marching passes do.
+  auto advance = [&](auto edge) {
+    constexpr bool EDGE = decltype(edge)::value;
+    int buf = 0;
+    for (int k = 0; k < a.steps; ++k) {
+#pragma unroll
+      for (int st = 0; st < S::kStages; ++st, buf ^= 1) {
+        Mov<T> r[RW], l[RW];
+        if (S::pre_x(st)) {
+#pragma unroll
+          for (int j = 0; j < RW; ++j) {
+            Site<T> o;
+            x_transport_inner<T, AX0>(s[j], o);
+            s[j] = o;
+            if (TWO) Axis<AX1, T>::movers(s[j], r[j], l[j]);
+          }
+        }
+        if (!TWO || !S::pre_x(st)) {
+#pragma unroll
+          for (int j = 0; j < RW; ++j) Axis<AX1, T>::movers(s[j], r[j], l[j]);
+        }
+        sr[buf][wv].put(lane, r[RW - 1]);
+        sl[buf][wv].put(lane, l[0]);
+        __syncthreads();
+        Mov<T> rb, la;  // from the row below the wave's first, above its last
+        sr[buf][below].get(lane, rb);
+        sl[buf][above].get(lane, la);
+#pragma unroll
+        for (int j = 0; j < RW; ++j) {
+          Axis<AX1, T>::combine(j > 0 ? r[j - 1] : rb, j < RW - 1 ? l[j + 1] : la, s[j]);
+          if (S::phase(st)) apply_local<MODE>(s[j], f[j], a.ph);
+          if (S::post_x(st)) {
+            Site<T> o;
+            x_transport_inner<T, AX0>(s[j], o);
+            s[j] = o;
+          }
+          if (EDGE && walls && (!((yin >> j) & 1u) || !xin)) zero(s[j]);
+        }
+      }
+    }
+  };
+  // waves of two rows run a loop without the wall test where no cell lies
+  // beyond a wall; with more rows per wave that loop spills (the test's branch
+  // keeps the compiler from interleaving the rows' temporaries), so those
+  // waves test in every stage
+  if (RW > 2 || walls)
+    advance(std::true_type{});
+  else
+    advance(std::false_type{});
+  if (!xin || lane < X || lane > 63 - X) return;
+#pragma unroll
+  for (int j = 0; j < RW; ++j) {
+    const int t = wv * RW + j;  // tile row
+    if (((yin >> j) & 1u) && t >= X && t < W * RW - X)
+      store_site(dst + ((y0 + j) * nx + x) * 8, s[j]);
+  }
+}
+
+template <typename T, class S, bool BIG, int AX0, int AX1>
+const void* tile2d_mode(int mode) {
+  constexpr TileShape t = tile_shape(sizeof(T) == 8, BIG);
+  switch (mode) {
+    case 0: return reinterpret_cast<const void*>(&k_tile2d<T, S, t.waves, t.rows, AX0, AX1, 0>);
+    case 1: return reinterpret_cast<const void*>(&k_tile2d<T, S, t.waves, t.rows, AX0, AX1, 1>);
+    case 2: return reinterpret_cast<const void*>(&k_tile2d<T, S, t.waves, t.rows, AX0, AX1, 2>);
+    default: return nullptr;
+  }
+}
+
+template <typename T, class S, bool BIG>
+const void* tile2d_axes(int axes_code, int mode) {
+  switch (axes_code) {
+    case 10: return tile2d_mode<T, S, BIG, 0, 1>(mode);
+    case 20: return tile2d_mode<T, S, BIG, 0, 2>(mode);
+    case 21: return tile2d_mode<T, S, BIG, 1, 2>(mode);
+    default: return nullptr;
+  }
+}
+
+template <typename T>
+const void* kernel_tile2d(bool strang, bool big, int axes_code, int mode) {
+  if (strang)
+    return big ? tile2d_axes<T, StrangStep, true>(axes_code, mode)
+               : tile2d_axes<T, StrangStep, false>(axes_code, mode);
+  return big ? tile2d_axes<T, LieStep, true>(axes_code, mode)
+             : tile2d_axes<T, LieStep, false>(axes_code, mode);
+}
+
+// the instance groups (nullptr for combinations that are not built)
+const void* kernel_tile2d_f32(bool strang, bool big, int axes_code, int mode);
+const void* kernel_tile2d_f64(bool strang, bool big, int axes_code, int mode);
+
+}  // namespace dirac
