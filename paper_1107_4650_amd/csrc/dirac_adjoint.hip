@@ -23,6 +23,7 @@
 #include "dirac_device.h"
 #include "dirac_plan.h"
 #include "dirac_sweep_impl.h"
+#include "dirac_tile2d_kernels.h"
 #include "dirac_trace.h"
 
 #include <utility>
@@ -99,6 +100,17 @@ __device__ __forceinline__ void x_transport_adj(const Site<T>& in, Site<T>& out)
 __host__ __device__ constexpr int rev_min_blocks(bool fp64, int depth) {
   return (fp64 || depth > 1) ? 1 : 2;
 }
+
+// the register tiles of the reverse steps: eight waves of two (small planes)
+// or three rows, two workgroups per compute unit with FP32 state (26
+// registers per cell and 64 KiB of movers in LDS; one with FP64 state), and
+// the waves per SIMD they are compiled for.  At 1024^2 FP32 the three-row
+// tiles take 11.5 us per reverse step in passes of 4 or 5; sixteen waves of
+// two or three rows 13.0 to 13.8, eight of four rows 13.5 or more.
+__host__ __device__ constexpr TileShape rev_tile_shape(bool big) {
+  return TileShape{8, big ? 3 : 2};
+}
+__host__ __device__ constexpr int rev_tile_waves(bool fp64) { return fp64 ? 2 : 4; }
 
 // one input row of the reverse march: psi, lambda, V and Q at this lane's
 // (wrapped or clamped) column
@@ -323,6 +335,122 @@ __global__ __launch_bounds__(256, rev_min_blocks(sizeof(T) == 8, K)) void k_reve
   }
 }
 
+// ---------------------------------------------------------------------------
+// K reverse steps of a 2-D plane in a workgroup's registers (the tile of
+// dirac_tile2d_kernels.h, with both fields and the dL/dV accumulators): W
+// waves of RW rows hold 64 columns by W * RW rows, advance them a.steps
+// reverse steps and write the cells that many steps away from the edges.  A
+// step adds its term to dL/dV, applies D^H, then T_y^H (right movers from the
+// row above, left movers from the row below; a wave's first and last row pass
+// theirs to its neighbours through LDS) and T_x^H, the arithmetic and order
+// of rev_march, so the bits are the same.
+// ---------------------------------------------------------------------------
+template <typename T, int W, int RW, int AX0, int AX1, int MODE>
+__global__ __launch_bounds__(64 * W, rev_tile_waves(sizeof(T) == 8)) void k_reverse_tile(
+    T* __restrict__ psi_out, T* __restrict__ lam_out, const T* __restrict__ psi,
+    const T* __restrict__ lam, const double* __restrict__ V, double* __restrict__ Q, TileArgs a,
+    double qscale) {
+  constexpr bool TWO = sizeof(T) == 8;
+  __shared__ MovLds<T> sr[2][2][W], sl[2][2][W];  // [buffer][psi, lambda][wave]
+  const int lane = threadIdx.x & 63;
+  const int wv = wave_in_block();
+  int64_t blk = blockIdx.x;
+  if (a.xcd_remap) blk = (blk % 8) * (gridDim.x / 8) + blk / 8;
+  if (blk >= a.ntiles) return;  // the whole workgroup
+  const int64_t nx = a.nx, ny = a.ny;
+  const int64_t seg = blk / a.nstrips, strip = blk % a.nstrips;
+  const int X = a.halo;
+  const int64_t xs = strip * (64 - 2 * X) - X, x = xs + lane;
+  const int64_t y0 = seg * (W * RW - 2 * X) - X + wv * RW;  // this wave's first row
+  const int64_t col = tile_index(x, nx, a.periodic);
+  const bool xin = x >= 0 && x < nx;
+  const bool lane_own = xin && lane >= X && lane <= 63 - X;
+  // wave-uniform: some cell of the wave lies beyond a zero wall
+  const bool walls = !a.periodic && (xs < 0 || xs + 63 >= nx || y0 < 0 || y0 + RW > ny);
+  uint32_t yin = 0, yown = 0;  // bit j: row y0 + j lies in the box / is written
+#pragma unroll
+  for (int j = 0; j < RW; ++j) {
+    const int t = wv * RW + j;
+    if (y0 + j >= 0 && y0 + j < ny) {
+      yin |= 1u << j;
+      if (t >= X && t < W * RW - X) yown |= 1u << j;
+    }
+  }
+  yin = __builtin_amdgcn_readfirstlane(yin);
+  yown = __builtin_amdgcn_readfirstlane(yown);
+  Site<T> p[RW], l[RW];
+  double v[RW], qa[RW];
+#pragma unroll
+  for (int j = 0; j < RW; ++j) {
+    const int64_t q = tile_index(y0 + j, ny, a.periodic) * nx + col;
+    load_site(psi + q * 8, p[j]);
+    load_site(lam + q * 8, l[j]);
+    v[j] = (MODE == 2) ? V[q] : 0.0;
+    qa[j] = (((yown >> j) & 1u) && lane_own) ? Q[q] : 0.0;
+  }
+  Factors f[RW];
+#pragma unroll
+  for (int j = 0; j < RW; ++j) {
+    f[j] = factors_of<MODE, TWO>(v[j], a.ph);
+    factors_fix<MODE, TWO>(f[j], v[j], a.ph);
+    f[j].ui = -f[j].ui;  // D^H
+    f[j].di = -f[j].di;
+    if (walls && (!((yin >> j) & 1u) || !xin)) {
+      zero(p[j]);
+      zero(l[j]);
+    }
+  }
+  const int below = wv > 0 ? wv - 1 : 0, above = wv < W - 1 ? wv + 1 : W - 1;
+  for (int k = 0, buf = 0; k < a.steps; ++k, buf ^= 1) {
+    Mov<T> rp[RW], lp[RW], rl[RW], ll[RW];
+#pragma unroll
+    for (int j = 0; j < RW; ++j) {
+      qa[j] = fma(qscale, im_dot(l[j], p[j]), qa[j]);
+      // formed here: left to itself the compiler sinks this sum to the end of
+      // the step and carries its FP64 operands there
+      asm volatile("" : "+v"(qa[j]));
+      apply_local<MODE>(p[j], f[j], a.ph);
+      apply_local<MODE>(l[j], f[j], a.ph);
+      Axis<AX1, T>::movers(p[j], rp[j], lp[j]);
+      Axis<AX1, T>::movers(l[j], rl[j], ll[j]);
+      // one row's FP64 temporaries at a time (interleaved rows would spill)
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    sr[buf][0][wv].put(lane, rp[0]);
+    sr[buf][1][wv].put(lane, rl[0]);
+    sl[buf][0][wv].put(lane, lp[RW - 1]);
+    sl[buf][1][wv].put(lane, ll[RW - 1]);
+    __syncthreads();
+    Mov<T> rpa, rla, lpb, llb;  // from the row above the wave's last, below its first
+    sr[buf][0][above].get(lane, rpa);
+    sr[buf][1][above].get(lane, rla);
+    sl[buf][0][below].get(lane, lpb);
+    sl[buf][1][below].get(lane, llb);
+#pragma unroll
+    for (int j = 0; j < RW; ++j) {
+      Site<T> yp, yl;
+      Axis<AX1, T>::combine(j < RW - 1 ? rp[j + 1] : rpa, j > 0 ? lp[j - 1] : lpb, yp);
+      Axis<AX1, T>::combine(j < RW - 1 ? rl[j + 1] : rla, j > 0 ? ll[j - 1] : llb, yl);
+      x_transport_adj<T, AX0>(yp, p[j]);
+      x_transport_adj<T, AX0>(yl, l[j]);
+      if (walls && (!((yin >> j) & 1u) || !xin)) {
+        zero(p[j]);
+        zero(l[j]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (!lane_own) return;
+#pragma unroll
+  for (int j = 0; j < RW; ++j) {
+    if (!((yown >> j) & 1u)) continue;
+    const int64_t q = (y0 + j) * nx + x;
+    store_site(psi_out + q * 8, p[j]);
+    store_site(lam_out + q * 8, l[j]);
+    Q[q] = qa[j];
+  }
+}
+
 // lam = [x0 > x_b] psi, Q = 0
 template <typename T>
 __global__ __launch_bounds__(256) void k_seed(const T* __restrict__ psi, T* __restrict__ lam,
@@ -453,6 +581,47 @@ static const void* rev_kernel(bool fp64, int depth, int axes_code) {
     case 3: return rev_kernel_k<float, 3>(axes_code);
     default: return nullptr;
   }
+}
+
+template <typename T, bool BIG, int AX0, int AX1>
+static const void* rev_tile_mode(int mode) {
+  constexpr TileShape t = rev_tile_shape(BIG);
+  switch (mode) {
+    case 0: return reinterpret_cast<const void*>(&k_reverse_tile<T, t.waves, t.rows, AX0, AX1, 0>);
+    case 1: return reinterpret_cast<const void*>(&k_reverse_tile<T, t.waves, t.rows, AX0, AX1, 1>);
+    case 2: return reinterpret_cast<const void*>(&k_reverse_tile<T, t.waves, t.rows, AX0, AX1, 2>);
+    default: return nullptr;
+  }
+}
+
+template <typename T, bool BIG>
+static const void* rev_tile_axes(int axes_code, int mode) {
+  switch (axes_code) {
+    case 10: return rev_tile_mode<T, BIG, 0, 1>(mode);
+    case 20: return rev_tile_mode<T, BIG, 0, 2>(mode);
+    case 21: return rev_tile_mode<T, BIG, 1, 2>(mode);
+    default: return nullptr;
+  }
+}
+
+// a.steps reverse steps in register tiles (a made for rev_tile_shape(big))
+static hipError_t launch_rev_tile(bool fp64, bool big, void* po, void* lo, const void* pi,
+                                  const void* li, const double* V, double* Q, const TileArgs& a,
+                                  double qscale, hipStream_t st) {
+  const int mode = a.ph.mode;
+  const void* fn = fp64 ? (big ? rev_tile_axes<double, true>(a.axes_code, mode)
+                               : rev_tile_axes<double, false>(a.axes_code, mode))
+                        : (big ? rev_tile_axes<float, true>(a.axes_code, mode)
+                               : rev_tile_axes<float, false>(a.axes_code, mode));
+  const TileShape t = rev_tile_shape(big);
+  const int64_t blocks = (a.ntiles + 7) / 8 * 8;
+  if (!fn || a.ntiles < 1 || blocks > INT32_MAX || 2 * a.halo >= 64 ||
+      2 * a.halo >= t.waves * t.rows)
+    return hipErrorInvalidValue;
+  TileArgs args = a;
+  void* kargs[] = {&po, &lo, const_cast<void**>(&pi), const_cast<void**>(&li),
+                   const_cast<double**>(&V), &Q, &args, &qscale};
+  return hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(64 * t.waves), kargs, 0, st);
 }
 
 static hipError_t launch_rev(bool fp64, int depth, void* po, void* lo, const void* pi,
@@ -756,6 +925,74 @@ static void rev_tiling(dl_plan p, int depth, RevArgs& a, int& blocks) {
   a.qscale = 2.0 * p->dt * dV;
 }
 
+// tiling of a register-tile pass of `steps` reverse steps; false if the tile
+// is too small for them
+static bool rev_tile_args(dl_plan p, bool big, int steps, TileArgs& a) {
+  const TileShape t = rev_tile_shape(big);
+  const int64_t w = 64 - 2 * steps, h = t.waves * t.rows - 2 * steps;
+  if (w < 16 || h < 2) return false;
+  a.nx = p->g.n[0];
+  a.ny = p->g.n[1];
+  a.periodic = (p->bc == DL_BC_PERIODIC);
+  a.steps = steps;
+  a.halo = steps;
+  a.nstrips = (a.nx + w - 1) / w;
+  a.ntiles = a.nstrips * ((a.ny + h - 1) / h);
+  a.xcd_remap = 1;
+  a.axes_code = axes_code(p->g);
+  return a.ntiles <= INT32_MAX - 8;
+}
+
+// Time of a register-tile pass in us, fitted (rms error 6-8 %) to passes of 2
+// to 10 reverse steps on planes of 128^2 to 2048^2 cells: t0 + t1 per step for
+// a compute unit's first tile, n0 + n1 per step for every further one.
+// Negative: no such pass.
+static double rev_tile_cost(dl_plan p, bool big, int steps) {
+  struct Fit { double t0, t1, n0, n1; };
+  static const Fit fits[2][2] = {{{5.1, 1.06, 4.5, 0.29}, {6.5, 1.49, 6.7, 0.66}},
+                                 {{9.5, 0.79, 16.9, -0.67}, {12.6, 1.16, 25.8, -0.35}}};
+  TileArgs a{};
+  if (!rev_tile_args(p, big, steps, a)) return -1.0;
+  const Fit& f = fits[p->fp64][big];
+  const double per_cu = static_cast<double>(a.ntiles) / p->cu_count;
+  const double more = std::max(0.0, (per_cu < 4.0 ? std::ceil(per_cu) : per_cu) - 1.0);
+  return f.t0 + f.t1 * steps + more * (f.n0 + f.n1 * steps);
+}
+
+// 2-D plans whose passes are not capped or retiled by the caller run their
+// reverse steps in register tiles, which beat the marching reverse passes on
+// every plane and both state types (per step, FP32: 1.8 against 7.9 us at
+// 128^2, 11.5 against 15.0 at 1024^2, 38.8 against 50.6 at 2048^2; FP64: 2.2
+// against 11.1, 25.9 against 37.9, 101 against 136).
+static bool rev_tile_choice(dl_plan p, int64_t nsteps, bool* big, int64_t* passes) {
+  if (p->g.ndim != 2 || p->depth_limit < kMaxDepth || p->waves_per_cu > 0 || p->seg_override > 0)
+    return false;
+  int depth = 0;
+  double best = 0.0;
+  for (int b = 0; b < 2; ++b)
+    for (int k = 1; k <= kMaxTileDepth && k <= nsteps; ++k) {
+      const double t = rev_tile_cost(p, b != 0, k);
+      if (t > 0.0 && (depth == 0 || t / k < best)) {
+        best = t / k;
+        depth = k;
+        *big = b != 0;
+      }
+    }
+  if (depth == 0) return false;
+  // an odd number of passes ends in the plan's buffers: one pass more, unless
+  // copying both states back (about 4 us, then 4.5 TB/s each) is cheaper
+  auto cost = [&](int64_t n) -> double {
+    const int d = static_cast<int>(nsteps / n);
+    const double more = static_cast<double>(nsteps % n);
+    const double t = (more > 0.0 ? more * rev_tile_cost(p, *big, d + 1) : 0.0) +
+                     (static_cast<double>(n) - more) * rev_tile_cost(p, *big, d);
+    return n % 2 == 0 ? t : t + 2.0 * (4.0 + 2.0 * static_cast<double>(p->state_bytes) / 4.5e6);
+  };
+  const int64_t n = (nsteps + depth - 1) / depth;
+  *passes = (n < nsteps && cost(n + 1) < cost(n)) ? n + 1 : n;
+  return true;
+}
+
 static int check_adjoint_plan(dl_plan p) {
   int rc = check_live(p);
   if (rc) return rc;
@@ -840,6 +1077,22 @@ extern "C" int dl_grad_step(dl_plan p, void* psi, void* lam, const double* V, do
   void* pb = p->tmp;
   void* lb = p->tmp2;
   int64_t left = nsteps;
+  bool big = false;
+  int64_t passes = 0;
+  if (rev_tile_choice(p, nsteps, &big, &passes)) {  // passes of d + 1 steps, then of d
+    for (int64_t i = 0; i < passes; ++i) {
+      TileArgs a{};
+      const int d = static_cast<int>(nsteps / passes + (i < nsteps % passes ? 1 : 0));
+      if (!rev_tile_args(p, big, d, a)) return set_error(DL_ERR_STATE, "reverse tile too small");
+      a.ph = ph;
+      hipError_t e = launch_rev_tile(p->fp64, big, pb, lb, pa, la, V, Q, a,
+                                     2.0 * p->dt * (p->dx * p->dx), st);
+      if (e != hipSuccess) return set_hip_error(e, "reverse sweep launch");
+      std::swap(pa, pb);
+      std::swap(la, lb);
+    }
+    left = 0;
+  }
   for (int d = dmax; d >= 1; --d) {
     if (left < d) continue;
     RevArgs a{};
