@@ -310,12 +310,13 @@ int dl_batch_create(dl_plan *out, const dl_grid *grids, const double *dx,
 /* Advance instance k in place by nsteps[k] steps: psi[k] (device), V[k]
  * (device or NULL).  The arrays psi, V and nsteps are HOST arrays of length
  * count.  Each instance's result is bit-identical to dl_step on a plan with
- * the same parameters.  1-D instances of up to 4096 cells, or of up to four
- * times an even share of the batch's cells per compute unit if that is more
+ * the same parameters.  1-D instances of up to 4096 cells, or of up to an even
+ * share of the batch's cells per compute unit if that is more
  * (at most 2^20 cells), run whole in a
  * persistent kernel (a workgroup carries a bin of such lines through all of
  * their steps); the others advance by one launch per pass of fused steps over
- * a table of tiles; the two run concurrently (a second stream forked from and
+ * a table of tiles (register tiles, as in dl_step, until dl_batch_set or a
+ * tuning chooses marching passes); the two run concurrently (a second stream forked from and
  * joined to `stream`).  Synchronises `stream` before it rewrites the
  * descriptors of the previous call. */
 int dl_batch_step(dl_plan b, void *const *psi, const double *const *V,
@@ -360,8 +361,8 @@ int dl_plan_set_depth(dl_plan p, int depth);
  * batch) and [16] their threads. */
 int dl_plan_info(dl_plan p, int64_t *info, int n);
 
-/* Batch tiling: seg_len >= 1 rows per 2-D march segment of every size class,
- * depth in 1 .. the batch's largest (5, less on periodic boxes of few rows)
+/* Batch tiling: marching passes with seg_len >= 1 rows per 2-D march segment of
+ * every size class, depth in 1 .. the batch's largest (5, less on periodic boxes of few rows)
  * fused steps per pass.  Results stay bit-identical. */
 int dl_batch_set(dl_plan b, int seg_len, int depth);
 
@@ -371,14 +372,16 @@ int dl_batch_set(dl_plan b, int seg_len, int depth);
  * fused per pass (3 .. the largest; the strip width 64 - 2 depth follows),
  * then the march segment length (16 .. 512 rows) of each 2-D size class
  * present (class = floor(log2(rows))), then the workgroup size of the lines
- * kernel (256 .. 1024 threads, 512 with complex128).  Each candidate runs
+ * kernel (256 .. 1024 threads, 512 with complex128); the marching passes so
+ * tuned are kept only if they beat the register tiles.  Each candidate runs
  * `trials` passes after a warm-up and is scored by its time per step.
  * chosen (HOST, may be NULL) receives 3 ints: the depth, the lines workgroup
  * size and the segment length of the largest size class (0 if none).
  * Allocates a scratch copy of all states for the call; synchronises
  * `stream`.  When the environment variable LIBDIRAC_TUNE_CACHE names a file,
  * appends one line per setting, "dirac-batch <c64|c128> <key> <value>" with
- * key 2d-depth, 2d-rows<class>-seg or 1d-threads; dl_batch_create reads that
+ * key 2d-depth, 2d-march (1: marching passes, 2: register tiles),
+ * 2d-rows<class>-seg or 1d-threads; dl_batch_create reads that
  * file and applies the settings whose dtype (and size class) match. */
 int dl_batch_autotune(dl_plan b, void *const *psi, const double *const *V, int trials,
                       int *chosen, void *stream);

@@ -8,10 +8,14 @@
 //     the passes, and the line's two buffers (at most a few MiB) stay in the
 //     caches, so HBM sees a line at the start and at the end only;
 //   * 2-D instances (and 1-D instances too long for a bin) advance pass by
-//     pass: one launch per pass of D fused steps over a flat table of tiles
-//     (instance, strip of 64 - 2D columns, march segment), longest first, so
-//     that the in-order workgroup dispatch is a longest-processing-time list
-//     schedule;
+//     pass in the register tiles of the single plans (k_batch_tile): one
+//     launch per pass over a flat table of tiles, every instance splitting its
+//     steps evenly over its passes;
+//   * once the caller sets march segments and a depth (dl_batch_set, or a
+//     tuning that found them faster), those instances march instead: one
+//     launch per pass of D fused steps over a table of tiles (instance, strip
+//     of 64 - 2D columns, march segment), longest first, so that the in-order
+//     workgroup dispatch is a longest-processing-time list schedule;
 //   * the two run concurrently: the lines kernel on a second stream forked
 //     from the caller's and joined before a last kernel that moves every state
 //     whose pass count was odd from the batch's buffer back to the caller's.
@@ -38,6 +42,7 @@
 
 #include "dirac_plan.h"
 #include "dirac_sweep_impl.h"
+#include "dirac_tile2d_kernels.h"
 #include "dirac_trace.h"
 
 namespace dirac {
@@ -50,6 +55,8 @@ struct BatchInst {
   int64_t nsteps;     // per call
   int64_t passes;     // per call: passes of the batch's depth ...
   int64_t rem;        // ... then this many single steps
+  int64_t total;      // per call: passes in all (register tiles: of nsteps / total steps,
+                      // the first nsteps % total of them one more)
   int64_t words;      // state size in 16-byte words
   int periodic;
   int axes_code;
@@ -129,6 +136,100 @@ __global__ __launch_bounds__(256) void k_batch(const BatchInst* __restrict__ ins
   }
 }
 
+// `steps` steps of a strip of a 1-D instance (one_row with the count read at
+// run time; lanes halo .. 63 - halo are written, steps <= halo)
+template <typename T, int AX, int MODE>
+__device__ __forceinline__ void line_steps(const T* __restrict__ src, T* __restrict__ dst,
+                                           const double* __restrict__ V, const TileArgs& a,
+                                           int64_t xs, int lane) {
+  constexpr bool TWO = sizeof(T) == 8;
+  const Lanes c = lanes_of(a.nx, a.periodic, xs, lane);
+  const bool walls = !a.periodic && !c.inside;
+  Site<T> m;
+  load_site(src + c.col * 8, m);
+  if (c.out) zero(m);
+  const double v = (MODE == 2) ? V[c.col] : 0.0;
+  Factors fd = factors_of<MODE, TWO>(v, a.ph);
+  factors_fix<MODE, TWO>(fd, v, a.ph);
+  const typename Stored<T>::type f = Stored<T>::of(fd);
+  for (int k = 0; k < a.steps; ++k) {
+    Site<T> o;
+    x_transport_inner<T, AX>(m, o);
+    m = o;
+    if (walls) zero(m);
+    apply_local<MODE>(m, f, a.ph);
+  }
+  if (c.inside && lane >= a.halo && lane <= 63 - a.halo) store_site(dst + c.x * 8, m);
+}
+
+// One launch advances every instance off the lines kernel that is still due by
+// one pass in register tiles (workgroup blk: tile tiles[blk], `strip` and the
+// tile row `jb` of a 2-D instance, or W strips from `strip` on of a 1-D one).
+// Instance I does its index-th pass of nsteps / total steps, the first
+// nsteps % total passes one more, none more than halo.  Bound as the single
+// plans' register tiles are; 32 mixed instances of 7.2 million cells take 230
+// us per pass of 7 to 8 steps (marching passes 260 us per 5 steps).
+template <typename T, bool BIG>
+__global__ __launch_bounds__(64 * tile_shape(sizeof(T) == 8, BIG).waves,
+                             tile2d_waves(sizeof(T) == 8, tile_shape(sizeof(T) == 8, BIG).rows))
+void k_batch_tile(const BatchInst* __restrict__ insts, const BatchTile* __restrict__ tiles,
+                  int ntiles, int64_t index, int halo) {
+  constexpr TileShape t = tile_shape(sizeof(T) == 8, BIG);
+  constexpr int W = t.waves, RW = t.rows;
+  __shared__ MovLds<T> sr[2][W], sl[2][W];
+  const int lane = threadIdx.x & 63;
+  const int wv = wave_in_block();
+  const int per = static_cast<int>(gridDim.x) / 8;  // XCD-contiguous runs of tiles
+  const int blk = (static_cast<int>(blockIdx.x) % 8) * per + static_cast<int>(blockIdx.x) / 8;
+  if (blk >= ntiles) return;  // the whole workgroup
+  const BatchTile tl = tiles[blk];
+  const BatchInst& I = insts[tl.inst];
+  if (index >= I.total) return;
+  const int parity = static_cast<int>(index & 1);
+  const T* src = static_cast<const T*>(parity ? I.b : I.a);
+  T* dst = static_cast<T*>(parity ? I.a : I.b);
+  TileArgs a{};
+  a.nx = I.nx;
+  a.ny = I.ny;
+  a.periodic = I.periodic;
+  a.steps = static_cast<int>(I.nsteps / I.total) + (index < I.nsteps % I.total ? 1 : 0);
+  a.halo = halo;
+  a.ph = I.ph;
+  const double* V = I.V;
+  auto line = [&](auto ax) {
+    constexpr int AX = decltype(ax)::value;
+    const int64_t xs = (int64_t(tl.strip) + wv) * (64 - 2 * halo) - halo;
+    if (xs >= I.nx) return;
+    if (a.ph.mode == 0)
+      line_steps<T, AX, 0>(src, dst, V, a, xs, lane);
+    else if (a.ph.mode == 1)
+      line_steps<T, AX, 1>(src, dst, V, a, xs, lane);
+    else
+      line_steps<T, AX, 2>(src, dst, V, a, xs, lane);
+  };
+  auto plane = [&](auto ax0, auto ax1) {
+    constexpr int AX0 = decltype(ax0)::value, AX1 = decltype(ax1)::value;
+    if (a.ph.mode == 0)
+      tile2d<T, LieStep, W, RW, AX0, AX1, 0>(src, dst, V, a, lane, wv, tl.strip, tl.jb, sr, sl);
+    else if (a.ph.mode == 1)
+      tile2d<T, LieStep, W, RW, AX0, AX1, 1>(src, dst, V, a, lane, wv, tl.strip, tl.jb, sr, sl);
+    else
+      tile2d<T, LieStep, W, RW, AX0, AX1, 2>(src, dst, V, a, lane, wv, tl.strip, tl.jb, sr, sl);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  switch (I.axes_code) {
+    case 0: line(I0{}); break;
+    case 1: line(I1{}); break;
+    case 2: line(I2{}); break;
+    case 10: plane(I0{}, I1{}); break;
+    case 20: plane(I0{}, I2{}); break;
+    case 21: plane(I1{}, I2{}); break;
+    default: break;
+  }
+}
+
 // Whole 1-D instances in one workgroup each, all steps in one launch.
 // Workgroup b advances the lines ids[bin_start[b] .. bin_start[b + 1]) one
 // after the other; for each line it runs the line's passes of the batch's
@@ -159,8 +260,7 @@ __global__ __launch_bounds__(line_threads_max<T>()) void k_batch_lines(const Bat
     a.periodic = I.periodic;
     a.ph = I.ph;
     const int64_t nstrips = (I.nx + sw - 1) / sw;
-    const int64_t total = I.passes + I.rem;
-    for (int64_t pass = 0; pass < total; ++pass) {
+    for (int64_t pass = 0; pass < I.total; ++pass) {
       const int parity = static_cast<int>(pass & 1);
       const T* src = static_cast<const T*>(parity ? I.b : I.a);
       T* dst = static_cast<T*>(parity ? I.a : I.b);
@@ -183,7 +283,7 @@ __global__ __launch_bounds__(256) void k_batch_fix(const BatchInst* __restrict__
   const int k = static_cast<int>(blockIdx.x / kFixBlocks);
   const int j = static_cast<int>(blockIdx.x % kFixBlocks);
   const BatchInst& I = insts[k];
-  if (((I.passes + I.rem) & 1) == 0) return;
+  if ((I.total & 1) == 0) return;
   const uint4* __restrict__ src = static_cast<const uint4*>(I.b);
   uint4* __restrict__ dst = static_cast<uint4*>(I.a);
   for (int64_t w = int64_t(j) * 256 + threadIdx.x; w < I.words; w += int64_t(kFixBlocks) * 256)
@@ -214,6 +314,9 @@ struct Batch {
   bool use_graph = true;
   int depth = 1;                    // steps fused per pass
   int depth_cap = 5;                // largest depth the instances allow
+  bool tiles = true;                // 2-D instances and long lines: register tiles, else march
+  bool tile_big = false;            // ... their shape and largest depth
+  int tile_depth = 1;
   int seg_of[kMaxClass] = {};       // march segment length per 2-D size class
   int line_threads = kLineThreadsDefault;
   int cu_count = 256;
@@ -245,13 +348,15 @@ int size_class(int64_t rows) {
 int64_t cells_of(const dl_grid& g) { return g.n[0] * (g.ndim > 1 ? g.n[1] : 1); }
 
 // instances advanced whole by the lines kernel: 1-D instances whose cell
-// count is at most four times an even share of the batch per compute unit
-// (and at most 2^20 cells), so that no bin outlasts the tiled passes
+// count is at most an even share of the batch per compute unit (and at most
+// 2^20 cells), so that no bin outlasts the tiled passes: a line takes 0.7 ns
+// per cell and step in its workgroup, the tiles of all 2-D instances 3.4 ps,
+// so a line of 1.26 shares ends with them.  Longer lines join the tiles.
 void choose_lines(Batch& B) {
   int64_t total = 0;
   for (int k = 0; k < B.count; ++k) total += cells_of(B.grids[k]);
   const int64_t limit =
-      std::min<int64_t>(int64_t(1) << 20, std::max<int64_t>(4096, 4 * total / B.cu_count));
+      std::min<int64_t>(int64_t(1) << 20, std::max<int64_t>(4096, total / B.cu_count));
   for (int k = 0; k < B.count; ++k) {
     const dl_grid& g = B.grids[k];
     B.h_insts[k].line = (g.ndim == 1 && g.n[0] <= limit) ? 1 : 0;
@@ -288,6 +393,48 @@ std::vector<BatchTile> make_tiles(const Batch& B) {
   });
   two.insert(two.end(), one.begin(), one.end());
   return two;
+}
+
+// the register tiles of the instances off the lines kernel for passes of up
+// to `halo` steps: count only, or the table (2-D tiles instance by instance,
+// row by row, so that neighbours share halos in an XCD's L2; lines last)
+int64_t register_tiles(const Batch& B, bool big, int halo, std::vector<BatchTile>* out) {
+  const TileShape t = tile_shape(B.fp64, big);
+  const int64_t w = 64 - 2 * halo, h = t.waves * t.rows - 2 * halo;
+  int64_t n = 0;
+  for (int two = 1; two >= 0; --two)
+    for (int k = 0; k < B.count; ++k) {
+      const dl_grid& g = B.grids[k];
+      if (B.h_insts[k].line || (g.ndim == 2) != (two == 1)) continue;
+      const int64_t nstrips = (g.n[0] + w - 1) / w;
+      const int64_t nseg = two ? (g.n[1] + h - 1) / h : 1;
+      const int64_t step = two ? 1 : t.waves;  // a workgroup takes W strips of a line
+      n += nseg * ((nstrips + step - 1) / step);
+      if (!out) continue;
+      for (int64_t q = 0; q < nseg; ++q)
+        for (int64_t s = 0; s < nstrips; s += step)
+          out->push_back(BatchTile{k, static_cast<int>(s), static_cast<int>(q), 0, 1});
+    }
+  return n;
+}
+
+// shape and depth of the register-tile passes: the least fitted time per step
+void choose_register_tiles(Batch& B) {
+  double best = 0.0;
+  B.tile_depth = 0;
+  for (int big = 0; big < 2; ++big)
+    for (int k = 1; k <= kMaxTileDepth; ++k) {
+      const TileShape t = tile_shape(B.fp64, big != 0);
+      if (64 - 2 * k < 16 || t.waves * t.rows - 2 * k < 8) break;
+      const double us = tile_time(B.fp64, false, big != 0, k,
+                                  static_cast<double>(register_tiles(B, big != 0, k, nullptr)),
+                                  B.cu_count) / k;
+      if (B.tile_depth == 0 || us < best) {
+        best = us;
+        B.tile_depth = k;
+        B.tile_big = big != 0;
+      }
+    }
 }
 
 // bins of lines: as many as the lines' share of the cells asks for (twice
@@ -336,7 +483,15 @@ void drop_graph(Batch& B) {
 
 // rebuild the tile table and the line bins for the current tuning
 int upload_layout(Batch& B) {
-  std::vector<BatchTile> t = make_tiles(B);
+  std::vector<BatchTile> t;
+  if (B.tiles) {
+    choose_register_tiles(B);
+    if (register_tiles(B, B.tile_big, B.tile_depth, nullptr) > INT32_MAX / 2)
+      return set_error(DL_ERR_ARG, "batch too large");
+    register_tiles(B, B.tile_big, B.tile_depth, &t);
+  } else {
+    t = make_tiles(B);
+  }
   if (t.size() > B.tiles_cap) {
     if (B.d_tiles) (void)hipFree(B.d_tiles);
     B.d_tiles = nullptr;
@@ -413,6 +568,25 @@ hipError_t launch_lines_t(const Batch& B, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <typename T, bool BIG>
+hipError_t launch_tiles_t(const Batch& B, int64_t index, hipStream_t st) {
+  constexpr TileShape t = tile_shape(sizeof(T) == 8, BIG);
+  const unsigned blocks = static_cast<unsigned>((B.ntiles + 7) / 8 * 8);
+  hipLaunchKernelGGL((k_batch_tile<T, BIG>), dim3(blocks), dim3(64 * t.waves), 0, st, B.d_insts,
+                     B.d_tiles, B.ntiles, index, B.tile_depth);
+  return hipGetLastError();
+}
+
+// the index-th register-tile pass
+hipError_t launch_tiles(const Batch& B, int64_t index, hipStream_t st) {
+  if (B.ntiles == 0) return hipSuccess;
+  if (B.fp64)
+    return B.tile_big ? launch_tiles_t<double, true>(B, index, st)
+                      : launch_tiles_t<double, false>(B, index, st);
+  return B.tile_big ? launch_tiles_t<float, true>(B, index, st)
+                    : launch_tiles_t<float, false>(B, index, st);
+}
+
 // phase 0: the index-th pass of the batch's depth; phase 1: the index-th
 // single step of the remainder
 hipError_t launch_pass(const Batch& B, int phase, int64_t index, hipStream_t st) {
@@ -435,6 +609,12 @@ int prepare(Batch& B, void* const* psi, const double* const* V, const int64_t* n
     I.nsteps = nsteps[k];
     I.passes = nsteps[k] / B.depth;
     I.rem = nsteps[k] % B.depth;
+    I.total = I.passes + I.rem;
+    if (B.tiles && !I.line) {
+      // an even number of passes ends in the caller's buffer
+      I.total = (nsteps[k] + B.tile_depth - 1) / B.tile_depth;
+      if (I.total % 2 == 1 && nsteps[k] > I.total) ++I.total;
+    }
     I.ph = make_phase(B.grids[k].ndim, B.dt[k], B.c[k], B.m[k], phase_mode(B.m[k], I.V), B.fp64);
   }
   hipError_t e = hipMemcpyAsync(B.d_insts, B.h_insts.data(), B.count * sizeof(BatchInst),
@@ -443,9 +623,10 @@ int prepare(Batch& B, void* const* psi, const double* const* V, const int64_t* n
 }
 
 // the launches of one call on stream cs: the lines kernel on the side stream
-// (forked from cs and joined back), the tiled passes on cs, then the copy of
-// odd-parity states
-hipError_t enqueue_call(Batch& B, int64_t pmax, int64_t rmax, bool lines, hipStream_t cs) {
+// (forked from cs and joined back), the tiled passes on cs, then (fix) the copy
+// of odd-parity states
+hipError_t enqueue_call(Batch& B, int64_t pmax, int64_t rmax, bool lines, bool fix,
+                        hipStream_t cs) {
   hipError_t e = hipSuccess;
   if (lines) {
     if ((e = hipEventRecord(B.ev_fork, cs)) != hipSuccess) return e;
@@ -454,10 +635,12 @@ hipError_t enqueue_call(Batch& B, int64_t pmax, int64_t rmax, bool lines, hipStr
     if (e != hipSuccess) return e;
     if ((e = hipEventRecord(B.ev_join, B.side)) != hipSuccess) return e;
   }
-  for (int64_t q = 0; q < pmax && e == hipSuccess; ++q) e = launch_pass(B, 0, q, cs);
+  for (int64_t q = 0; q < pmax && e == hipSuccess; ++q)
+    e = B.tiles ? launch_tiles(B, q, cs) : launch_pass(B, 0, q, cs);
   for (int64_t r = 0; r < rmax && e == hipSuccess; ++r) e = launch_pass(B, 1, r, cs);
   if (e != hipSuccess) return e;
   if (lines && (e = hipStreamWaitEvent(cs, B.ev_join, 0)) != hipSuccess) return e;
+  if (!fix) return hipSuccess;
   hipLaunchKernelGGL(k_batch_fix, dim3(static_cast<unsigned>(B.count) * kFixBlocks), dim3(256), 0,
                      cs, B.d_insts);
   return hipGetLastError();
@@ -466,22 +649,25 @@ hipError_t enqueue_call(Batch& B, int64_t pmax, int64_t rmax, bool lines, hipStr
 // run every instance through its steps (descriptors already uploaded)
 int run(Batch& B, const int64_t* nsteps, hipStream_t st) {
   int64_t pmax = 0, rmax = 0;
-  bool lines = false;
+  bool lines = false, fix = false;
   for (int k = 0; k < B.count; ++k) {
+    fix = fix || B.h_insts[k].total % 2 == 1;
     if (B.h_insts[k].line) {
       lines = lines || nsteps[k] > 0;
+    } else if (B.tiles) {
+      pmax = std::max(pmax, B.h_insts[k].total);
     } else {
       pmax = std::max(pmax, nsteps[k] / B.depth);
       rmax = std::max(rmax, nsteps[k] % B.depth);
     }
   }
   if (!B.use_graph) {
-    hipError_t e = enqueue_call(B, pmax, rmax, lines, st);
+    hipError_t e = enqueue_call(B, pmax, rmax, lines, fix, st);
     return e == hipSuccess ? DL_OK : set_hip_error(e, "batch launch");
   }
   // the kernels read pointers and counts from the device descriptor table, so
   // one captured graph serves every call of the same shape
-  const int64_t key[4] = {pmax, rmax, lines ? 1 : 0, B.version};
+  const int64_t key[4] = {pmax, rmax, (lines ? 1 : 0) + (fix ? 2 : 0), B.version};
   if (!B.graph || !std::equal(key, key + 4, B.gkey)) {
     drop_graph(B);
     if (!B.cap_stream) {
@@ -491,7 +677,7 @@ int run(Batch& B, const int64_t* nsteps, hipStream_t st) {
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamBeginCapture(B.cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return set_hip_error(e, "begin capture");
-    hipError_t e2 = enqueue_call(B, pmax, rmax, lines, B.cap_stream);
+    hipError_t e2 = enqueue_call(B, pmax, rmax, lines, fix, B.cap_stream);
     e = hipStreamEndCapture(B.cap_stream, &g);
     if (e2 != hipSuccess || e != hipSuccess) {
       if (g) (void)hipGraphDestroy(g);
@@ -525,7 +711,8 @@ void free_batch(Batch* B) {
 }
 
 // ---- tuning cache: one "dirac-batch <dtype> <key> <value>" line per setting
-// keys: "2d-depth" (steps per pass), "2d-rows<class>-seg" (segment length of
+// keys: "2d-depth" (steps per pass), "2d-march" (1: marching passes, 2: register
+// tiles), "2d-rows<class>-seg" (segment length of
 // the 2-D size class), "1d-threads" (lines kernel workgroup size)
 const char* dtype_name(const Batch& B) { return B.fp64 ? "c128" : "c64"; }
 
@@ -544,6 +731,8 @@ void apply_cache(Batch& B) {
     int cls = -1;
     if (std::strcmp(key, "2d-depth") == 0) {
       B.depth = std::min(v, B.depth_cap);
+    } else if (std::strcmp(key, "2d-march") == 0) {
+      B.tiles = v != 1;
     } else if (std::strcmp(key, "1d-threads") == 0) {
       if (v % 64 == 0 && v <= 1024) B.line_threads = v;
     } else if (std::sscanf(key, "2d-rows%d-seg", &cls) == 1 && cls >= 0 && cls < kMaxClass) {
@@ -559,6 +748,7 @@ void append_cache(const Batch& B, const std::vector<int>& classes) {
   FILE* f = std::fopen(path, "a");
   if (!f) return;
   std::fprintf(f, "dirac-batch %s 2d-depth %d\n", dtype_name(B), B.depth);
+  std::fprintf(f, "dirac-batch %s 2d-march %d\n", dtype_name(B), B.tiles ? 2 : 1);
   for (int cls : classes)
     std::fprintf(f, "dirac-batch %s 2d-rows%d-seg %d\n", dtype_name(B), cls, B.seg_of[cls]);
   std::fprintf(f, "dirac-batch %s 1d-threads %d\n", dtype_name(B), B.line_threads);
@@ -758,8 +948,14 @@ extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* cons
     *ms_per_step = ms / (double(trials) * B.depth);
     return DL_OK;
   };
+  // 0. register tiles; the steps below tune the marching passes
+  double tiles_t = 0;
+  B.tiles = true;
+  rc = score(&tiles_t);
+  B.tiles = false;
+  double march_t = 1e300;
   // 1. the pass depth
-  {
+  if (rc == DL_OK) {
     int best = B.depth;
     double best_t = 1e300;
     for (int d = std::min(3, B.depth_cap); d <= B.depth_cap && rc == DL_OK; ++d) {
@@ -772,6 +968,7 @@ extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* cons
       }
     }
     B.depth = best;
+    march_t = std::min(march_t, best_t);
   }
   // 2. the segment length of each 2-D size class, largest class first
   std::vector<int> classes;
@@ -796,7 +993,9 @@ extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* cons
       }
     }
     B.seg_of[cls] = best;
+    march_t = std::min(march_t, best_t);
   }
+  B.tiles = tiles_t <= march_t;
   // 3. the lines kernel's workgroup size
   bool any_line = false;
   for (const BatchInst& I : B.h_insts) any_line = any_line || I.line;
@@ -840,6 +1039,7 @@ extern "C" int dl_batch_set(dl_plan b, int seg_len, int depth) {
     return set_error(DL_ERR_ARG, "depth outside 1 .. the batch's largest depth");
   for (int& s : B.seg_of) s = seg_len;
   B.depth = depth;
+  B.tiles = false;
   if (b->dry) return DL_OK;
   return upload_layout(B);
 }

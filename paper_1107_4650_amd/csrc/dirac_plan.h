@@ -119,6 +119,7 @@ int phase_mode(double m, const double* V);
 int axes_code(const dl_grid& g);
 void make_tiling(const dl_grid& g, int64_t target, int seg_override, SweepArgs& a, int& blocks,
                  int strip_width);
+double tile_time(bool fp64, bool strang, bool big, int halo, double tiles, int cu_count);
 int check_live(dl_plan p);
 int check_state_ptr(const void* ptr, const char* name);
 int check_f64_ptr(const void* ptr, const char* name, bool nullable);

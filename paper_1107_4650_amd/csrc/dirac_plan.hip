@@ -142,6 +142,23 @@ void make_tiling(const dl_grid& g, int64_t target, int seg_override, SweepArgs& 
   a.axes_code = axes_code(g);
 }
 
+// Time of a register-tile pass in us, from fits (rms error 5-8 %) to the
+// passes of 1 to 12 steps on planes of 128^2 to 4096^2 cells: a compute unit's
+// first tile takes t0 + t1 per transport pair, every further one n0 + n1 per
+// transport pair.
+double tile_time(bool fp64, bool strang, bool big, int halo, double tiles, int cu_count) {
+  struct Fit { double t0, t1, n0, n1; };
+  static const Fit fits[2][2][2] = {  // [fp64][strang][big]
+      {{{5.0, 0.74, 4.2, 0.28}, {7.1, 1.07, 6.4, 0.51}},
+       {{5.1, 0.63, 5.2, 0.11}, {6.5, 1.04, 6.0, 0.43}}},
+      {{{9.3, 0.79, 15.5, 0.0}, {11.1, 1.0, 10.9, 0.17}},
+       {{8.8, 0.79, 14.8, 0.0}, {11.8, 0.89, 10.4, 0.18}}}};
+  const Fit& f = fits[fp64][strang][big];
+  const double per_cu = tiles / cu_count;
+  const double more = std::max(0.0, (per_cu < 4.0 ? std::ceil(per_cu) : per_cu) - 1.0);
+  return f.t0 + f.t1 * halo + more * (f.n0 + f.n1 * halo);
+}
+
 // 3-D tiling: strips of `strip_width` x cells by blocks of `ty` y rows, march
 // segments along z.  A tile (a wave, or with per_block = 1 a workgroup) of a
 // segment of H planes runs H + halo plane iterations; with `target` tiles
@@ -241,23 +258,11 @@ static bool tile_args(dl_plan p, bool big, int steps, TileArgs& a) {
   return a.ntiles <= INT32_MAX - 8;
 }
 
-// Time of a register-tile pass in us, from fits (rms error 5-8 %) to the
-// passes of 1 to 12 steps on planes of 128^2 to 4096^2 cells: a tile alone on
-// its compute unit takes t0 + t1 per transport pair, every further tile of
-// the compute unit n0 + n1 per transport pair.  Negative: no such pass.
+// fitted time of a register-tile pass in us; negative: no such pass
 static double tile_cost(dl_plan p, bool big, int steps) {
-  struct Fit { double t0, t1, n0, n1; };
-  static const Fit fits[2][2][2] = {  // [fp64][strang][big]
-      {{{5.0, 0.74, 4.2, 0.28}, {7.1, 1.07, 6.4, 0.51}},
-       {{5.1, 0.63, 5.2, 0.11}, {6.5, 1.04, 6.0, 0.43}}},
-      {{{9.3, 0.79, 15.5, 0.0}, {11.1, 1.0, 10.9, 0.17}},
-       {{8.8, 0.79, 14.8, 0.0}, {11.8, 0.89, 10.4, 0.18}}}};
   TileArgs a{};
   if (!tile_args(p, big, steps, a)) return -1.0;
-  const Fit& f = fits[p->fp64][p->strang][big];
-  const double per_cu = static_cast<double>(a.ntiles) / p->cu_count;
-  const double more = std::max(0.0, (per_cu < 4.0 ? std::ceil(per_cu) : per_cu) - 1.0);
-  return f.t0 + f.t1 * a.halo + more * (f.n0 + f.n1 * a.halo);
+  return tile_time(p->fp64, p->strang, big, a.halo, static_cast<double>(a.ntiles), p->cu_count);
 }
 
 // 2-D plans whose passes are not capped or retiled by the caller run in

@@ -60,18 +60,15 @@ __device__ __forceinline__ int64_t tile_index(int64_t r, int64_t n, int periodic
   return r;
 }
 
+// the pass on tile (strip, seg) of the plane: strips of 64 - 2 a.halo written
+// columns, tile rows of W * RW - 2 a.halo
 template <typename T, class S, int W, int RW, int AX0, int AX1, int MODE>
-__global__ __launch_bounds__(64 * W, tile2d_waves(sizeof(T) == 8, RW)) void k_tile2d(
-    const T* __restrict__ src, T* __restrict__ dst, const double* __restrict__ V, TileArgs a) {
+__device__ __forceinline__ void tile2d(const T* __restrict__ src, T* __restrict__ dst,
+                                       const double* __restrict__ V, const TileArgs& a, int lane,
+                                       int wv, int64_t strip, int64_t seg,
+                                       MovLds<T> (&sr)[2][W], MovLds<T> (&sl)[2][W]) {
   constexpr bool TWO = sizeof(T) == 8;
-  __shared__ MovLds<T> sr[2][W], sl[2][W];  // right movers up, left movers down
-  const int lane = threadIdx.x & 63;
-  const int wv = wave_in_block();
-  int64_t blk = blockIdx.x;
-  if (a.xcd_remap) blk = (blk % 8) * (gridDim.x / 8) + blk / 8;
-  if (blk >= a.ntiles) return;  // the whole workgroup
   const int64_t nx = a.nx, ny = a.ny;
-  const int64_t seg = blk / a.nstrips, strip = blk % a.nstrips;
   const int X = a.halo;  // transports per axis of the pass
   const int64_t x = strip * (64 - 2 * X) - X + lane;
   const int64_t y0 = seg * (W * RW - 2 * X) - X + wv * RW;  // this wave's first row
@@ -157,6 +154,17 @@ __global__ __launch_bounds__(64 * W, tile2d_waves(sizeof(T) == 8, RW)) void k_ti
     if (((yin >> j) & 1u) && t >= X && t < W * RW - X)
       store_site(dst + ((y0 + j) * nx + x) * 8, s[j]);
   }
+}
+
+template <typename T, class S, int W, int RW, int AX0, int AX1, int MODE>
+__global__ __launch_bounds__(64 * W, tile2d_waves(sizeof(T) == 8, RW)) void k_tile2d(
+    const T* __restrict__ src, T* __restrict__ dst, const double* __restrict__ V, TileArgs a) {
+  __shared__ MovLds<T> sr[2][W], sl[2][W];  // right movers up, left movers down
+  int64_t blk = blockIdx.x;
+  if (a.xcd_remap) blk = (blk % 8) * (gridDim.x / 8) + blk / 8;
+  if (blk >= a.ntiles) return;  // the whole workgroup
+  tile2d<T, S, W, RW, AX0, AX1, MODE>(src, dst, V, a, threadIdx.x & 63, wave_in_block(),
+                                      blk % a.nstrips, blk / a.nstrips, sr, sl);
 }
 
 template <typename T, class S, bool BIG, int AX0, int AX1>
