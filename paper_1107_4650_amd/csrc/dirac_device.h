@@ -547,11 +547,69 @@ struct FieldFactors {
   double ax, ay, az;  // At
 };
 
-template <bool TWO>
+// cos(A) and sin(A)/A as functions of z = A^2 <= kCosSincMax (A <= 12.5), for
+// the FP32 state: Taylor series at x = A/16 <= pi/4 (to r^15 and r^16,
+// truncation below 1e-16), then the angle doubled four times:
+// sinc 2x = sinc x cos x and cos 2x = 1 - 2 sin^2 x.  No square root, division
+// or quadrant: 31 FP64 operations in one block against 82 with them, with
+// errors below 6e-15 (the general form with sincos_fast<1>: 2.1e-14).
+constexpr double kCosSincMax = 156.8;  // (A/16)^2 below (pi/4)^2
+
+__device__ __forceinline__ void cos_sinc(double z, double* c_out, double* s_out) {
+  double w = 0.00390625 * z;               // x^2
+  double s = -1.0 / 1307674368000.0;       // 1/15!
+  s = fma(s, w, 1.0 / 6227020800.0);       // 1/13!
+  s = fma(s, w, -1.0 / 39916800.0);        // 1/11!
+  s = fma(s, w, 1.0 / 362880.0);           // 1/9!
+  s = fma(s, w, -1.0 / 5040.0);            // 1/7!
+  s = fma(s, w, 1.0 / 120.0);              // 1/5!
+  s = fma(s, w, -1.0 / 6.0);               // 1/3!
+  s = fma(s, w, 1.0);
+  double c = 1.0 / 20922789888000.0;       // 1/16!
+  c = fma(c, w, -1.0 / 87178291200.0);     // 1/14!
+  c = fma(c, w, 1.0 / 479001600.0);        // 1/12!
+  c = fma(c, w, -1.0 / 3628800.0);         // 1/10!
+  c = fma(c, w, 1.0 / 40320.0);            // 1/8!
+  c = fma(c, w, -1.0 / 720.0);             // 1/6!
+  c = fma(c, w, 1.0 / 24.0);               // 1/4!
+  c = fma(c, w, -0.5);                     // 1/2!
+  c = fma(c, w, 1.0);
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const double q = s * s * w;            // sin^2 of the current angle
+    s = s * c;
+    c = fma(-2.0, q, 1.0);
+    w = 4.0 * w;
+  }
+  *s_out = s;
+  *c_out = c;
+}
+
+// the same for any z, out of line
+__device__ __attribute__((noinline)) double2 cos_sinc_far(double z) {
+  const double A = sqrt(z);
+  double2 r;
+  double sA;
+  sincos_any<1>(A, &sA, &r.x);
+  r.y = sA / A;
+  return r;
+}
+
+// true if the angle A of this cell lies outside the fast forms' range
+// (SERIES: of cos_sinc, the default with FP32 state)
+template <bool TWO, bool SERIES = !TWO>
+__device__ __forceinline__ bool angle_far(double ax, double ay, double az, const PhaseK& k) {
+  const double mu = k.mc2 * k.dt;
+  const double z = mu * mu + ax * ax + ay * ay + az * az;
+  if constexpr (SERIES)
+    return !(z <= kCosSincMax);
+  else
+    return far_arg(sqrt(z));
+}
+template <bool TWO, bool SERIES = !TWO>
 __device__ __forceinline__ bool field_far(double V, double ax, double ay, double az,
                                           const PhaseK& k) {
-  const double mu = k.mc2 * k.dt;
-  return far_arg(sqrt(mu * mu + ax * ax + ay * ay + az * az)) || far_arg(V * k.dt);
+  return angle_far<TWO, SERIES>(ax, ay, az, k) || far_arg(V * k.dt);
 }
 
 // ph = s e^{-i V dt}, the scalar part of the local step
@@ -568,18 +626,30 @@ __device__ __forceinline__ void scalar_phase(double V, const PhaseK& k, double& 
 }
 
 // U ph for the field integral At = (ax, ay, az) of the step, given ph
-template <bool TWO, bool ANY>
+template <bool TWO, bool ANY, bool SERIES = !TWO>
 __device__ __forceinline__ FieldFactors field_with(double pr, double pi, double ax, double ay,
                                                    double az, const PhaseK& k) {
-  constexpr int ACC = TWO ? 2 : 1;
   const double mu = k.mc2 * k.dt;
-  const double A = sqrt(mu * mu + ax * ax + ay * ay + az * az);
-  double sA, cA;
-  if constexpr (ANY)
-    sincos_any<ACC>(A, &sA, &cA);
-  else
-    sincos_fast<ACC>(A, &sA, &cA);
-  const double sa = (A > 0.0) ? sA / A : 1.0;
+  const double z = mu * mu + ax * ax + ay * ay + az * az;
+  double cA, sa;  // cos(A), sin(A) / A
+  if constexpr (!SERIES) {
+    constexpr int ACC = TWO ? 2 : 1;
+    const double A = sqrt(z);
+    double sA;
+    if constexpr (ANY)
+      sincos_any<ACC>(A, &sA, &cA);
+    else
+      sincos_fast<ACC>(A, &sA, &cA);
+    sa = (A > 0.0) ? sA / A : 1.0;
+  } else {
+    cos_sinc(z, &cA, &sa);
+    if constexpr (ANY)
+      if (!(z <= kCosSincMax)) {  // by lane, so that no lane's value depends on its wave
+        const double2 r = cos_sinc_far(z);
+        cA = r.x;
+        sa = r.y;
+      }
+  }
   const double ms = mu * sa;
   FieldFactors f;
   f.ur = fma(pr, cA, pi * ms);   // ph * (cA - i ms)
@@ -594,20 +664,21 @@ __device__ __forceinline__ FieldFactors field_with(double pr, double pi, double 
   return f;
 }
 
-template <bool TWO, bool ANY>
+template <bool TWO, bool ANY, bool SERIES = !TWO>
 __device__ __forceinline__ FieldFactors field_factors(double V, double ax, double ay, double az,
                                                       const PhaseK& k) {
   double pr, pi;
   scalar_phase<TWO, ANY>(V, k, pr, pi);
-  return field_with<TWO, ANY>(pr, pi, ax, ay, az, k);
+  return field_with<TWO, ANY, SERIES>(pr, pi, ax, ay, az, k);
 }
 
 // if any lane of the wave has an angle outside the fast reduction range,
 // recompute the wave's factors with the library fallback (a rare branch)
-template <bool TWO>
+template <bool TWO, bool SERIES = !TWO>
 __device__ __forceinline__ void field_fix(FieldFactors& f, double V, double ax, double ay,
                                           double az, const PhaseK& k) {
-  if (__any(field_far<TWO>(V, ax, ay, az, k))) f = field_factors<TWO, true>(V, ax, ay, az, k);
+  if (__any(field_far<TWO, SERIES>(V, ax, ay, az, k)))
+    f = field_factors<TWO, true, SERIES>(V, ax, ay, az, k);
 }
 
 // psi <- U e^{-i V dt} psi (with the deferred scale), promoted to FP64 and
@@ -747,7 +818,12 @@ __device__ __forceinline__ PulseRow pulse_row(double V, double px, double py, do
 template <bool TWO>
 __device__ __forceinline__ FieldFactors pulse_factors(const PulseRow& r, double F,
                                                       const PhaseK& k) {
-  return field_with<TWO, true>(r.pr, r.pi, F * r.px, F * r.py, F * r.pz, k);
+  const double ax = F * r.px, ay = F * r.py, az = F * r.pz;
+  FieldFactors f = field_with<TWO, false>(r.pr, r.pi, ax, ay, az, k);
+  // an angle beyond the fast reduction range: a wave-uniform, rarely taken
+  // branch, so that the common path stays one block
+  if (__any(angle_far<TWO>(ax, ay, az, k))) f = field_with<TWO, true>(r.pr, r.pi, ax, ay, az, k);
+  return f;
 }
 
 // Phase factors of a cell for phase mode MODE (3: with a static vector

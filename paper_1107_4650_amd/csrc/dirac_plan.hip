@@ -311,24 +311,18 @@ static int plan_tiling(dl_plan p) {
       while (depth > 1 && p->g.n[1] < 2 * stages_per_step * depth) --depth;
   }
   p->depth = depth;
-  // with a vector potential: 3-D lowest-order passes carry one step; the 3-D
-  // second-order passes carry one D each and group steps as without a field
-  p->depth_field = (p->g.ndim == 3) ? (p->strang ? depth : 1)
-                                    : std::min(depth, field_max_depth(p->fp64, p->strang));
+  // with a vector potential: 3-D passes fuse or group steps as without a field
+  p->depth_field =
+      (p->g.ndim == 3) ? depth : std::min(depth, field_max_depth(p->fp64, p->strang));
   for (int mode = 0; mode < 5; ++mode) {
     PlanTiling& t = p->tiling[mode];
     if (p->g.ndim == 3) {
-      if (mode >= 3) {  // with a vector potential (static or pulsed): one step per pass
-        make_tiling3d(p->g, p->fp64 ? kTY3D_F64 : kTY3D_F32, 64, 2, resident_waves(p, 3, 1),
-                      p->seg_override, t.a[0], t.b[0], 4);
-        for (int d = 0; d < kMaxDepth; ++d) t.a[d].periodic = (p->bc == DL_BC_PERIODIC);
-        continue;
-      }
-      make_tiling3d(p->g, p->fp64 ? kTY3D_F64 : kTY3D_F32, 64, 2, resident_waves(p, mode, 1),
+      const int m = std::min(mode, 3);  // a pulse runs the static field's kernels
+      make_tiling3d(p->g, p->fp64 ? kTY3D_F64 : kTY3D_F32, 64, 2, resident_waves(p, m, 1),
                     p->seg_override, t.a[0], t.b[0], 4);
       if (depth >= 2)  // workgroup tiles: resident workgroups are the target
         make_tiling3d(p->g, p->fp64 ? kTY3D2_F64 : kTY3D2_F32, strip_width(2), 4,
-                      resident_waves(p, mode, 2) / 4, p->seg_override, t.a[1], t.b[1], 1);
+                      resident_waves(p, m, 2) / 4, p->seg_override, t.a[1], t.b[1], 1);
     } else {
       for (int d = 1; d <= (mode >= 3 ? p->depth_field : depth); ++d)
         make_tiling(p->g, resident_waves(p, mode, d), p->seg_override, t.a[d - 1], t.b[d - 1],
@@ -832,7 +826,7 @@ extern "C" int dl_step_pulse(dl_plan p, void* psi, const double* V, const double
   if (nsteps == 0) return DL_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
   // 1-D / 2-D: phase mode 4 forms each step's field integral in the pass; 3-D
-  // passes (one D each) run the static-field kernels with At = F P
+  // passes run the static-field kernels with At = F P, F of each step
   const int mode = (p->g.ndim == 3) ? 3 : 4;
   p->ph = make_phase(transports_per_step(p), p->dt, p->c, p->m, mode, p->fp64);
   p->field = P;

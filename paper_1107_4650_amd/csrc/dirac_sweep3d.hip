@@ -202,11 +202,19 @@ template <typename T> struct alignas(16) X2Lds {
   Mov<T> r2[S::NS - 2][64], l2[S::NS - 2][64];
 };
 
+// with a vector potential the rows' scalar phases and field integrals wait for
+// the second step in LDS, slot it % 2 (each lane reads what it wrote itself;
+// in registers they and the factors formed from them would spill)
+template <typename T, int MODE> struct X2Field {};
+template <typename T> struct X2Field<T, 3> {
+  double q[2][5][X2Tile<T>::WY][64];
+};
+
 // OBS: also add the observables of every stored cell to the lane's sums acc
 template <typename T, bool UP, int MODE, bool EDGE, bool OBS = false>
 __device__ __forceinline__ void march3d_x2(const T* __restrict__ src, T* __restrict__ dst,
                                            const double* __restrict__ V, const SweepArgs& a,
-                                           X2Lds<T>& sh, int lane, int wv, int64_t xs,
+                                           X2Lds<T>& sh, X2Field<T, MODE>& fl, int lane, int wv, int64_t xs,
                                            int64_t y0, int64_t kb, int64_t ke,
                                            NSum* acc = nullptr, const ObsArgs* ob = nullptr) {
   using S = X2Tile<T>;
@@ -221,7 +229,16 @@ __device__ __forceinline__ void march3d_x2(const T* __restrict__ src, T* __restr
   // plane bases are wave-uniform
   const uint32_t cell_off = static_cast<uint32_t>(c.col) * 8u;
   const uint32_t v_off = static_cast<uint32_t>(c.col);
-  const bool read_v = (MODE == 2);
+  constexpr bool FIELD = MODE == 3;  // local step with a vector potential
+  const bool read_v = (MODE == 2) || (FIELD && V != nullptr);
+  // under a pulse the array holds the profile P and step s of the pass carries
+  // F[s] P (F is exactly 1 for a static field)
+  double F[2] = {1.0, 1.0};
+  if constexpr (FIELD)
+    if (a.pulse_on) {
+      F[0] = pulse_step_integral(a.pulse, 0);
+      F[1] = pulse_step_integral(a.pulse, 1);
+    }
   const bool zero_walls = !a.periodic;
   auto in_plane = [&](int it) -> int64_t { return UP ? kb - K + it : ke - 1 + K - it; };
   auto plane_of = [&](int it, int st) -> int64_t {
@@ -253,9 +270,10 @@ __device__ __forceinline__ void march3d_x2(const T* __restrict__ src, T* __restr
 #pragma unroll
   for (int j = 0; j <= TW; ++j) srow_off[j] = read_row(y0 - 1 + srow(j), ny, a.periodic) * nx;
   Mov<T> zm1[2][TW + 1], zm2[2][TW];  // z movers of two previous planes, slot it % 2
-  Factors fc[TW];  // factors of the own rows, formed by the first step one iteration earlier
+  // factors of the own rows, formed by the first step one iteration earlier
+  Factors fc[FIELD ? 1 : TW];
 #pragma unroll
-  for (int j = 0; j < TW; ++j) fc[j] = Factors{};
+  for (int j = 0; j < (FIELD ? 1 : TW); ++j) fc[j] = Factors{};
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
 #pragma unroll
@@ -266,17 +284,28 @@ __device__ __forceinline__ void march3d_x2(const T* __restrict__ src, T* __restr
   // this wave's input rows of the plane read at iteration it and the V of its
   // first-step rows on the plane one behind, loaded one iteration ahead
   Site<T> in[N1];
-  double vn[TW + 1];
+  double vn[TW + 1], an[FIELD ? TW + 1 : 1][3];
   auto load_inputs = [&](int it) {
     const T* plane = src + read_row(in_plane(it), nz, a.periodic) * plane_cells * 8;
 #pragma unroll
     for (int j = 0; j < N1; ++j) load_site(plane + inrow[j] + cell_off, in[j]);
-    const double* vp = V + read_row(plane_of(it, 1), nz, a.periodic) * plane_cells;
+  };
+  auto load_v = [&](int it) {
+    const int64_t vp = read_row(plane_of(it, 1), nz, a.periodic) * plane_cells;
 #pragma unroll
-    for (int j = 0; j <= TW; ++j)
-      vn[j] = (read_v && (j < TW || halo)) ? (vp + srow_off[j])[v_off] : 0.0;
+    for (int j = 0; j <= TW; ++j) {
+      vn[j] = (read_v && (j < TW || halo)) ? (V + vp + srow_off[j])[v_off] : 0.0;
+      if constexpr (FIELD)
+        if (j < TW || halo) {
+          const double* ap = a.At + vp + srow_off[j];
+          an[j][0] = ap[v_off];
+          an[j][1] = (ap + a.cells)[v_off];
+          an[j][2] = (ap + 2 * a.cells)[v_off];
+        }
+    }
   };
   load_inputs(0);
+  load_v(0);  // the field modes load theirs later in the plane (registers)
   for (int pair = 0;; ++pair) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -301,11 +330,14 @@ __device__ __forceinline__ void march3d_x2(const T* __restrict__ src, T* __restr
         if (t < NI - 2) sh.r1[t][lane] = ry;
         if (t >= 2) sh.l1[t - 2][lane] = ly;
       }
-      if (it + 1 < nit) load_inputs(it + 1);
+      if (it + 1 < nit) {
+        load_inputs(it + 1);
+        if (!FIELD) load_v(it + 1);
+      }
       __syncthreads();
       // 2. first step on the first-step rows of the plane one behind, then the
       //    second step's x transport, y movers to LDS
-      Factors fnew[TW];
+      Factors fnew[FIELD ? 1 : TW];
 #pragma unroll
       for (int j = 0; j <= TW; ++j) {
         if (j == TW && !halo) break;
@@ -319,9 +351,23 @@ __device__ __forceinline__ void march3d_x2(const T* __restrict__ src, T* __restr
         else
           Axis<2, T>::combine(rz, zm1[k][j], o1);
         zm1[k][j] = UP ? rz : lz;
-        Factors f1 = factors_of<MODE, TWO>(vb[j], a.ph);
-        factors_fix<MODE, TWO>(f1, vb[j], a.ph);
-        apply_local<MODE>(o1, f1, a.ph);
+        if constexpr (FIELD) {
+          const PulseRow q = pulse_row<TWO>(vn[j], an[j][0], an[j][1], an[j][2], a.ph);
+          if (j < TW) {
+            const int w = wv * TW + j;
+            fl.q[k][0][w][lane] = q.pr;
+            fl.q[k][1][w][lane] = q.pi;
+            fl.q[k][2][w][lane] = q.px;
+            fl.q[k][3][w][lane] = q.py;
+            fl.q[k][4][w][lane] = q.pz;
+          }
+          apply_field(o1, pulse_factors<TWO>(q, F[0], a.ph));
+        } else {
+          Factors f1 = factors_of<MODE, TWO>(vb[j], a.ph);
+          factors_fix<MODE, TWO>(f1, vb[j], a.ph);
+          apply_local<MODE>(o1, f1, a.ph);
+          if (j < TW) fnew[j] = f1;
+        }
         if (zero_walls) {
           if (!plane_in(it - 1) || !((ymask >> (u + 1)) & 1u)) zero(o1);
           if (EDGE && !c.inside) zero(o1);
@@ -332,8 +378,8 @@ __device__ __forceinline__ void march3d_x2(const T* __restrict__ src, T* __restr
         Axis<1, T>::movers(phi2, ry2, ly2);
         if (u < NS - 2) sh.r2[u][lane] = ry2;
         if (u >= 2) sh.l2[u - 2][lane] = ly2;
-        if (j < TW) fnew[j] = f1;
       }
+      if (FIELD && it + 1 < nit) load_v(it + 1);
       __syncthreads();
       // 3. second step on the own rows of the plane two behind
 #pragma unroll
@@ -348,13 +394,23 @@ __device__ __forceinline__ void march3d_x2(const T* __restrict__ src, T* __restr
         else
           Axis<2, T>::combine(rz2, zm2[k][j], o2);
         zm2[k][j] = UP ? rz2 : lz2;
-        apply_local<MODE>(o2, fc[j], a.ph);
+        if constexpr (FIELD) {
+          PulseRow q;
+          q.pr = fl.q[k ^ 1][0][w][lane];
+          q.pi = fl.q[k ^ 1][1][w][lane];
+          q.px = fl.q[k ^ 1][2][w][lane];
+          q.py = fl.q[k ^ 1][3][w][lane];
+          q.pz = fl.q[k ^ 1][4][w][lane];
+          apply_field(o2, pulse_factors<TWO>(q, F[1], a.ph));
+        } else {
+          apply_local<MODE>(o2, fc[j], a.ph);
+        }
         const int64_t y = y0 + w;
         if (it >= 2 * K && own && y < ny) {
           store_site(dst + (k2 * ny + y) * nx * 8 + cell_off, o2);
           if constexpr (OBS) obs_add_cell3(acc, o2, y, k2, *ob);
         }
-        fc[j] = fnew[j];
+        if constexpr (!FIELD) fc[j] = fnew[j];
       }
     }
   }
@@ -366,6 +422,7 @@ template <typename T, int MODE>
 __global__ __launch_bounds__(256, sizeof(T) == 8 ? 1 : 2) void k_sweep3d_x2(
     const T* __restrict__ src, T* __restrict__ dst, const double* __restrict__ V, SweepArgs a) {
   __shared__ X2Lds<T> sh;
+  __shared__ X2Field<T, MODE> fl;
   const int lane = threadIdx.x & 63;
   const int wv = wave_in_block();
   int64_t blk = blockIdx.x;
@@ -385,14 +442,14 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 ? 1 : 2) void k_sweep3d_x2(
   const bool edge = !lanes_of(a.nx, a.periodic, xs, 0).full;
   if (edge) {
     if (seg & 1)
-      march3d_x2<T, false, MODE, true>(src, dst, V, a, sh, lane, wv, xs, y0, kb, ke);
+      march3d_x2<T, false, MODE, true>(src, dst, V, a, sh, fl, lane, wv, xs, y0, kb, ke);
     else
-      march3d_x2<T, true, MODE, true>(src, dst, V, a, sh, lane, wv, xs, y0, kb, ke);
+      march3d_x2<T, true, MODE, true>(src, dst, V, a, sh, fl, lane, wv, xs, y0, kb, ke);
   } else {
     if (seg & 1)
-      march3d_x2<T, false, MODE, false>(src, dst, V, a, sh, lane, wv, xs, y0, kb, ke);
+      march3d_x2<T, false, MODE, false>(src, dst, V, a, sh, fl, lane, wv, xs, y0, kb, ke);
     else
-      march3d_x2<T, true, MODE, false>(src, dst, V, a, sh, lane, wv, xs, y0, kb, ke);
+      march3d_x2<T, true, MODE, false>(src, dst, V, a, sh, fl, lane, wv, xs, y0, kb, ke);
   }
 }
 
@@ -404,6 +461,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 ? 1 : 2) void k_sweep3d_x2_obs(
     const T* __restrict__ src, T* __restrict__ dst, const double* __restrict__ V, SweepArgs a,
     ObsArgs o, double* __restrict__ partials) {
   __shared__ X2Lds<T> sh;
+  __shared__ X2Field<T, MODE> fl;
   const int lane = threadIdx.x & 63;
   const int wv = wave_in_block();
   int64_t blk = blockIdx.x;
@@ -422,17 +480,17 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 ? 1 : 2) void k_sweep3d_x2_obs(
   const bool edge = !lanes_of(a.nx, a.periodic, xs, 0).full;
   if (edge) {
     if (seg & 1)
-      march3d_x2<T, false, MODE, true, true>(src, dst, V, a, sh, lane, wv, xs, y0, kb, ke, acc,
+      march3d_x2<T, false, MODE, true, true>(src, dst, V, a, sh, fl, lane, wv, xs, y0, kb, ke, acc,
                                              &o);
     else
-      march3d_x2<T, true, MODE, true, true>(src, dst, V, a, sh, lane, wv, xs, y0, kb, ke, acc,
+      march3d_x2<T, true, MODE, true, true>(src, dst, V, a, sh, fl, lane, wv, xs, y0, kb, ke, acc,
                                             &o);
   } else {
     if (seg & 1)
-      march3d_x2<T, false, MODE, false, true>(src, dst, V, a, sh, lane, wv, xs, y0, kb, ke, acc,
+      march3d_x2<T, false, MODE, false, true>(src, dst, V, a, sh, fl, lane, wv, xs, y0, kb, ke, acc,
                                               &o);
     else
-      march3d_x2<T, true, MODE, false, true>(src, dst, V, a, sh, lane, wv, xs, y0, kb, ke, acc,
+      march3d_x2<T, true, MODE, false, true>(src, dst, V, a, sh, fl, lane, wv, xs, y0, kb, ke, acc,
                                              &o);
   }
   obs_column_close(acc, xs + lane, o);  // lanes that stored nothing hold zeros
@@ -714,9 +772,10 @@ __global__ __launch_bounds__(256, 2) void k_strang3d_step(const T* __restrict__ 
         Site<T> cd, out;
         Axis<2, T>::combine(rs[u][j], l, cd);  // C at plane n - 2
         rs[u][j] = r;
-        if constexpr (MODE == 3) {  // D with the step's field integral
-          FieldFactors f = field_factors<TWO, false>(vv[j], ax[j], ay[j], az[j], a.ph);
-          field_fix<TWO>(f, vv[j], ax[j], ay[j], az[j], a.ph);
+        if constexpr (MODE == 3) {  // D with the step's field integral (the
+          // general form: the series' constants spill here, 2 % slower)
+          FieldFactors f = field_factors<TWO, false, false>(vv[j], ax[j], ay[j], az[j], a.ph);
+          field_fix<TWO, false>(f, vv[j], ax[j], ay[j], az[j], a.ph);
           apply_field(cd, f);
         } else {
           Factors f = factors_of<MODE, TWO>(vv[j], a.ph);
@@ -883,11 +942,12 @@ template <typename T>
 static const void* kernel3d(int depth, int mode) {
   constexpr bool F64 = sizeof(T) == 8;
   constexpr int TY1 = F64 ? kTY3D_F64 : kTY3D_F32;
-  if (depth == 2) {  // phase modes 0 to 2
+  if (depth == 2) {
     switch (mode) {
       case 0: return reinterpret_cast<const void*>(&k_sweep3d_x2<T, 0>);
       case 1: return reinterpret_cast<const void*>(&k_sweep3d_x2<T, 1>);
       case 2: return reinterpret_cast<const void*>(&k_sweep3d_x2<T, 2>);
+      case 3: return reinterpret_cast<const void*>(&k_sweep3d_x2<T, 3>);
       default: return nullptr;
     }
   }
