@@ -157,7 +157,8 @@ int dl_step(dl_plan p, void *psi, const double *V, int64_t nsteps, void *stream)
  * cell centres, each block in psi's cell order; held fixed for the nsteps
  * steps of the call (a time-dependent field is applied by calls over shorter
  * spans).  A = NULL is dl_step.  1-D and 2-D grids, both splittings, passes
- * of at most 3 steps (1 with DL_STRANG) with the bits of single steps; 3-D
+ * of at most 3 steps (1 with DL_STRANG; up to 7 in the register tiles of
+ * planes of up to 600 thousand cells) with the bits of single steps; 3-D
  * grids: the same grouping of steps as dl_step (second-order steps with U in
  * the middle D of each step).  Same buffers and copy rule as dl_step. */
 int dl_step_field(dl_plan p, void *psi, const double *V, const double *A, int64_t nsteps,
@@ -181,8 +182,8 @@ typedef struct {
  * Sec. 2.3, as dl_step_field): step n = 0 .. nsteps - 1 covers
  * [t0 + n dt, t0 + (n + 1) dt] and uses the field integral (eq:field_dis1)
  *     At^n(x) = P(x) F_n,  F_n = int_{t0 + n dt}^{t0 + (n + 1) dt} f(t) dt,
- * F_n evaluated on the device in closed form for every step (so passes still
- * fuse up to 3 lowest-order steps, each with its own F_n; 1-D and 2-D grids,
+ * F_n evaluated in closed form for every step (so passes still
+ * fuse as in dl_step_field, each step with its own F_n; 1-D and 2-D grids,
  * both splittings).  3-D grids: steps grouped as in dl_step, each D with its
  * own F_n.  P: device array of 3 * cells doubles, planar
  * (x, y, z blocks in psi's cell order): e times the amplitude of A at the

@@ -171,7 +171,7 @@ __device__ __forceinline__ void line_steps(const T* __restrict__ src, T* __restr
 // us per pass of 7 to 8 steps (marching passes 260 us per 5 steps).
 template <typename T, bool BIG>
 __global__ __launch_bounds__(64 * tile_shape(sizeof(T) == 8, BIG).waves,
-                             tile2d_waves(sizeof(T) == 8, tile_shape(sizeof(T) == 8, BIG).rows))
+                             tile2d_waves(sizeof(T) == 8, tile_shape(sizeof(T) == 8, BIG).rows, 2))
 void k_batch_tile(const BatchInst* __restrict__ insts, const BatchTile* __restrict__ tiles,
                   int ntiles, int64_t index, int halo) {
   constexpr TileShape t = tile_shape(sizeof(T) == 8, BIG);
@@ -426,7 +426,7 @@ void choose_register_tiles(Batch& B) {
     for (int k = 1; k <= kMaxTileDepth; ++k) {
       const TileShape t = tile_shape(B.fp64, big != 0);
       if (64 - 2 * k < 16 || t.waves * t.rows - 2 * k < 8) break;
-      const double us = tile_time(B.fp64, false, big != 0, k,
+      const double us = tile_time(B.fp64, false, false, big != 0, k,
                                   static_cast<double>(register_tiles(B, big != 0, k, nullptr)),
                                   B.cu_count) / k;
       if (B.tile_depth == 0 || us < best) {

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "dirac_device.h"
+#include "dirac_pulse.h"
 
 namespace dirac {
 
@@ -53,6 +54,8 @@ constexpr int kMaxRevDepthF64 = 2;
 __host__ __device__ constexpr int field_max_depth(bool /*fp64*/, bool strang) {
   return strang ? 1 : 3;
 }
+constexpr int kMaxFieldSteps = 3;
+constexpr int kMaxTileDepth = 12;  // steps of a register-tile pass
 __host__ __device__ constexpr int strip_width(int xlanes) { return 64 - 2 * xlanes; }
 __host__ __device__ constexpr int pass_xlanes(bool strang, int depth) {
   return strang ? 2 * depth : depth;
@@ -72,8 +75,8 @@ struct SweepArgs {
   // phase mode 3: field integrals At, planar (x, y, z blocks of `cells`);
   // phase mode 4: the pulse's field profile P in the same layout
   const double* At;
-  PulseK pulse;        // phase mode 4 (and 3-D passes with pulse_on)
-  int pulse_on;        // 3-D passes: the field integral is P times the pulse's F
+  double F[kMaxFieldSteps];  // the field integral of step s of the pass is F[s] At (mode 4
+                             // and 3-D passes; 1 for a static field)
   int64_t cells;
   int nc;              // components stored per cell: 4, or 2 (two-component 1-D line)
 };
@@ -89,19 +92,26 @@ struct TileArgs {
   int xcd_remap;       // blocks dealt XCD-contiguously (grid a multiple of 8)
   int axes_code;
   PhaseK ph;
+  const double* At;    // phase mode 3: field integrals, 4: the pulse's profile (planar,
+                       // blocks of `cells`)
+  int64_t cells;
+  double F[kMaxTileDepth];  // phase mode 4: the field integral of step s is F[s] At
 };
 
 // the register tiles: W waves of RW rows.  `big` has fewer halo rows per
 // written row (48 of FP32 state, 32 of FP64 state, two workgroups per CU),
 // the other (32 rows of sixteen waves) the shorter chain of work per step,
 // which counts when the grid is a few tiles per CU.
-constexpr int kMaxTileDepth = 12;
 struct TileShape { int waves, rows; };
-__host__ __device__ constexpr TileShape tile_shape(bool fp64, bool big) {
+__host__ __device__ constexpr TileShape tile_shape(bool fp64, bool big, bool field = false) {
+  // with a vector potential a cell takes 18 to 34 registers and the step is
+  // bound by FP64 issue, so the tiles are smaller
+  if (field) return big ? (fp64 ? TileShape{8, 4} : TileShape{16, 2}) : TileShape{8, 2};
   return big ? (fp64 ? TileShape{4, 8} : TileShape{8, 6}) : TileShape{16, 2};
 }
 // waves per SIMD the register tile kernel is compiled for
-__host__ __device__ constexpr int tile2d_waves(bool fp64, int rows) {
+__host__ __device__ constexpr int tile2d_waves(bool fp64, int rows, int mode) {
+  if (mode >= 3) return fp64 ? 2 : (rows > 4 ? 3 : 4);
   return fp64 ? (rows > 2 ? 2 : 4) : (rows > 2 ? 4 : 8);
 }
 
@@ -139,8 +149,9 @@ bool sweep2d_obs_available(bool fp64, int depth, int mode);
 // modes 0-2; tiling made for strip_width(kDeep1D))
 hipError_t launch_sweep1d_deep(bool fp64, const void* src, void* dst, const double* V,
                                const SweepArgs& a, int blocks, hipStream_t st);
-// a.steps full steps src -> dst on a 2-D grid in register tiles (phase modes
-// 0-2; a.nstrips, a.ntiles made for tile_shape(fp64, big) and a.halo)
+// a.steps full steps src -> dst on a 2-D grid in register tiles (a.nstrips,
+// a.ntiles made for tile_shape(fp64, big, mode >= 3) and a.halo; with a vector
+// potential second-order steps have the big tiles only)
 hipError_t launch_tile2d(bool fp64, bool strang, bool big, const void* src, void* dst,
                          const double* V, const TileArgs& a, hipStream_t st);
 // the two-step 3-D pass (phase modes 0-2) that also sums the observables of
@@ -162,9 +173,11 @@ int occupancy3d(bool fp64, int mode, int depth);
 // nsteps >= 1 second-order steps src -> dst on a 3-D grid (Sec. 2.4) in
 // nsteps + 1 passes through `mid` and `mid2` (state buffers distinct from src,
 // dst and each other; src == dst is allowed), or, with mid2 = NULL, through
-// mid and dst (src != dst); a needs nx, ny, nz, periodic and ph
+// mid and dst (src != dst); a needs nx, ny, nz, periodic and ph; pulse: the
+// steps' field integrals are its F times the profile a.At (NULL: a.At itself)
 hipError_t launch_strang3d(bool fp64, const void* src, void* dst, void* mid, void* mid2,
-                           const double* V, const SweepArgs& a, int64_t nsteps, hipStream_t st);
+                           const double* V, const SweepArgs& a, const PulseK* pulse,
+                           int64_t nsteps, hipStream_t st);
 // nsteps in place in one workgroup of `threads` threads, `spt` cells each
 hipError_t launch_resident1d(bool fp64, int axis, void* psi, const double* V,
                              const ResidentArgs& a, int spt, int threads, hipStream_t st);

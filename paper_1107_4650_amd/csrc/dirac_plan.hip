@@ -142,18 +142,23 @@ void make_tiling(const dl_grid& g, int64_t target, int seg_override, SweepArgs& 
   a.axes_code = axes_code(g);
 }
 
-// Time of a register-tile pass in us, from fits (rms error 5-8 %) to the
-// passes of 1 to 12 steps on planes of 128^2 to 4096^2 cells: a compute unit's
-// first tile takes t0 + t1 per transport pair, every further one n0 + n1 per
-// transport pair.
-double tile_time(bool fp64, bool strang, bool big, int halo, double tiles, int cu_count) {
+// Time of a register-tile pass in us, from fits (rms error 4-9 %) to the
+// passes of 1 to 12 steps (8 with a vector potential) on planes of 128^2 to
+// 4096^2 (2048^2) cells: a compute unit's first tile takes t0 + t1 per transport
+// pair, every further one n0 + n1 per transport pair.
+double tile_time(bool fp64, bool strang, bool field, bool big, int halo, double tiles,
+                 int cu_count) {
   struct Fit { double t0, t1, n0, n1; };
-  static const Fit fits[2][2][2] = {  // [fp64][strang][big]
-      {{{5.0, 0.74, 4.2, 0.28}, {7.1, 1.07, 6.4, 0.51}},
-       {{5.1, 0.63, 5.2, 0.11}, {6.5, 1.04, 6.0, 0.43}}},
-      {{{9.3, 0.79, 15.5, 0.0}, {11.1, 1.0, 10.9, 0.17}},
-       {{8.8, 0.79, 14.8, 0.0}, {11.8, 0.89, 10.4, 0.18}}}};
-  const Fit& f = fits[fp64][strang][big];
+  static const Fit fits[2][2][2][2] = {  // [field][fp64][strang][big]
+      {{{{5.0, 0.74, 4.2, 0.28}, {7.1, 1.07, 6.4, 0.51}},
+        {{5.1, 0.63, 5.2, 0.11}, {6.5, 1.04, 6.0, 0.43}}},
+       {{{9.3, 0.79, 15.5, 0.0}, {11.1, 1.0, 10.9, 0.17}},
+        {{8.8, 0.79, 14.8, 0.0}, {11.8, 0.89, 10.4, 0.18}}}},
+      {{{{5.1, 1.63, 4.4, 0.76}, {7.7, 2.37, 9.1, 2.21}},
+        {{0.0, 0.0, 0.0, 0.0}, {9.0, 1.59, 11.0, 1.28}}},
+       {{{5.9, 1.79, 8.6, 0.92}, {12.2, 3.10, 18.1, 2.76}},
+        {{0.0, 0.0, 0.0, 0.0}, {13.7, 2.01, 20.5, 1.52}}}}};
+  const Fit& f = fits[field][fp64][strang][big];
   const double per_cu = tiles / cu_count;
   const double more = std::max(0.0, (per_cu < 4.0 ? std::ceil(per_cu) : per_cu) - 1.0);
   return f.t0 + f.t1 * halo + more * (f.n0 + f.n1 * halo);
@@ -241,11 +246,12 @@ static int64_t resident_waves(dl_plan p, int mode, int depth) {
 
 // tiling of a register-tile pass of `steps` steps; false if the tile is too
 // small for them
-static bool tile_args(dl_plan p, bool big, int steps, TileArgs& a) {
-  const TileShape t = tile_shape(p->fp64, big);
+static bool tile_args(dl_plan p, bool field, bool big, int steps, TileArgs& a) {
+  if (field && p->strang && !big) return false;
+  const TileShape t = tile_shape(p->fp64, big, field);
   const int halo = steps * (p->strang ? 2 : 1);
   const int64_t w = 64 - 2 * halo, h = t.waves * t.rows - 2 * halo;
-  if (w < 16 || h < 8) return false;
+  if (w < 16 || h < (field ? 2 : 8)) return false;
   a.nx = p->g.n[0];
   a.ny = p->g.n[1];
   a.periodic = (p->bc == DL_BC_PERIODIC);
@@ -259,10 +265,11 @@ static bool tile_args(dl_plan p, bool big, int steps, TileArgs& a) {
 }
 
 // fitted time of a register-tile pass in us; negative: no such pass
-static double tile_cost(dl_plan p, bool big, int steps) {
+static double tile_cost(dl_plan p, bool field, bool big, int steps) {
   TileArgs a{};
-  if (!tile_args(p, big, steps, a)) return -1.0;
-  return tile_time(p->fp64, p->strang, big, a.halo, static_cast<double>(a.ntiles), p->cu_count);
+  if (!tile_args(p, field, big, steps, a)) return -1.0;
+  return tile_time(p->fp64, p->strang, field, big, a.halo, static_cast<double>(a.ntiles),
+                   p->cu_count);
 }
 
 // 2-D plans whose passes are not capped or retiled by the caller run in
@@ -272,23 +279,31 @@ static double tile_cost(dl_plan p, bool big, int steps) {
 // FP64 state up to 600 thousand cells (768^2: 5.5 against 6.4 us, second
 // order 11.0 against 11.1 us; 1024^2: 9.1 against 8.7 and 18.4 against 15.5
 // us).  The tile and the depth are those of the least fitted time per step.
-constexpr int64_t kTileMaxCellsF64 = 600000;
+// With a vector potential: up to 600 thousand cells (768^2 lowest order, pulse:
+// FP32 9.0 against 11.1 us, FP64 14.1 against 14.8; 1024^2: 15.6 against 13.7
+// and 24.2 against 18.7).
+constexpr int64_t kTileMaxCells = 600000;
 
 static void choose_tile(dl_plan p) {
-  p->tile_depth = 0;
+  p->tile_depth = p->tile_depth_field = 0;
   if (p->g.ndim != 2 || p->depth_limit < kMaxDepth || p->waves_per_cu > 0 || p->seg_override > 0)
     return;
-  if (p->fp64 && p->g.n[0] * p->g.n[1] > kTileMaxCellsF64) return;
-  double best = 0.0;
-  for (int big = 0; big < 2; ++big)
-    for (int k = 1; k <= kMaxTileDepth; ++k) {
-      const double t = tile_cost(p, big != 0, k);
-      if (t > 0.0 && (p->tile_depth == 0 || t / k < best)) {
-        best = t / k;
-        p->tile_depth = k;
-        p->tile_big = big != 0;
+  const bool few = p->g.n[0] * p->g.n[1] <= kTileMaxCells;
+  for (int field = 0; field < 2; ++field) {
+    if (!few && (p->fp64 || field)) continue;
+    int& depth = field ? p->tile_depth_field : p->tile_depth;
+    bool& in_big = field ? p->tile_big_field : p->tile_big;
+    double best = 0.0;
+    for (int big = 0; big < 2; ++big)
+      for (int k = 1; k <= kMaxTileDepth; ++k) {
+        const double t = tile_cost(p, field != 0, big != 0, k);
+        if (t > 0.0 && (depth == 0 || t / k < best)) {
+          best = t / k;
+          depth = k;
+          in_big = big != 0;
+        }
       }
-    }
+  }
 }
 
 static int plan_tiling(dl_plan p) {
@@ -478,6 +493,13 @@ int check_f64_ptr(const void* ptr, const char* name, bool nullable) {
   return DL_OK;
 }
 
+// the field integral factors of the next `n` steps of the call (1 unless a
+// pulse is on)
+static void set_pulse(dl_plan p, double* F, int n) {
+  for (int s = 0; s < n; ++s)
+    F[s] = p->pulse_on ? pulse_step_integral(p->pulse, s) : 1.0;
+}
+
 // one pass of `depth` fused steps src -> dst with the current phase and tiling
 hipError_t launch_pass(dl_plan p, int depth, const void* src, void* dst, const double* V,
                        hipStream_t st) {
@@ -485,17 +507,17 @@ hipError_t launch_pass(dl_plan p, int depth, const void* src, void* dst, const d
     SweepArgs a = p->sw[p->strang ? 0 : depth - 1];  // second-order passes size their own grids
     a.ph = p->ph;
     a.At = p->field;
-    a.pulse = p->pulse;
-    a.pulse_on = p->pulse_on ? 1 : 0;
+    set_pulse(p, a.F, std::min(depth, kMaxFieldSteps));
     a.cells = p->cells;
-    if (p->strang) return launch_strang3d(p->fp64, src, dst, p->tmp2, nullptr, V, a, depth, st);
+    if (p->strang)
+      return launch_strang3d(p->fp64, src, dst, p->tmp2, nullptr, V, a,
+                             p->pulse_on ? &p->pulse : nullptr, depth, st);
     return launch_sweep3d(p->fp64, depth, src, dst, V, a, p->bl[depth - 1], st);
   }
   SweepArgs a = p->sw[depth - 1];
   a.ph = p->ph;
   a.At = p->field;
-  a.pulse = p->pulse;
-  a.pulse_on = p->pulse_on ? 1 : 0;
+  set_pulse(p, a.F, std::min(depth, kMaxFieldSteps));
   a.cells = p->cells;
   a.nc = p->nc;
   return launch_sweep2d(p->fp64, p->strang, depth, src, dst, V, a, p->bl[depth - 1], st);
@@ -512,8 +534,6 @@ static hipError_t launch_pass_obs(dl_plan p, int depth, const void* src, void* d
     SweepArgs a = p->sw[1];
     a.ph = p->ph;
     a.At = nullptr;
-    a.pulse = p->pulse;
-    a.pulse_on = 0;
     a.cells = p->cells;
     *waves = a.ntiles * 4;  // four waves per workgroup tile
     return launch_sweep3d_obs(p->fp64, src, dst, V, a, o, p->tile_partials, p->bl[1], st);
@@ -521,8 +541,6 @@ static hipError_t launch_pass_obs(dl_plan p, int depth, const void* src, void* d
   SweepArgs a = p->sw[depth - 1];
   a.ph = p->ph;
   a.At = nullptr;
-  a.pulse = p->pulse;
-  a.pulse_on = 0;
   a.cells = p->cells;
   a.nc = p->nc;
   *waves = a.ntiles;
@@ -543,8 +561,6 @@ static hipError_t launch_pass_deep(dl_plan p, const void* src, void* dst, const 
   SweepArgs a = p->sw_deep;
   a.ph = p->ph;
   a.At = nullptr;
-  a.pulse = p->pulse;
-  a.pulse_on = 0;
   a.cells = p->cells;
   a.nc = p->nc;
   return launch_sweep1d_deep(p->fp64, src, dst, V, a, p->bl_deep, st);
@@ -554,8 +570,11 @@ static hipError_t launch_pass_deep(dl_plan p, const void* src, void* dst, const 
 static hipError_t launch_pass_tile(dl_plan p, bool big, int depth, const void* src, void* dst,
                                    const double* V, hipStream_t st) {
   TileArgs a{};
-  if (!tile_args(p, big, depth, a)) return hipErrorInvalidValue;
+  if (!tile_args(p, p->ph.mode >= 3, big, depth, a)) return hipErrorInvalidValue;
   a.ph = p->ph;
+  a.At = p->field;
+  a.cells = p->cells;
+  if (p->pulse_on) set_pulse(p, a.F, depth);
   return launch_tile2d(p->fp64, p->strang, big, src, dst, V, a, st);
 }
 
@@ -572,18 +591,21 @@ static PassList pass_list(dl_plan p, int64_t nsteps, bool obs) {
     l.add(PassRun::kDeep, kDeep1D, left / kDeep1D);
     left %= kDeep1D;
   }
-  if (p->tile_depth > 0 && p->ph.mode <= 2) {
+  const bool field = p->ph.mode >= 3;
+  const int tile = field ? p->tile_depth_field : p->tile_depth;
+  const bool big = field ? p->tile_big_field : p->tile_big;
+  if (tile > 0) {
     const int64_t n = obs ? left - std::min<int64_t>(left, dmax) : left;
     if (n > 0) {
-      const PassRun::Kind kind = p->tile_big ? PassRun::kTileBig : PassRun::kTile;
-      int64_t passes = (n + p->tile_depth - 1) / p->tile_depth;
+      const PassRun::Kind kind = big ? PassRun::kTileBig : PassRun::kTile;
+      int64_t passes = (n + tile - 1) / tile;
       if (passes == 1 && n > 1 && left == n) {
         // a single pass ends in the plan's buffer: two shallower ones, unless
         // copying the state back (about 4 us, then 4.5 TB/s) is cheaper
         const double copy = 4.0 + 2.0 * static_cast<double>(p->state_bytes) / 4.5e6;
-        if (tile_cost(p, p->tile_big, static_cast<int>(n - n / 2)) +
-                tile_cost(p, p->tile_big, static_cast<int>(n / 2)) <
-            tile_cost(p, p->tile_big, static_cast<int>(n)) + copy)
+        if (tile_cost(p, field, big, static_cast<int>(n - n / 2)) +
+                tile_cost(p, field, big, static_cast<int>(n / 2)) <
+            tile_cost(p, field, big, static_cast<int>(n)) + copy)
           passes = 2;
       }
       const int d = static_cast<int>(n / passes);  // passes of d + 1 and d steps
@@ -641,10 +663,9 @@ hipError_t enqueue_steps(dl_plan p, void* psi, const double* V, int64_t nsteps, 
     SweepArgs a = p->sw[0];
     a.ph = p->ph;
     a.At = p->field;
-    a.pulse = p->pulse;
-    a.pulse_on = p->pulse_on ? 1 : 0;
     a.cells = p->cells;
-    hipError_t e = launch_strang3d(p->fp64, psi, psi, p->tmp2, p->tmp, V, a, nsteps, st);
+    hipError_t e = launch_strang3d(p->fp64, psi, psi, p->tmp2, p->tmp, V, a,
+                                   p->pulse_on ? &p->pulse : nullptr, nsteps, st);
     if (e != hipSuccess) return e;
     p->pulse.n0 += nsteps;
     *result = psi;

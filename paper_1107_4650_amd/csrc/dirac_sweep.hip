@@ -149,7 +149,7 @@ hipError_t launch_tile2d(bool fp64, bool strang, bool big, const void* src, void
                          const double* V, const TileArgs& a, hipStream_t st) {
   const void* fn = fp64 ? kernel_tile2d_f64(strang, big, a.axes_code, a.ph.mode)
                         : kernel_tile2d_f32(strang, big, a.axes_code, a.ph.mode);
-  const TileShape t = tile_shape(fp64, big);
+  const TileShape t = tile_shape(fp64, big, a.ph.mode >= 3);
   const int64_t blocks = (a.ntiles + 7) / 8 * 8;
   if (!fn || a.ntiles < 1 || blocks > INT32_MAX || 2 * a.halo >= 64 ||
       2 * a.halo >= t.waves * t.rows)

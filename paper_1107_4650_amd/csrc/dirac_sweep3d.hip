@@ -34,9 +34,7 @@ __device__ __forceinline__ void march3d(const T* __restrict__ src, T* __restrict
   const bool read_v = (MODE == 2) || (FIELD && V != nullptr);
   // under a pulse the array holds the profile P and the step's field integral
   // is F P (a pass is one step; the scale is exactly 1 for a static field)
-  double fscale = 1.0;
-  if constexpr (FIELD)
-    if (a.pulse_on) fscale = pulse_step_integral(a.pulse, 0);
+  const double fscale = a.F[0];
   auto kout_of = [&](int it) -> int64_t { return UP ? kb - 2 + it : ke - it + 1; };
   // the potential (and field integrals) of the TY output rows of iteration it
   auto load_v = [&](int it, double* v, double (*at)[3]) {
@@ -233,12 +231,7 @@ __device__ __forceinline__ void march3d_x2(const T* __restrict__ src, T* __restr
   const bool read_v = (MODE == 2) || (FIELD && V != nullptr);
   // under a pulse the array holds the profile P and step s of the pass carries
   // F[s] P (F is exactly 1 for a static field)
-  double F[2] = {1.0, 1.0};
-  if constexpr (FIELD)
-    if (a.pulse_on) {
-      F[0] = pulse_step_integral(a.pulse, 0);
-      F[1] = pulse_step_integral(a.pulse, 1);
-    }
+  const double F[2] = {a.F[0], a.F[1]};
   const bool zero_walls = !a.periodic;
   auto in_plane = [&](int it) -> int64_t { return UP ? kb - K + it : ke - 1 + K - it; };
   auto plane_of = [&](int it, int st) -> int64_t {
@@ -647,9 +640,7 @@ __global__ __launch_bounds__(256, 2) void k_strang3d_step(const T* __restrict__ 
   const MarchBounds planes(kb, nz, nit);
   // phase mode 3: under a pulse the field array holds the profile P and the
   // step's integral is F P (a pass carries one step's D)
-  double fscale = 1.0;
-  if constexpr (MODE == 3)
-    if (a.pulse_on) fscale = pulse_step_integral(a.pulse, 0);
+  const double fscale = a.F[0];
   // bit t: row y0 - XL + t lies in the box
   uint32_t rin = 0;
 #pragma unroll
@@ -872,7 +863,8 @@ static int64_t strang_step_grid(const SweepArgs& a, SweepArgs& t) {
 
 template <typename T>
 static hipError_t strang3d_t(const void* src, void* dst, void* mid, void* mid2, const double* V,
-                             const SweepArgs& a, int64_t nsteps, hipStream_t st) {
+                             const SweepArgs& a, const PulseK* pulse, int64_t nsteps,
+                             hipStream_t st) {
   const T* s = static_cast<const T*>(src);
   T* d = static_cast<T*>(dst);
   T* m = static_cast<T*>(mid);
@@ -896,7 +888,7 @@ static hipError_t strang3d_t(const void* src, void* dst, void* mid, void* mid2, 
   // with a second scratch state (mid2) src and dst may be the same buffer.
   auto step_pass = [&](bool first_pass, int64_t step, const T* in, T* out) {
     SweepArgs t = first_pass ? first : next;
-    t.pulse.n0 += step;  // the pulse's step index of this pass's D
+    t.F[0] = pulse ? pulse_step_integral(*pulse, static_cast<int>(step)) : 1.0;
     const dim3 g(static_cast<unsigned>(first_pass ? bfirst : bnext));
     if (first_pass) {
       switch (mode) {
@@ -930,11 +922,12 @@ static hipError_t strang3d_t(const void* src, void* dst, void* mid, void* mid2, 
 }
 
 hipError_t launch_strang3d(bool fp64, const void* src, void* dst, void* mid, void* mid2,
-                           const double* V, const SweepArgs& a, int64_t nsteps, hipStream_t st) {
+                           const double* V, const SweepArgs& a, const PulseK* pulse,
+                           int64_t nsteps, hipStream_t st) {
   if (nsteps < 1) return hipErrorInvalidValue;
   if (!mid2 && src == dst) return hipErrorInvalidValue;
-  return fp64 ? strang3d_t<double>(src, dst, mid, mid2, V, a, nsteps, st)
-              : strang3d_t<float>(src, dst, mid, mid2, V, a, nsteps, st);
+  return fp64 ? strang3d_t<double>(src, dst, mid, mid2, V, a, pulse, nsteps, st)
+              : strang3d_t<float>(src, dst, mid, mid2, V, a, pulse, nsteps, st);
 }
 
 // ---- 3-D kernels: one step, or a pass of two fused steps ---------------------

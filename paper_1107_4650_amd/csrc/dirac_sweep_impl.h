@@ -243,10 +243,6 @@ __device__ __forceinline__ void march2d(const T* __restrict__ src, T* __restrict
   using FT = typename std::conditional<FIELD, typename FactorOf<MODE>::type,
                                        typename Stored<T>::type>::type;
   const bool read_v = (MODE == 2) || (FIELD && V != nullptr) || (MODE < 0 && a.ph.mode == 2);
-  // pulse: the field integral factor of each step of the pass
-  double Fs[PULSE ? K : 1];
-#pragma unroll
-  for (int s = 0; s < (PULSE ? K : 1); ++s) Fs[s] = PULSE ? pulse_step_integral(a.pulse, s) : 0.0;
   const bool zero_walls = !a.periodic;
   // input row of iteration it; stage st completes row in_row(it) -+ (st + 1)
   auto in_row = [&](int it) -> int64_t { return UP ? jb - NS + it : je - 1 + NS - it; };
@@ -358,7 +354,7 @@ __device__ __forceinline__ void march2d(const T* __restrict__ src, T* __restrict
         if (S::phase(st)) {
           if constexpr (PULSE)
             apply_field(o, pulse_factors<TWO>(f[((k - st - 1) % P + P) % P],
-                                              Fs[st / S::kStages], a.ph));
+                                              a.F[st / S::kStages], a.ph));
           else if constexpr (FIELD)
             apply_field(o, f[((k - st - 1) % P + P) % P]);
           else
@@ -433,7 +429,7 @@ __device__ __forceinline__ void one_row(const T* __restrict__ src, T* __restrict
     }
     if (S::phase(s)) {
       if constexpr (PULSE)
-        apply_field(m, pulse_factors<TWO>(f, pulse_step_integral(a.pulse, s / S::kStages), a.ph));
+        apply_field(m, pulse_factors<TWO>(f, a.F[s / S::kStages], a.ph));
       else if constexpr (FIELD)
         apply_field(m, f);
       else

@@ -21,7 +21,11 @@
 // order at 2048^2 FP32 28.4 -> 25.7 us.  Large planes are bound by VALU issue
 // (the halo makes a tile of 48 rows and K = 7 do 1.8 times the work it writes)
 // at 4.5 TB/s of reads and writes; small ones by the launch and the first load
-// (about 5 us) and by the barrier and LDS latency of a step (0.7 us).
+// (about 5 us) and by the barrier and LDS latency of a step (0.7 us).  With a
+// vector potential a step is bound by some 150 FP64 operations per cell, the
+// halo counts for more and the tiles win on planes of up to 768^2 cells only
+// (pulse, FP32: 256^2 7.3 -> 2.8 us per step, 768^2 11.1 -> 9.0, 1024^2 13.7
+// marching against 15.6).
 #pragma once
 #include "dirac_device.h"
 #include "dirac_launch.h"
@@ -77,32 +81,53 @@ __device__ __forceinline__ void tile2d(const T* __restrict__ src, T* __restrict_
   // wave-uniform: some cell of the wave lies beyond a zero wall
   const int64_t xs = strip * (64 - 2 * X) - X;
   const bool walls = !a.periodic && (xs < 0 || xs + 63 >= nx || y0 < 0 || y0 + RW > ny);
+  constexpr bool PULSE = MODE == 4;           // ... with a pulse
+  constexpr bool FIELD = MODE == 3 || PULSE;  // local step with a vector potential
   Site<T> s[RW];
-  double v[RW];
+  double v[RW], at[FIELD ? RW : 1][3];
   uint32_t yin = 0;  // bit j: row y0 + j lies in the box
 #pragma unroll
   for (int j = 0; j < RW; ++j) {
     const int64_t q = tile_index(y0 + j, ny, a.periodic) * nx + col;
     load_site(src + q * 8, s[j]);
-    v[j] = (MODE == 2) ? V[q] : 0.0;
+    v[j] = (MODE == 2 || (FIELD && V != nullptr)) ? V[q] : 0.0;
+    if constexpr (FIELD) {
+      at[j][0] = a.At[q];
+      at[j][1] = a.At[a.cells + q];
+      at[j][2] = a.At[2 * a.cells + q];
+    }
     if (y0 + j >= 0 && y0 + j < ny) yin |= 1u << j;
   }
   yin = __builtin_amdgcn_readfirstlane(yin);
-  typename Stored<T>::type f[RW];
+  // the rows' phase factors, U (static field), or scalar phase and profile
+  // (pulse: U is formed per step)
+  using FT = typename std::conditional<FIELD, typename FactorOf<MODE>::type,
+                                       typename Stored<T>::type>::type;
+  FT f[RW];
 #pragma unroll
   for (int j = 0; j < RW; ++j) {
-    Factors fd = factors_of<MODE, TWO>(v[j], a.ph);
-    factors_fix<MODE, TWO>(fd, v[j], a.ph);
-    f[j] = Stored<T>::of(fd);
+    if constexpr (PULSE) {
+      f[j] = pulse_row<TWO>(v[j], at[j][0], at[j][1], at[j][2], a.ph);
+    } else if constexpr (FIELD) {
+      f[j] = field_factors<TWO, false>(v[j], at[j][0], at[j][1], at[j][2], a.ph);
+      field_fix<TWO>(f[j], v[j], at[j][0], at[j][1], at[j][2], a.ph);
+    } else {
+      Factors fd = factors_of<MODE, TWO>(v[j], a.ph);
+      factors_fix<MODE, TWO>(fd, v[j], a.ph);
+      f[j] = Stored<T>::of(fd);
+    }
     if (walls && (!((yin >> j) & 1u) || !xin)) zero(s[j]);
   }
   const int below = wv > 0 ? wv - 1 : 0, above = wv < W - 1 ? wv + 1 : W - 1;
   // One transport pair and its local work per stage.  EDGE: zero the cells
   // beyond a zero wall after every stage, as the marching passes do.
-  auto advance = [&](auto edge) {
+  // FAR: form U with the general sine and cosine where an angle needs them.
+  auto advance = [&](auto edge, auto far) {
     constexpr bool EDGE = decltype(edge)::value;
+    constexpr bool FAR = decltype(far)::value;
     int buf = 0;
     for (int k = 0; k < a.steps; ++k) {
+      const double F = PULSE ? a.F[k] : 1.0;
 #pragma unroll
       for (int st = 0; st < S::kStages; ++st, buf ^= 1) {
         Mov<T> r[RW], l[RW];
@@ -128,13 +153,23 @@ __device__ __forceinline__ void tile2d(const T* __restrict__ src, T* __restrict_
 #pragma unroll
         for (int j = 0; j < RW; ++j) {
           Axis<AX1, T>::combine(j > 0 ? r[j - 1] : rb, j < RW - 1 ? l[j + 1] : la, s[j]);
-          if (S::phase(st)) apply_local<MODE>(s[j], f[j], a.ph);
+          if (S::phase(st)) {
+            if constexpr (PULSE)
+              apply_field(s[j], field_with<TWO, FAR>(f[j].pr, f[j].pi, F * f[j].px, F * f[j].py,
+                                                     F * f[j].pz, a.ph));
+            else if constexpr (FIELD)
+              apply_field(s[j], f[j]);
+            else
+              apply_local<MODE>(s[j], f[j], a.ph);
+          }
           if (S::post_x(st)) {
             Site<T> o;
             x_transport_inner<T, AX0>(s[j], o);
             s[j] = o;
           }
           if (EDGE && walls && (!((yin >> j) & 1u) || !xin)) zero(s[j]);
+          // one row's FP64 temporaries at a time (interleaved rows spill)
+          if (FIELD) __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
@@ -143,10 +178,23 @@ __device__ __forceinline__ void tile2d(const T* __restrict__ src, T* __restrict_
   // beyond a wall; with more rows per wave that loop spills (the test's branch
   // keeps the compiler from interleaving the rows' temporaries), so those
   // waves test in every stage
-  if (RW > 2 || walls)
-    advance(std::true_type{});
-  else
-    advance(std::false_type{});
+  if constexpr (PULSE) {
+    // the largest angle of the pass decides for the whole wave
+    double Fm = 0.0;
+    for (int k = 0; k < a.steps; ++k) Fm = fmax(Fm, fabs(a.F[k]));
+    bool far = false;
+#pragma unroll
+    for (int j = 0; j < RW; ++j)
+      far = far || angle_far<TWO>(Fm * f[j].px, Fm * f[j].py, Fm * f[j].pz, a.ph);
+    if (__any(far))
+      advance(std::true_type{}, std::true_type{});
+    else
+      advance(std::true_type{}, std::false_type{});
+  } else if (RW > 2 || walls) {
+    advance(std::true_type{}, std::false_type{});
+  } else {
+    advance(std::false_type{}, std::false_type{});
+  }
   if (!xin || lane < X || lane > 63 - X) return;
 #pragma unroll
   for (int j = 0; j < RW; ++j) {
@@ -157,7 +205,7 @@ __device__ __forceinline__ void tile2d(const T* __restrict__ src, T* __restrict_
 }
 
 template <typename T, class S, int W, int RW, int AX0, int AX1, int MODE>
-__global__ __launch_bounds__(64 * W, tile2d_waves(sizeof(T) == 8, RW)) void k_tile2d(
+__global__ __launch_bounds__(64 * W, tile2d_waves(sizeof(T) == 8, RW, MODE)) void k_tile2d(
     const T* __restrict__ src, T* __restrict__ dst, const double* __restrict__ V, TileArgs a) {
   __shared__ MovLds<T> sr[2][W], sl[2][W];  // right movers up, left movers down
   int64_t blk = blockIdx.x;
@@ -170,10 +218,22 @@ __global__ __launch_bounds__(64 * W, tile2d_waves(sizeof(T) == 8, RW)) void k_ti
 template <typename T, class S, bool BIG, int AX0, int AX1>
 const void* tile2d_mode(int mode) {
   constexpr TileShape t = tile_shape(sizeof(T) == 8, BIG);
+  constexpr TileShape f = tile_shape(sizeof(T) == 8, BIG, true);
+  constexpr bool kField = BIG || std::is_same<S, LieStep>::value;
   switch (mode) {
     case 0: return reinterpret_cast<const void*>(&k_tile2d<T, S, t.waves, t.rows, AX0, AX1, 0>);
     case 1: return reinterpret_cast<const void*>(&k_tile2d<T, S, t.waves, t.rows, AX0, AX1, 1>);
     case 2: return reinterpret_cast<const void*>(&k_tile2d<T, S, t.waves, t.rows, AX0, AX1, 2>);
+    case 3:
+      if constexpr (kField)
+        return reinterpret_cast<const void*>(&k_tile2d<T, S, f.waves, f.rows, AX0, AX1, 3>);
+      else
+        return nullptr;
+    case 4:
+      if constexpr (kField)
+        return reinterpret_cast<const void*>(&k_tile2d<T, S, f.waves, f.rows, AX0, AX1, 4>);
+      else
+        return nullptr;
     default: return nullptr;
   }
 }
