@@ -352,10 +352,11 @@ int dl_plan_set_depth(dl_plan p, int depth);
  * [7] waves_per_cu setting, [8] XCD-contiguous block order (0/1),
  * [9] graph_pairs, [10] fused steps per pass, [11] workgroups of a
  * single-step pass, [12] reverse steps per pass of dl_grad_step, [13] steps
- * per pass of dl_step_field, [14] steps per pass of the deep passes that 1-D
- * lines run first (0 if the plan has none), [15] steps per register-tile pass
- * of 2-D planes (0: marching passes).  Works on DL_DRY plans.  On a
- * batch handle every
+ * per pass of dl_step_field, [14] 24 on lowest-order lines of at most 65536
+ * cells without a cap on the depth, where the passes of a long run have at least
+ * that many steps (0: other plans), [15] steps per register-tile pass
+ * of 2-D planes (0: marching passes), [16] steps per register pass of 1-D
+ * lines (0: marching passes).  Works on DL_DRY plans.  On a batch handle every
  * value is 0 but [10], the steps fused per pass of the batch, [14] the
  * instances run whole by the lines kernel, [15] its workgroups (0 on a dry
  * batch) and [16] their threads. */

@@ -26,11 +26,8 @@ constexpr int64_t kMaxRow3DFused = int64_t(1) << 28;
 // compiler parking part of the working set in the accumulation registers.
 constexpr int kMaxDepth = 5;
 constexpr int kMaxDepthF64 = 5;
-// 1-D lines of at most kDeep1DMaxCells cells without a vector potential also
-// run passes of kDeep1D lowest-order steps (each wave writes 64 - 2 kDeep1D =
-// 16 cells): such a line's pass is short next to a kernel launch, so fewer,
-// deeper passes win, while on longer lines the fourfold arithmetic of the
-// deep pass costs more than the launches it saves
+// the least steps a pass of a long lowest-order run without a vector potential
+// has on lines of at most kDeep1DMaxCells cells (dl_plan_info)
 constexpr int kDeep1D = 24;
 constexpr int64_t kDeep1DMaxCells = 65536;
 __host__ __device__ constexpr int max_depth(bool fp64, bool strang) {
@@ -115,6 +112,28 @@ __host__ __device__ constexpr int tile2d_waves(bool fp64, int rows, int mode) {
   return fp64 ? (rows > 2 ? 2 : 4) : (rows > 2 ? 4 : 8);
 }
 
+// passes of many steps over a 1-D line (dirac_line_kernels.h): transports
+// between two exchanges, waves of a workgroup and the cells it holds
+constexpr int kLineSync = 8;
+constexpr int kLineWaves = 4;
+constexpr int kLineWavesBig = 16;
+__host__ __device__ constexpr int line_span(int waves) {
+  return waves * (64 - 2 * kLineSync) + 2 * kLineSync;
+}
+// workgroups of kLineWaves or of kLineWavesBig waves; kLineSplit: of kLineWaves,
+// the two uncoupled pairs of a spinor of four in workgroups of their own
+enum LineKind { kLineSmall, kLineBig, kLineSplit };
+constexpr int line_waves(LineKind kind) { return kind == kLineBig ? kLineWavesBig : kLineWaves; }
+constexpr int kMaxLineHalo = 96;  // transports of a pass: 16 of 208 cells written
+struct LineArgs {
+  int64_t nx;
+  int periodic;
+  int steps;
+  int halo;   // cells of a workgroup's span at each end that it does not write
+  int own;    // cells it writes
+  PhaseK ph;
+};
+
 struct ResidentArgs {
   int64_t n;
   int64_t nsteps;
@@ -145,10 +164,12 @@ hipError_t launch_sweep2d_obs(bool fp64, int depth, const void* src, void* dst, 
                               hipStream_t st);
 // true if launch_sweep2d_obs has a kernel for this depth and phase mode
 bool sweep2d_obs_available(bool fp64, int depth, int mode);
-// kDeep1D lowest-order steps src -> dst in one pass over a 1-D line (phase
-// modes 0-2; tiling made for strip_width(kDeep1D))
-hipError_t launch_sweep1d_deep(bool fp64, const void* src, void* dst, const double* V,
-                               const SweepArgs& a, int blocks, hipStream_t st);
+// a.steps steps src -> dst in one pass over a 1-D line (phase modes 0-2) held in
+// workgroups' registers; halo >= transports of the pass, 2 halo + own <= span of
+// the kind, blocks * own >= cells
+hipError_t launch_line(bool fp64, bool strang, LineKind kind, int axis, int nc, const void* src,
+                       void* dst, const double* V, const LineArgs& a, int64_t blocks,
+                       hipStream_t st);
 // a.steps full steps src -> dst on a 2-D grid in register tiles (a.nstrips,
 // a.ntiles made for tile_shape(fp64, big, mode >= 3) and a.halo; with a vector
 // potential second-order steps have the big tiles only)

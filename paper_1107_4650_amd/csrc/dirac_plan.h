@@ -13,14 +13,12 @@ namespace dirac {
 struct PlanTiling {
   SweepArgs a[kMaxDepth]{};  // index depth - 1 (3-D grids: depth 1 only)
   int b[kMaxDepth] = {};     // blocks
-  SweepArgs deep{};          // 1-D lines: passes of kDeep1D steps
-  int deep_b = 0;
 };
 
 // a run of equal passes of a call: marching passes or register tiles of
-// `depth` steps, or the deep passes of 1-D lines
+// `depth` steps, or the register passes of 1-D lines
 struct PassRun {
-  enum Kind { kMarch, kDeep, kTile, kTileBig } kind;
+  enum Kind { kMarch, kLine, kTile, kTileBig } kind;
   int depth;
   int64_t count;
 };
@@ -28,6 +26,7 @@ struct PassList {
   PassRun run[kMaxDepth + 4];
   int n = 0;
   int64_t passes = 0;
+  int line_steps = 0;  // kLine: the most steps of a pass, which set the split of the line
   void add(PassRun::Kind kind, int depth, int64_t count) {
     if (count <= 0) return;
     run[n++] = PassRun{kind, depth, count};
@@ -64,12 +63,11 @@ struct dl_plan_s {
   // for the phase mode of the current call
   dirac::SweepArgs sw[dirac::kMaxDepth]{};
   int bl[dirac::kMaxDepth] = {};
-  dirac::SweepArgs sw_deep{};  // 1-D lines: passes of kDeep1D steps
-  int bl_deep = 0;
   int depth_limit = dirac::kMaxDepth;  // caller's cap on fused steps per pass
   int depth = 1;                        // fused steps per pass in use
   int waves_per_cu = 0;        // 0: size the grid from the kernels' occupancy
   int cu_count = 256;
+  int line_depth = 0;          // 1-D: steps per register pass (0: marching passes)
   int tile_depth = 0;          // 2-D: steps per register-tile pass (0: marching passes)
   bool tile_big = false;       // ... in the larger tiles
   int tile_depth_field = 0;    // the same with a vector potential

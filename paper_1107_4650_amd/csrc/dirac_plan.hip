@@ -230,8 +230,6 @@ static void select_tiling(dl_plan p, int mode) {
     p->sw[d] = t.a[d];
     p->bl[d] = t.b[d];
   }
-  p->sw_deep = t.deep;
-  p->bl_deep = t.deep_b;
 }
 
 // waves that can be resident at once for the sweep kernel of this plan
@@ -306,6 +304,86 @@ static void choose_tile(dl_plan p) {
   }
 }
 
+// The split of a line into workgroups of `kind` for passes of up to `steps`
+// steps: halo and own, and the workgroups (0: no such pass).  own is a whole
+// number of cache lines, and passes that follow each other share the split, so
+// the cells a workgroup reads were written through its own L2 (3e5 cells, FP32,
+// passes of 3 and 2 steps split on their own: 8.6 and 7.9 us, of 2 and 2 5.9).
+static int64_t line_blocks(dl_plan p, LineKind kind, int steps, LineArgs& a) {
+  if (kind == kLineSplit && p->nc != 4) return 0;
+  a.halo = steps * (p->strang ? 2 : 1);
+  a.own = (line_span(line_waves(kind)) - 2 * a.halo) / 8 * 8;
+  if (a.halo > kMaxLineHalo || a.own <= 0) return 0;
+  const int64_t blocks = (p->g.n[0] + a.own - 1) / a.own;
+  // the pairs apart load every cache line twice: only where compute units are
+  // idle otherwise (at most two workgroups each; 4096 cells, FP64: 0.142
+  // against 0.197 us per step, 65536: 0.297 against 0.303, 262144: no gain)
+  if (kind == kLineSplit && 2 * blocks > 2 * int64_t(p->cu_count)) return 0;
+  return blocks <= INT32_MAX ? blocks : 0;
+}
+
+// Fitted time of such a pass in us (rms error 5-10 %, 15 % for the pairs apart;
+// lines of 1000 to 2^22 cells, 2 to 96 transports): a compute unit's first
+// workgroup takes t0 + t1 per step, every further one n0 + n1 per step; at the
+// least the state's bytes at 4.5 TB/s.  Negative: no such pass.
+static double line_cost(dl_plan p, LineKind kind, int steps) {
+  struct Fit { double t0, t1, n0, n1; };
+  static const Fit all[2][2][3] = {  // [fp64][strang][kind]
+      {{{2.66, 0.138, 0.29, 0.067}, {2.71, 0.330, 1.52, 0.261}, {3.15, 0.078, 0.51, 0.026}},
+       {{2.81, 0.210, 0.26, 0.105}, {2.64, 0.522, 1.39, 0.404}, {3.04, 0.124, 0.43, 0.041}}},
+      {{{3.03, 0.149, 1.02, 0.059}, {3.64, 0.361, 4.47, 0.232}, {3.52, 0.088, 1.10, 0.022}},
+       {{2.99, 0.260, 0.95, 0.104}, {3.75, 0.601, 4.57, 0.394}, {3.20, 0.154, 1.05, 0.038}}}};
+  static const Fit pair[2][2][2] = {
+      {{{2.91, 0.076, 0.17, 0.031}, {2.84, 0.166, 0.88, 0.129}},
+       {{2.83, 0.119, 0.16, 0.047}, {2.77, 0.266, 0.84, 0.195}}},
+      {{{2.98, 0.081, 0.41, 0.031}, {3.27, 0.199, 2.04, 0.123}},
+       {{2.94, 0.140, 0.39, 0.054}, {3.19, 0.337, 2.02, 0.206}}}};
+  LineArgs a{};
+  const int64_t blocks = line_blocks(p, kind, steps, a);
+  if (blocks == 0) return -1.0;
+  const Fit& f = p->nc == 4 ? all[p->fp64][p->strang][kind] : pair[p->fp64][p->strang][kind];
+  const double per_cu =
+      static_cast<double>(kind == kLineSplit ? 2 * blocks : blocks) / p->cu_count;
+  const double more = std::max(0.0, (per_cu < 4.0 ? std::ceil(per_cu) : per_cu) - 1.0);
+  return std::max(f.t0 + f.t1 * steps + more * (f.n0 + f.n1 * steps),
+                  2.0 * static_cast<double>(p->state_bytes) / 4.5e6);
+}
+
+// the kind of least fitted time for a pass of `steps` steps; its time
+static double line_best(dl_plan p, int steps, LineKind* kind) {
+  double best = -1.0;
+  for (int k = 0; k < 3; ++k) {
+    const double t = line_cost(p, static_cast<LineKind>(k), steps);
+    if (t > 0.0 && (best < 0.0 || t < best)) {
+      best = t;
+      *kind = static_cast<LineKind>(k);
+    }
+  }
+  return best;
+}
+
+constexpr int64_t kLineFewCells = 200000;
+
+// Lines without a vector potential whose passes are not capped by the caller
+// run register passes of the depth of least fitted time per step (whole
+// exchanges, kLineSync transports); they beat the marching passes at every
+// length (lowest order, FP32, per step: 1000 cells 0.13 us, 2^22 cells 6.8
+// against 12.7 us; second order at 2^20 cells 2.9 us).
+static void choose_line(dl_plan p) {
+  p->line_depth = 0;
+  if (p->g.ndim != 1 || p->depth_limit < kMaxDepth) return;
+  const int per = kLineSync / (p->strang ? 2 : 1);
+  double best = 0.0;
+  for (int k = per; k <= kMaxLineHalo; k += per) {
+    LineKind kind = kLineSmall;
+    const double t = line_best(p, k, &kind);
+    if (t > 0.0 && (p->line_depth == 0 || t / k < best)) {
+      best = t / k;
+      p->line_depth = k;
+    }
+  }
+}
+
 static int plan_tiling(dl_plan p) {
   // fused steps per pass.  A periodic 2-D pass reaches one row per stage (one
   // per lowest-order step, two per second-order step) beyond a segment on each
@@ -342,16 +420,12 @@ static int plan_tiling(dl_plan p) {
       for (int d = 1; d <= (mode >= 3 ? p->depth_field : depth); ++d)
         make_tiling(p->g, resident_waves(p, mode, d), p->seg_override, t.a[d - 1], t.b[d - 1],
                     strip_width(pass_xlanes(p->strang, d)));
-      if (p->g.ndim == 1 && !p->strang && mode <= 2 && p->g.n[0] <= kDeep1DMaxCells) {
-        make_tiling(p->g, resident_waves(p, mode, 1), p->seg_override, t.deep, t.deep_b,
-                    strip_width(kDeep1D));
-        t.deep.periodic = (p->bc == DL_BC_PERIODIC);
-      }
     }
     for (int d = 0; d < kMaxDepth; ++d) t.a[d].periodic = (p->bc == DL_BC_PERIODIC);
   }
   select_tiling(p, 2);
   choose_tile(p);
+  choose_line(p);
   // resident 1-D path: the whole line in one workgroup (4 cells per thread)
   // for all steps of a call.  One workgroup issues every step, so it only
   // beats the tiled passes when those pay a launch for every one or two
@@ -548,22 +622,19 @@ static hipError_t launch_pass_obs(dl_plan p, int depth, const void* src, void* d
                             p->bl[depth - 1], st);
 }
 
-// 1-D lines of lowest-order steps without a vector potential (and no cap on
-// the depth) run passes of kDeep1D steps first
-static bool deep1d(dl_plan p) {
-  return p->g.ndim == 1 && !p->strang && p->ph.mode <= 2 && p->depth_limit >= kMaxDepth &&
-         p->bl_deep > 0;
-}
-
-// one pass of kDeep1D steps src -> dst on a 1-D line
-static hipError_t launch_pass_deep(dl_plan p, const void* src, void* dst, const double* V,
-                                   hipStream_t st) {
-  SweepArgs a = p->sw_deep;
+// one register pass of `steps` steps src -> dst over a 1-D line split for
+// passes of up to `most` steps
+static hipError_t launch_pass_line(dl_plan p, int steps, int most, const void* src, void* dst,
+                                   const double* V, hipStream_t st) {
+  LineKind kind = kLineSmall;
+  LineArgs a{};
+  if (steps > most || line_best(p, most, &kind) < 0.0) return hipErrorInvalidValue;
+  const int64_t blocks = line_blocks(p, kind, most, a);
+  a.nx = p->g.n[0];
+  a.periodic = (p->bc == DL_BC_PERIODIC);
+  a.steps = steps;
   a.ph = p->ph;
-  a.At = nullptr;
-  a.cells = p->cells;
-  a.nc = p->nc;
-  return launch_sweep1d_deep(p->fp64, src, dst, V, a, p->bl_deep, st);
+  return launch_line(p->fp64, p->strang, kind, p->g.axis[0], p->nc, src, dst, V, a, blocks, st);
 }
 
 // one register-tile pass of `depth` steps src -> dst
@@ -578,8 +649,20 @@ static hipError_t launch_pass_tile(dl_plan p, bool big, int depth, const void* s
   return launch_tile2d(p->fp64, p->strang, big, src, dst, V, a, st);
 }
 
-// The passes of a call of `nsteps` steps with the current phase: deep passes
-// (1-D) or register tiles (2-D) where the plan uses them, marching passes for
+// passes for n steps where a pass has at most `depth`: a single one ends in the
+// plan's buffer, so two shallower ones, unless copying the state back (9 us up
+// to 25 MB, then 5.4 TB/s) is cheaper.  time(steps): of a pass
+template <class F>
+static int64_t even_passes(dl_plan p, int64_t n, int depth, F time) {
+  const int64_t passes = (n + depth - 1) / depth;
+  if (passes != 1 || n == 1) return passes;
+  const double copy = std::max(9.0, 2.0 * static_cast<double>(p->state_bytes) / 5.4e6);
+  const int k = static_cast<int>(n);
+  return time(k - k / 2) + time(k / 2) < time(k) + copy ? 2 : 1;
+}
+
+// The passes of a call of `nsteps` steps with the current phase: register
+// passes (1-D) or register tiles (2-D) where the plan uses them, marching passes for
 // the rest, deepest first.  obs: the last pass is the marching pass that sums
 // the observables (on 3-D plans a two-step one, after the single step of an
 // odd count).
@@ -587,9 +670,20 @@ static PassList pass_list(dl_plan p, int64_t nsteps, bool obs) {
   PassList l;
   int64_t left = nsteps;
   const int dmax = (p->ph.mode >= 3) ? p->depth_field : p->depth;
-  if (deep1d(p)) {
-    l.add(PassRun::kDeep, kDeep1D, left / kDeep1D);
-    left %= kDeep1D;
+  // (FP64 calls of two marching passes or one on long lines run those: a wave of
+  // a register pass reads 64 cells to write 48, and short passes are bound by the
+  // bytes; 10 steps: 1e6 cells 63 against 66 us, 4e6 228 against 240)
+  const bool few = p->fp64 && p->cells >= kLineFewCells && left <= 2 * dmax;
+  if (p->line_depth > 0 && p->ph.mode <= 2 && left > 0 && !few) {
+    const int64_t passes = even_passes(p, left, p->line_depth, [&](int k) {
+      LineKind kind = kLineSmall;
+      return line_best(p, k, &kind);
+    });
+    const int d = static_cast<int>(left / passes);  // passes of d + 1 and d steps
+    l.line_steps = static_cast<int>((left + passes - 1) / passes);
+    l.add(PassRun::kLine, d + 1, left % passes);
+    l.add(PassRun::kLine, d, passes - left % passes);
+    return l;
   }
   const bool field = p->ph.mode >= 3;
   const int tile = field ? p->tile_depth_field : p->tile_depth;
@@ -598,16 +692,9 @@ static PassList pass_list(dl_plan p, int64_t nsteps, bool obs) {
     const int64_t n = obs ? left - std::min<int64_t>(left, dmax) : left;
     if (n > 0) {
       const PassRun::Kind kind = big ? PassRun::kTileBig : PassRun::kTile;
-      int64_t passes = (n + tile - 1) / tile;
-      if (passes == 1 && n > 1 && left == n) {
-        // a single pass ends in the plan's buffer: two shallower ones, unless
-        // copying the state back (about 4 us, then 4.5 TB/s) is cheaper
-        const double copy = 4.0 + 2.0 * static_cast<double>(p->state_bytes) / 4.5e6;
-        if (tile_cost(p, field, big, static_cast<int>(n - n / 2)) +
-                tile_cost(p, field, big, static_cast<int>(n / 2)) <
-            tile_cost(p, field, big, static_cast<int>(n)) + copy)
-          passes = 2;
-      }
+      const int64_t passes =
+          left == n ? even_passes(p, n, tile, [&](int k) { return tile_cost(p, field, big, k); })
+                    : (n + tile - 1) / tile;
       const int d = static_cast<int>(n / passes);  // passes of d + 1 and d steps
       l.add(kind, d + 1, n % passes);
       l.add(kind, d, passes - n % passes);
@@ -683,8 +770,8 @@ hipError_t enqueue_steps(dl_plan p, void* psi, const double* V, int64_t nsteps, 
       void* out = third ? (last ? psi : (i % 2 == 0 ? p->tmp : third))
                         : (in == psi ? p->tmp : psi);
       hipError_t e;
-      if (run.kind == PassRun::kDeep)
-        e = launch_pass_deep(p, in, out, V, st);
+      if (run.kind == PassRun::kLine)
+        e = launch_pass_line(p, run.depth, list.line_steps, in, out, V, st);
       else if (run.kind == PassRun::kTile || run.kind == PassRun::kTileBig)
         e = launch_pass_tile(p, run.kind == PassRun::kTileBig, run.depth, in, out, V, st);
       else if (obs && last)
@@ -1108,9 +1195,9 @@ extern "C" int dl_plan_info(dl_plan p, int64_t* info, int n) {
                           t.ntiles,            p->resident,  p->res_threads, p->waves_per_cu,
                           t.xcd_remap,         p->graph_pairs, p->depth,     p->bl[0],
                           reverse_depth(p),    p->depth_field,
-                          (p->g.ndim == 1 && !p->strang && p->depth_limit >= kMaxDepth &&
-                           p->bl_deep > 0) ? kDeep1D : 0,
-                          p->tile_depth};
+                          (p->line_depth > 0 && !p->strang && p->g.n[0] <= kDeep1DMaxCells)
+                              ? kDeep1D : 0,
+                          p->tile_depth, p->line_depth};
   const int nv = static_cast<int>(sizeof vals / sizeof vals[0]);
   for (int i = 0; i < n && i < nv; ++i) info[i] = vals[i];
   return DL_OK;

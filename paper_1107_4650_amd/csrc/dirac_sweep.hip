@@ -136,13 +136,22 @@ hipError_t launch_sweep2d_obs(bool fp64, int depth, const void* src, void* dst, 
   return hipLaunchKernel(fn, dim3(blocks), dim3(256), kargs, 0, st);
 }
 
-hipError_t launch_sweep1d_deep(bool fp64, const void* src, void* dst, const double* V,
-                               const SweepArgs& a, int blocks, hipStream_t st) {
-  const void* fn = kernel1d_deep(fp64, a.axes_code, a.ph.mode, a.nc);
-  if (!fn || blocks <= 0) return hipErrorInvalidValue;
-  SweepArgs args = a;
+const void* kernel_line_f32(bool strang, LineKind kind, int axis, int mode, int nc);
+const void* kernel_line_f64(bool strang, LineKind kind, int axis, int mode, int nc);
+
+hipError_t launch_line(bool fp64, bool strang, LineKind kind, int axis, int nc, const void* src,
+                       void* dst, const double* V, const LineArgs& a, int64_t blocks,
+                       hipStream_t st) {
+  const void* fn = fp64 ? kernel_line_f64(strang, kind, axis, a.ph.mode, nc)
+                        : kernel_line_f32(strang, kind, axis, a.ph.mode, nc);
+  const int W = line_waves(kind);
+  if (!fn || blocks <= 0 || blocks > INT32_MAX || a.own <= 0 || blocks * a.own < a.nx ||
+      a.halo < a.steps * (strang ? 2 : 1) || 2 * a.halo + a.own > line_span(W))
+    return hipErrorInvalidValue;
+  LineArgs args = a;
   void* kargs[] = {const_cast<void**>(&src), &dst, const_cast<double**>(&V), &args};
-  return hipLaunchKernel(fn, dim3(blocks), dim3(256), kargs, 0, st);
+  return hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks), kind == kLineSplit ? 2 : 1),
+                         dim3(64 * W), kargs, 0, st);
 }
 
 hipError_t launch_tile2d(bool fp64, bool strang, bool big, const void* src, void* dst,
