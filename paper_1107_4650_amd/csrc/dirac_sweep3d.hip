@@ -597,6 +597,12 @@ constexpr int kStrangWaves = 4;
 // n - 4 (rings of the right movers of the last four planes per row).  The
 // x-y results are rounded as a stored pass would round them, so the bits are
 // those of the separate passes.
+// What bounds it: operation issue (736 vector operations per wave and plane, 100
+// of them FP64) at the two waves per SIMD that the rings leave.  The rows of the
+// next plane are loaded once those of this one are in LDS, and the stored plane
+// is counted on rather than wrapped anew (300 x 260 x 280, FP32, 8 steps: rows
+// loaded where they are used 4.54 ms, now 3.93 ms, 2.9 TB/s; 1 or 3 rows per wave
+// 4.21 and 4.14 ms).
 template <typename T, int MODE, bool FIRST>
 __global__ __launch_bounds__(256, 2) void k_strang3d_step(const T* __restrict__ src,
                                                           T* __restrict__ dst,
@@ -664,9 +670,16 @@ __global__ __launch_bounds__(256, 2) void k_strang3d_step(const T* __restrict__ 
     x_transport_inner<T, 0>(in, out);
     if (lanes_out) zero(out);
   };
+  // stored plane of the plane after n (stored plane p), wrapped or clamped
+  auto next_plane = [&](int64_t n, int64_t p) -> int64_t {
+    if (a.periodic) return p + 1 < nz ? p + 1 : 0;
+    return n + 1 < 0 ? 0 : (n + 1 >= nz ? nz - 1 : n + 1);
+  };
+  int64_t pin = wrap_or_clamp(kb - 4, nz, a.periodic);  // plane read
+  int64_t pv = wrap_or_clamp(kb - 6, nz, a.periodic);   // plane n - 2
   Site<T> ld[N1];  // this wave's rows of the plane read
-  auto load_rows = [&](int it) {
-    const T* plane = src + wrap_or_clamp(kb - 4 + it, nz, a.periodic) * ny * nx * 8;
+  auto load_rows = [&]() {
+    const T* plane = src + pin * ny * nx * 8;
 #pragma unroll
     for (int j = 0; j < N1; ++j) load_site(plane + rowoff[j] * 8, ld[j]);
   };
@@ -679,6 +692,7 @@ __global__ __launch_bounds__(256, 2) void k_strang3d_step(const T* __restrict__ 
       zero(rd[q][w]);
     }
   }
+  load_rows();
   for (int base = 0;; base += 4) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -687,7 +701,6 @@ __global__ __launch_bounds__(256, 2) void k_strang3d_step(const T* __restrict__ 
       const int64_t n = kb - 4 + it;  // plane read
       const bool n_in = planes.in(it);
       const int bf = FIRST ? (u & 1) : 0;
-      load_rows(it);
       // A on this wave's rows of plane n, their y movers to LDS
 #pragma unroll
       for (int j = 0; j < N1; ++j) {
@@ -701,7 +714,8 @@ __global__ __launch_bounds__(256, 2) void k_strang3d_step(const T* __restrict__ 
         if (t >= 4) l1s[bf][t - 4][lane] = l;
       }
       // potential (and field integrals) of the output rows at plane n - 2
-      const int64_t vplane = wrap_or_clamp(n - 2, nz, a.periodic) * ny * nx;
+      const int64_t vplane = pv * ny * nx;
+      pv = next_plane(n - 2, pv);
       double vv[TW], ax[TW], ay[TW], az[TW];
 #pragma unroll
       for (int j = 0; j < TW; ++j) {
@@ -713,6 +727,10 @@ __global__ __launch_bounds__(256, 2) void k_strang3d_step(const T* __restrict__ 
           az[j] = fscale * a.At[2 * a.cells + q];
         }
       }
+      // the next plane's rows, on their way during the rest of this plane
+      __builtin_amdgcn_sched_barrier(0);
+      pin = next_plane(n, pin);
+      load_rows();
       __syncthreads();
       Site<T> o[TW];  // output rows of the x-y transports
       if constexpr (FIRST) {
