@@ -426,7 +426,7 @@ void choose_register_tiles(Batch& B) {
     for (int k = 1; k <= kMaxTileDepth; ++k) {
       const TileShape t = tile_shape(B.fp64, big != 0);
       if (64 - 2 * k < 16 || t.waves * t.rows - 2 * k < 8) break;
-      const double us = tile_time(B.fp64, false, false, big != 0, k,
+      const double us = tile_time(B.fp64, false, false, big ? kTileBig : kTileSmall, k,
                                   static_cast<double>(register_tiles(B, big != 0, k, nullptr)),
                                   B.cu_count) / k;
       if (B.tile_depth == 0 || us < best) {

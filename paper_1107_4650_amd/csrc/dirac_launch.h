@@ -99,8 +99,15 @@ struct TileArgs {
 // written row (48 of FP32 state, 32 of FP64 state, two workgroups per CU),
 // the other (32 rows of sixteen waves) the shorter chain of work per step,
 // which counts when the grid is a few tiles per CU.
+// On planes of alpha_x and alpha_y without a vector potential the two uncoupled
+// pairs of a spinor can run in workgroups of their own (kTilePairs, kTilePairsBig:
+// tiles of 32 and 64 rows with half the work per row), which fills the chip where
+// the plane has too few tiles.
+enum TileKind { kTileSmall, kTileBig, kTilePairs, kTilePairsBig };
 struct TileShape { int waves, rows; };
-__host__ __device__ constexpr TileShape tile_shape(bool fp64, bool big, bool field = false) {
+__host__ __device__ constexpr TileShape tile_shape(bool fp64, int kind, bool field = false) {
+  const bool big = kind == kTileBig;
+  if (kind >= kTilePairs) return kind == kTilePairs ? TileShape{16, 2} : TileShape{16, 4};
   // with a vector potential a cell takes 18 to 34 registers and the step is
   // bound by FP64 issue, so the tiles are smaller
   if (field) return big ? (fp64 ? TileShape{8, 4} : TileShape{16, 2}) : TileShape{8, 2};
@@ -171,9 +178,9 @@ hipError_t launch_line(bool fp64, bool strang, LineKind kind, int axis, int nc, 
                        void* dst, const double* V, const LineArgs& a, int64_t blocks,
                        hipStream_t st);
 // a.steps full steps src -> dst on a 2-D grid in register tiles (a.nstrips,
-// a.ntiles made for tile_shape(fp64, big, mode >= 3) and a.halo; with a vector
+// a.ntiles made for tile_shape(fp64, kind, mode >= 3) and a.halo; with a vector
 // potential second-order steps have the big tiles only)
-hipError_t launch_tile2d(bool fp64, bool strang, bool big, const void* src, void* dst,
+hipError_t launch_tile2d(bool fp64, bool strang, TileKind kind, const void* src, void* dst,
                          const double* V, const TileArgs& a, hipStream_t st);
 // the two-step 3-D pass (phase modes 0-2) that also sums the observables of
 // the cells it stores: 10 doubles per wave (4 per workgroup tile, a.ntiles

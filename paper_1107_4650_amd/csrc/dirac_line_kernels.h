@@ -29,58 +29,6 @@
 
 namespace dirac {
 
-// The components of a cell that a wave holds.  Along one axis the four fall
-// into two pairs that no term couples: (0, J) and the other two.
-//   kAll: a stored spinor of four; kPair: a stored pair (0, J);
-//   kFirst, kSecond: one pair of a stored spinor of four.
-enum LinePart { kAll, kPair, kFirst, kSecond };
-
-template <int AX, LinePart P>
-struct LineCell {
-  static constexpr int NC = P == kPair ? 2 : 4;  // components of a stored cell
-  static constexpr int NR = P == kAll ? 8 : 4;   // reals held
-  static constexpr int J = pair_second<AX>();
-  // the k-th real held, as real of the spinor
-  __host__ __device__ static constexpr int real_of(int k) {
-    if (P == kAll) return k;
-    const int c = P == kSecond ? (k < 2 ? 1 : 5 - J) : (k < 2 ? 0 : J);
-    return 2 * c + k % 2;
-  }
-  template <typename T>
-  __device__ __forceinline__ static void load(const T* __restrict__ p, int64_t cell, Site<T>& s) {
-    if constexpr (P == kFirst || P == kSecond) {
-      zero(s);
-      load_complex(p + cell * 8 + real_of(0), s.v[real_of(0)], s.v[real_of(1)]);
-      load_complex(p + cell * 8 + real_of(2), s.v[real_of(2)], s.v[real_of(3)]);
-    } else {
-      load_cell<NC, AX>(p, cell, s);
-    }
-  }
-  template <typename T>
-  __device__ __forceinline__ static void store(T* __restrict__ p, int64_t cell, const Site<T>& s) {
-    if constexpr (P == kFirst || P == kSecond) {
-      store_complex(p + cell * 8 + real_of(0), s.v[real_of(0)], s.v[real_of(1)]);
-      store_complex(p + cell * 8 + real_of(2), s.v[real_of(2)], s.v[real_of(3)]);
-    } else {
-      store_cell<NC, AX>(p, cell, s);
-    }
-  }
-  __device__ __forceinline__ static void load_complex(const float* p, float& re, float& im) {
-    const float2 q = *reinterpret_cast<const float2*>(p);
-    re = q.x; im = q.y;
-  }
-  __device__ __forceinline__ static void load_complex(const double* p, double& re, double& im) {
-    const double2 q = *reinterpret_cast<const double2*>(p);
-    re = q.x; im = q.y;
-  }
-  __device__ __forceinline__ static void store_complex(float* p, float re, float im) {
-    *reinterpret_cast<float2*>(p) = make_float2(re, im);
-  }
-  __device__ __forceinline__ static void store_complex(double* p, double re, double im) {
-    *reinterpret_cast<double2*>(p) = make_double2(re, im);
-  }
-};
-
 // what neighbouring waves hand over: the kLineSync valid cells next to the
 // shared ones at the left, then at the right end of every wave
 // ([buffer][16-byte part][wave][cell])
@@ -90,11 +38,11 @@ struct LineEnds {
   uint4 q[2][kParts][W * 2 * kLineSync];
 };
 
-template <typename T, class S, int W, int AX, int MODE, LinePart P>
+template <typename T, class S, int W, int AX, int MODE, CellPart P>
 __device__ __forceinline__ void line_pass(const T* __restrict__ src, T* __restrict__ dst,
                                           const double* __restrict__ V, const LineArgs& a,
-                                          LineEnds<T, W, LineCell<AX, P>::NR>& ends) {
-  using C = LineCell<AX, P>;
+                                          LineEnds<T, W, PartCell<AX, P>::NR>& ends) {
+  using C = PartCell<AX, P>;
   constexpr bool TWO = sizeof(T) == 8;
   constexpr int H = kLineSync, OWN = 64 - 2 * H;
   constexpr int NR = C::NR, PT = LineEnds<T, W, NR>::kParts;
@@ -164,10 +112,10 @@ __device__ __forceinline__ void line_pass(const T* __restrict__ src, T* __restri
 }
 
 // P = kFirst: the workgroups of blockIdx.y = 0 and 1 advance the two pairs
-template <typename T, class S, int W, int AX, int MODE, LinePart P>
+template <typename T, class S, int W, int AX, int MODE, CellPart P>
 __global__ __launch_bounds__(64 * W) void k_line(const T* __restrict__ src, T* __restrict__ dst,
                                                  const double* __restrict__ V, LineArgs a) {
-  __shared__ LineEnds<T, W, LineCell<AX, P>::NR> ends;
+  __shared__ LineEnds<T, W, PartCell<AX, P>::NR> ends;
   if constexpr (P == kFirst) {
     if (blockIdx.y == 0)
       line_pass<T, S, W, AX, MODE, kFirst>(src, dst, V, a, ends);
@@ -178,7 +126,7 @@ __global__ __launch_bounds__(64 * W) void k_line(const T* __restrict__ src, T* _
   }
 }
 
-template <typename T, class S, int W, LinePart P, int AX>
+template <typename T, class S, int W, CellPart P, int AX>
 const void* line_mode(int mode) {
   switch (mode) {
     case 0: return reinterpret_cast<const void*>(&k_line<T, S, W, AX, 0, P>);
@@ -188,7 +136,7 @@ const void* line_mode(int mode) {
   }
 }
 
-template <typename T, class S, int W, LinePart P>
+template <typename T, class S, int W, CellPart P>
 const void* line_axis(int axis, int mode) {
   switch (axis) {
     case 0: return line_mode<T, S, W, P, 0>(mode);

@@ -18,7 +18,7 @@ struct PlanTiling {
 // a run of equal passes of a call: marching passes or register tiles of
 // `depth` steps, or the register passes of 1-D lines
 struct PassRun {
-  enum Kind { kMarch, kLine, kTile, kTileBig } kind;
+  enum Kind { kMarch, kLine, kTile } kind;
   int depth;
   int64_t count;
 };
@@ -69,9 +69,9 @@ struct dl_plan_s {
   int cu_count = 256;
   int line_depth = 0;          // 1-D: steps per register pass (0: marching passes)
   int tile_depth = 0;          // 2-D: steps per register-tile pass (0: marching passes)
-  bool tile_big = false;       // ... in the larger tiles
+  dirac::TileKind tile_kind = dirac::kTileSmall;  // ... and their tiles
   int tile_depth_field = 0;    // the same with a vector potential
-  bool tile_big_field = false;
+  dirac::TileKind tile_kind_field = dirac::kTileSmall;
   dirac::PlanTiling tiling[5];  // per phase mode (3: a vector potential, 4: a pulse)
   int depth_field = 1;          // fused steps per pass with a vector potential
   const double* field = nullptr;  // field integrals (mode 3) or profile (mode 4) of the call
@@ -119,7 +119,7 @@ int phase_mode(double m, const double* V);
 int axes_code(const dl_grid& g);
 void make_tiling(const dl_grid& g, int64_t target, int seg_override, SweepArgs& a, int& blocks,
                  int strip_width);
-double tile_time(bool fp64, bool strang, bool field, bool big, int halo, double tiles,
+double tile_time(bool fp64, bool strang, bool field, TileKind kind, int halo, double tiles,
                  int cu_count);
 int check_live(dl_plan p);
 int check_state_ptr(const void* ptr, const char* name);

@@ -145,11 +145,24 @@ void make_tiling(const dl_grid& g, int64_t target, int seg_override, SweepArgs& 
 // Time of a register-tile pass in us, from fits (rms error 4-9 %) to the
 // passes of 1 to 12 steps (8 with a vector potential) on planes of 128^2 to
 // 4096^2 (2048^2) cells: a compute unit's first tile takes t0 + t1 per transport
-// pair, every further one n0 + n1 per transport pair.
-double tile_time(bool fp64, bool strang, bool field, bool big, int halo, double tiles,
+// pair, every further one n0 + n1 per transport pair.  Without a vector potential
+// and with at most one workgroup per unit (rms error 2-5 %, 64^2 to 640^2), the
+// loads of all workgroups add `load` on a full chip.
+double tile_time(bool fp64, bool strang, bool field, TileKind kind, int halo, double tiles,
                  int cu_count) {
   struct Fit { double t0, t1, n0, n1; };
-  static const Fit fits[2][2][2][2] = {  // [field][fp64][strang][big]
+  struct One { double t0, t1, load; };
+  static const One one[2][2][4] = {  // [fp64][strang][kind]
+      {{{4.7, 0.68, 2.2}, {6.3, 1.03, 3.8}, {4.7, 0.36, 1.4}, {6.8, 0.64, 3.3}},
+       {{4.8, 0.57, 2.8}, {5.8, 1.01, 3.5}, {4.6, 0.34, 1.3}, {6.5, 0.61, 3.1}}},
+      {{{8.4, 0.69, 6.1}, {9.9, 0.92, 6.4}, {6.5, 0.40, 3.2}, {10.3, 0.77, 7.5}},
+       {{8.3, 0.66, 5.7}, {10.8, 0.77, 5.8}, {6.3, 0.38, 3.1}, {10.1, 0.74, 6.5}}}};
+  const double per_cu = (kind >= kTilePairs ? 2.0 : 1.0) * tiles / cu_count;
+  if (!field && (per_cu <= 1.0 || kind >= kTilePairs)) {
+    const One& f = one[fp64][strang][kind];
+    return f.t0 + f.t1 * halo + f.load * per_cu;
+  }
+  static const Fit fits[2][2][2][2] = {  // [field][fp64][strang][kind]
       {{{{5.0, 0.74, 4.2, 0.28}, {7.1, 1.07, 6.4, 0.51}},
         {{5.1, 0.63, 5.2, 0.11}, {6.5, 1.04, 6.0, 0.43}}},
        {{{9.3, 0.79, 15.5, 0.0}, {11.1, 1.0, 10.9, 0.17}},
@@ -158,8 +171,7 @@ double tile_time(bool fp64, bool strang, bool field, bool big, int halo, double 
         {{0.0, 0.0, 0.0, 0.0}, {9.0, 1.59, 11.0, 1.28}}},
        {{{5.9, 1.79, 8.6, 0.92}, {12.2, 3.10, 18.1, 2.76}},
         {{0.0, 0.0, 0.0, 0.0}, {13.7, 2.01, 20.5, 1.52}}}}};
-  const Fit& f = fits[field][fp64][strang][big];
-  const double per_cu = tiles / cu_count;
+  const Fit& f = fits[field][fp64][strang][kind];
   const double more = std::max(0.0, (per_cu < 4.0 ? std::ceil(per_cu) : per_cu) - 1.0);
   return f.t0 + f.t1 * halo + more * (f.n0 + f.n1 * halo);
 }
@@ -244,9 +256,11 @@ static int64_t resident_waves(dl_plan p, int mode, int depth) {
 
 // tiling of a register-tile pass of `steps` steps; false if the tile is too
 // small for them
-static bool tile_args(dl_plan p, bool field, bool big, int steps, TileArgs& a) {
-  if (field && p->strang && !big) return false;
-  const TileShape t = tile_shape(p->fp64, big, field);
+static bool tile_args(dl_plan p, bool field, TileKind kind, int steps, TileArgs& a) {
+  if (field && p->strang && kind != kTileBig) return false;
+  const bool pairs = kind >= kTilePairs;
+  if (pairs && (field || axes_code(p->g) != 10)) return false;
+  const TileShape t = tile_shape(p->fp64, kind, field);
   const int halo = steps * (p->strang ? 2 : 1);
   const int64_t w = 64 - 2 * halo, h = t.waves * t.rows - 2 * halo;
   if (w < 16 || h < (field ? 2 : 8)) return false;
@@ -259,14 +273,20 @@ static bool tile_args(dl_plan p, bool field, bool big, int steps, TileArgs& a) {
   a.ntiles = a.nstrips * ((a.ny + h - 1) / h);
   a.xcd_remap = 1;
   a.axes_code = axes_code(p->g);
+  // the pairs apart double the loads, the set-up and the workgroups: only where
+  // each finds a compute unit of its own (256^2, FP32: 0.97 against 1.19 us per
+  // step; 384^2 with two workgroups on some units 1.45 against 1.34), which takes
+  // a few units to spare (64 rows, FP64, 12 steps: 242 workgroups on 256 units 22
+  // us, 256 of them 52 us)
+  if (pairs && 2 * a.ntiles > p->cu_count - p->cu_count / 20) return false;
   return a.ntiles <= INT32_MAX - 8;
 }
 
 // fitted time of a register-tile pass in us; negative: no such pass
-static double tile_cost(dl_plan p, bool field, bool big, int steps) {
+static double tile_cost(dl_plan p, bool field, TileKind kind, int steps) {
   TileArgs a{};
-  if (!tile_args(p, field, big, steps, a)) return -1.0;
-  return tile_time(p->fp64, p->strang, field, big, a.halo, static_cast<double>(a.ntiles),
+  if (!tile_args(p, field, kind, steps, a)) return -1.0;
+  return tile_time(p->fp64, p->strang, field, kind, a.halo, static_cast<double>(a.ntiles),
                    p->cu_count);
 }
 
@@ -274,9 +294,12 @@ static double tile_cost(dl_plan p, bool field, bool big, int steps) {
 // register tiles where those beat the marching passes: with FP32 state on
 // every plane (per step, Lie: 1.2 against 4.1 us at 256^2, 4.6 against 6.7 us
 // at 1024^2, 14.0 against 17.0 us at 2048^2, 49 against 57 us at 4096^2), with
-// FP64 state up to 600 thousand cells (768^2: 5.5 against 6.4 us, second
-// order 11.0 against 11.1 us; 1024^2: 9.1 against 8.7 and 18.4 against 15.5
-// us).  The tile and the depth are those of the least fitted time per step.
+// FP64 state up to 600 thousand cells (768^2: 5.5 against 6.4 us, second order
+// 600^2 7.9 against 9.2, 680^2 10.6 against 10.2, 760^2 10.8 against 11.3 us;
+// 1024^2: 9.1 against 8.7 and 18.4 against 15.5 us).  The tile and the depth are
+// those of the least fitted time per step; small planes of alpha_x and alpha_y
+// run the two pairs of a spinor apart (per step,
+// Lie: 128^2 FP32 1.15 -> 0.81 us, FP64 1.57 -> 1.06; 512^2 FP64 3.5 -> 2.8).
 // With a vector potential: up to 600 thousand cells (768^2 lowest order, pulse:
 // FP32 9.0 against 11.1 us, FP64 14.1 against 14.8; 1024^2: 15.6 against 13.7
 // and 24.2 against 18.7).
@@ -290,15 +313,15 @@ static void choose_tile(dl_plan p) {
   for (int field = 0; field < 2; ++field) {
     if (!few && (p->fp64 || field)) continue;
     int& depth = field ? p->tile_depth_field : p->tile_depth;
-    bool& in_big = field ? p->tile_big_field : p->tile_big;
+    TileKind& in_kind = field ? p->tile_kind_field : p->tile_kind;
     double best = 0.0;
-    for (int big = 0; big < 2; ++big)
+    for (TileKind kind : {kTileSmall, kTileBig, kTilePairs, kTilePairsBig})
       for (int k = 1; k <= kMaxTileDepth; ++k) {
-        const double t = tile_cost(p, field != 0, big != 0, k);
+        const double t = tile_cost(p, field != 0, kind, k);
         if (t > 0.0 && (depth == 0 || t / k < best)) {
           best = t / k;
           depth = k;
-          in_big = big != 0;
+          in_kind = kind;
         }
       }
   }
@@ -638,15 +661,17 @@ static hipError_t launch_pass_line(dl_plan p, int steps, int most, const void* s
 }
 
 // one register-tile pass of `depth` steps src -> dst
-static hipError_t launch_pass_tile(dl_plan p, bool big, int depth, const void* src, void* dst,
+static hipError_t launch_pass_tile(dl_plan p, int depth, const void* src, void* dst,
                                    const double* V, hipStream_t st) {
   TileArgs a{};
-  if (!tile_args(p, p->ph.mode >= 3, big, depth, a)) return hipErrorInvalidValue;
+  const bool field = p->ph.mode >= 3;
+  const TileKind kind = field ? p->tile_kind_field : p->tile_kind;
+  if (!tile_args(p, field, kind, depth, a)) return hipErrorInvalidValue;
   a.ph = p->ph;
   a.At = p->field;
   a.cells = p->cells;
   if (p->pulse_on) set_pulse(p, a.F, depth);
-  return launch_tile2d(p->fp64, p->strang, big, src, dst, V, a, st);
+  return launch_tile2d(p->fp64, p->strang, kind, src, dst, V, a, st);
 }
 
 // passes for n steps where a pass has at most `depth`: a single one ends in the
@@ -687,17 +712,16 @@ static PassList pass_list(dl_plan p, int64_t nsteps, bool obs) {
   }
   const bool field = p->ph.mode >= 3;
   const int tile = field ? p->tile_depth_field : p->tile_depth;
-  const bool big = field ? p->tile_big_field : p->tile_big;
+  const TileKind tkind = field ? p->tile_kind_field : p->tile_kind;
   if (tile > 0) {
     const int64_t n = obs ? left - std::min<int64_t>(left, dmax) : left;
     if (n > 0) {
-      const PassRun::Kind kind = big ? PassRun::kTileBig : PassRun::kTile;
       const int64_t passes =
-          left == n ? even_passes(p, n, tile, [&](int k) { return tile_cost(p, field, big, k); })
+          left == n ? even_passes(p, n, tile, [&](int k) { return tile_cost(p, field, tkind, k); })
                     : (n + tile - 1) / tile;
       const int d = static_cast<int>(n / passes);  // passes of d + 1 and d steps
-      l.add(kind, d + 1, n % passes);
-      l.add(kind, d, passes - n % passes);
+      l.add(PassRun::kTile, d + 1, n % passes);
+      l.add(PassRun::kTile, d, passes - n % passes);
       left -= n;
     }
   }
@@ -772,8 +796,8 @@ hipError_t enqueue_steps(dl_plan p, void* psi, const double* V, int64_t nsteps, 
       hipError_t e;
       if (run.kind == PassRun::kLine)
         e = launch_pass_line(p, run.depth, list.line_steps, in, out, V, st);
-      else if (run.kind == PassRun::kTile || run.kind == PassRun::kTileBig)
-        e = launch_pass_tile(p, run.kind == PassRun::kTileBig, run.depth, in, out, V, st);
+      else if (run.kind == PassRun::kTile)
+        e = launch_pass_tile(p, run.depth, in, out, V, st);
       else if (obs && last)
         e = launch_pass_obs(p, run.depth, in, out, V, *obs, st, obs_waves);
       else

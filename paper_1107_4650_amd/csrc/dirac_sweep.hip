@@ -154,18 +154,19 @@ hipError_t launch_line(bool fp64, bool strang, LineKind kind, int axis, int nc, 
                          dim3(64 * W), kargs, 0, st);
 }
 
-hipError_t launch_tile2d(bool fp64, bool strang, bool big, const void* src, void* dst,
+hipError_t launch_tile2d(bool fp64, bool strang, TileKind kind, const void* src, void* dst,
                          const double* V, const TileArgs& a, hipStream_t st) {
-  const void* fn = fp64 ? kernel_tile2d_f64(strang, big, a.axes_code, a.ph.mode)
-                        : kernel_tile2d_f32(strang, big, a.axes_code, a.ph.mode);
-  const TileShape t = tile_shape(fp64, big, a.ph.mode >= 3);
+  const void* fn = fp64 ? kernel_tile2d_f64(strang, kind, a.axes_code, a.ph.mode)
+                        : kernel_tile2d_f32(strang, kind, a.axes_code, a.ph.mode);
+  const TileShape t = tile_shape(fp64, kind, a.ph.mode >= 3);
   const int64_t blocks = (a.ntiles + 7) / 8 * 8;
   if (!fn || a.ntiles < 1 || blocks > INT32_MAX || 2 * a.halo >= 64 ||
       2 * a.halo >= t.waves * t.rows)
     return hipErrorInvalidValue;
   TileArgs args = a;
   void* kargs[] = {const_cast<void**>(&src), &dst, const_cast<double**>(&V), &args};
-  return hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(64 * t.waves), kargs, 0, st);
+  return hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks), kind >= kTilePairs ? 2 : 1),
+                         dim3(64 * t.waves), kargs, 0, st);
 }
 
 bool sweep2d_obs_available(bool fp64, int depth, int mode) {

@@ -95,6 +95,59 @@ __device__ __forceinline__ int64_t read_row(int64_t r, int64_t ny, int periodic)
   return w < 0 ? 0 : (w >= ny ? ny - 1 : w);
 }
 
+// The components of a cell that a wave holds.  Along one axis, and on the plane
+// of alpha_x and alpha_y, the four fall into two pairs that no transport, mass or
+// potential couples: (0, J) and the other two.
+//   kAll: a stored spinor of four; kPair: a stored pair (0, J);
+//   kFirst, kSecond: one pair of a stored spinor of four.
+enum CellPart { kAll, kPair, kFirst, kSecond };
+
+template <int AX, CellPart P>
+struct PartCell {
+  static constexpr int NC = P == kPair ? 2 : 4;  // components of a stored cell
+  static constexpr int NR = P == kAll ? 8 : 4;   // reals held
+  static constexpr int J = pair_second<AX>();
+  // the k-th real held, as real of the spinor
+  __host__ __device__ static constexpr int real_of(int k) {
+    if (P == kAll) return k;
+    const int c = P == kSecond ? (k < 2 ? 1 : 5 - J) : (k < 2 ? 0 : J);
+    return 2 * c + k % 2;
+  }
+  template <typename T>
+  __device__ __forceinline__ static void load(const T* __restrict__ p, int64_t cell, Site<T>& s) {
+    if constexpr (P == kFirst || P == kSecond) {
+      zero(s);
+      load_complex(p + cell * 8 + real_of(0), s.v[real_of(0)], s.v[real_of(1)]);
+      load_complex(p + cell * 8 + real_of(2), s.v[real_of(2)], s.v[real_of(3)]);
+    } else {
+      load_cell<NC, AX>(p, cell, s);
+    }
+  }
+  template <typename T>
+  __device__ __forceinline__ static void store(T* __restrict__ p, int64_t cell, const Site<T>& s) {
+    if constexpr (P == kFirst || P == kSecond) {
+      store_complex(p + cell * 8 + real_of(0), s.v[real_of(0)], s.v[real_of(1)]);
+      store_complex(p + cell * 8 + real_of(2), s.v[real_of(2)], s.v[real_of(3)]);
+    } else {
+      store_cell<NC, AX>(p, cell, s);
+    }
+  }
+  __device__ __forceinline__ static void load_complex(const float* p, float& re, float& im) {
+    const float2 q = *reinterpret_cast<const float2*>(p);
+    re = q.x; im = q.y;
+  }
+  __device__ __forceinline__ static void load_complex(const double* p, double& re, double& im) {
+    const double2 q = *reinterpret_cast<const double2*>(p);
+    re = q.x; im = q.y;
+  }
+  __device__ __forceinline__ static void store_complex(float* p, float re, float im) {
+    *reinterpret_cast<float2*>(p) = make_float2(re, im);
+  }
+  __device__ __forceinline__ static void store_complex(double* p, double re, double im) {
+    *reinterpret_cast<double2*>(p) = make_double2(re, im);
+  }
+};
+
 // this lane's column x wrapped around a periodic box, -1 beyond a wall
 __device__ __forceinline__ int64_t wave_col(int64_t nx, int periodic, int64_t x) {
   if (x >= 0 && x < nx) return x;

@@ -4,8 +4,8 @@
 
 namespace dirac {
 
-const void* kernel_tile2d_f32(bool strang, bool big, int axes_code, int mode) {
-  return kernel_tile2d<float>(strang, big, axes_code, mode);
+const void* kernel_tile2d_f32(bool strang, TileKind kind, int axes_code, int mode) {
+  return kernel_tile2d<float>(strang, kind, axes_code, mode);
 }
 
 }  // namespace dirac

@@ -26,6 +26,9 @@
 // halo counts for more and the tiles win on planes of up to 768^2 cells only
 // (pulse, FP32: 256^2 7.3 -> 2.8 us per step, 768^2 11.1 -> 9.0, 1024^2 13.7
 // marching against 15.6).
+// On a small plane of alpha_x and alpha_y the step is the issue of a unit's
+// sixteen waves while other units idle: the two uncoupled pairs of a spinor
+// go to workgroups of their own (256^2, FP32, 100 steps: 119 -> 97 us).
 #pragma once
 #include "dirac_device.h"
 #include "dirac_launch.h"
@@ -35,7 +38,7 @@ namespace dirac {
 
 // one y mover of every lane of a wave, in 16-byte parts (conflict-free
 // 128-bit LDS accesses for both state types)
-template <typename T> struct MovLds {
+template <typename T, CellPart P = kAll> struct MovLds {
   static constexpr int kParts = sizeof(Mov<T>) / 16;
   uint4 q[kParts][64];
   __device__ __forceinline__ void put(int lane, const Mov<T>& m) {
@@ -49,6 +52,24 @@ template <typename T> struct MovLds {
     for (int p = 0; p < kParts; ++p) d[p] = q[p][lane];
   }
 };
+
+// ... of a pair on the plane of alpha_x and alpha_y: one complex number
+template <typename T, CellPart P> struct MovPair {
+  static constexpr int at = P == kSecond ? 2 : 0;
+  struct alignas(2 * sizeof(T)) Complex { T re, im; };
+  Complex q[64];
+  __device__ __forceinline__ void put(int lane, const Mov<T>& m) {
+    q[lane] = Complex{m.v[at], m.v[at + 1]};
+  }
+  __device__ __forceinline__ void get(int lane, Mov<T>& m) const {
+    zero(m);
+    const Complex c = q[lane];
+    m.v[at] = c.re;
+    m.v[at + 1] = c.im;
+  }
+};
+template <typename T> struct MovLds<T, kFirst> : MovPair<T, kFirst> {};
+template <typename T> struct MovLds<T, kSecond> : MovPair<T, kSecond> {};
 
 // r (at most 2^31 + a tile) wrapped around a periodic box, or clamped to the box
 __device__ __forceinline__ int64_t tile_index(int64_t r, int64_t n, int periodic) {
@@ -65,12 +86,15 @@ __device__ __forceinline__ int64_t tile_index(int64_t r, int64_t n, int periodic
 }
 
 // the pass on tile (strip, seg) of the plane: strips of 64 - 2 a.halo written
-// columns, tile rows of W * RW - 2 a.halo
-template <typename T, class S, int W, int RW, int AX0, int AX1, int MODE>
+// columns, tile rows of W * RW - 2 a.halo.  P: the components held (a pair on the
+// plane of alpha_x and alpha_y only, without a vector potential)
+template <typename T, class S, int W, int RW, int AX0, int AX1, int MODE, CellPart P = kAll>
 __device__ __forceinline__ void tile2d(const T* __restrict__ src, T* __restrict__ dst,
                                        const double* __restrict__ V, const TileArgs& a, int lane,
                                        int wv, int64_t strip, int64_t seg,
-                                       MovLds<T> (&sr)[2][W], MovLds<T> (&sl)[2][W]) {
+                                       MovLds<T, P> (&sr)[2][W], MovLds<T, P> (&sl)[2][W]) {
+  static_assert(P == kAll || (AX0 == 0 && AX1 == 1 && MODE <= 2), "pairs do not couple");
+  using C = PartCell<AX0, P>;
   constexpr bool TWO = sizeof(T) == 8;
   const int64_t nx = a.nx, ny = a.ny;
   const int X = a.halo;  // transports per axis of the pass
@@ -89,7 +113,7 @@ __device__ __forceinline__ void tile2d(const T* __restrict__ src, T* __restrict_
 #pragma unroll
   for (int j = 0; j < RW; ++j) {
     const int64_t q = tile_index(y0 + j, ny, a.periodic) * nx + col;
-    load_site(src + q * 8, s[j]);
+    C::load(src, q, s[j]);
     v[j] = (MODE == 2 || (FIELD && V != nullptr)) ? V[q] : 0.0;
     if constexpr (FIELD) {
       at[j][0] = a.At[q];
@@ -200,7 +224,7 @@ __device__ __forceinline__ void tile2d(const T* __restrict__ src, T* __restrict_
   for (int j = 0; j < RW; ++j) {
     const int t = wv * RW + j;  // tile row
     if (((yin >> j) & 1u) && t >= X && t < W * RW - X)
-      store_site(dst + ((y0 + j) * nx + x) * 8, s[j]);
+      C::store(dst, (y0 + j) * nx + x, s[j]);
   }
 }
 
@@ -213,6 +237,41 @@ __global__ __launch_bounds__(64 * W, tile2d_waves(sizeof(T) == 8, RW, MODE)) voi
   if (blk >= a.ntiles) return;  // the whole workgroup
   tile2d<T, S, W, RW, AX0, AX1, MODE>(src, dst, V, a, threadIdx.x & 63, wave_in_block(),
                                       blk % a.nstrips, blk / a.nstrips, sr, sl);
+}
+
+// the pass with the two pairs of a plane of alpha_x and alpha_y in workgroups of
+// their own (blockIdx.y)
+template <typename T, class S, int W, int RW, int MODE>
+__global__ __launch_bounds__(64 * W, 4) void k_tile2d_pairs(const T* __restrict__ src,
+                                                            T* __restrict__ dst,
+                                                            const double* __restrict__ V,
+                                                            TileArgs a) {
+  union Movers {
+    MovLds<T, kFirst> first[2][W];
+    MovLds<T, kSecond> second[2][W];
+  };
+  __shared__ Movers sr, sl;
+  int64_t blk = blockIdx.x;
+  if (a.xcd_remap) blk = (blk % 8) * (gridDim.x / 8) + blk / 8;
+  if (blk >= a.ntiles) return;  // the whole workgroup
+  const int64_t strip = blk % a.nstrips, seg = blk / a.nstrips;
+  if (blockIdx.y == 0)
+    tile2d<T, S, W, RW, 0, 1, MODE, kFirst>(src, dst, V, a, threadIdx.x & 63, wave_in_block(),
+                                            strip, seg, sr.first, sl.first);
+  else
+    tile2d<T, S, W, RW, 0, 1, MODE, kSecond>(src, dst, V, a, threadIdx.x & 63, wave_in_block(),
+                                             strip, seg, sr.second, sl.second);
+}
+
+template <typename T, class S, int KIND>
+const void* tile2d_pairs(int mode) {
+  constexpr TileShape t = tile_shape(sizeof(T) == 8, KIND);
+  switch (mode) {
+    case 0: return reinterpret_cast<const void*>(&k_tile2d_pairs<T, S, t.waves, t.rows, 0>);
+    case 1: return reinterpret_cast<const void*>(&k_tile2d_pairs<T, S, t.waves, t.rows, 1>);
+    case 2: return reinterpret_cast<const void*>(&k_tile2d_pairs<T, S, t.waves, t.rows, 2>);
+    default: return nullptr;
+  }
 }
 
 template <typename T, class S, bool BIG, int AX0, int AX1>
@@ -248,17 +307,26 @@ const void* tile2d_axes(int axes_code, int mode) {
   }
 }
 
+template <typename T, class S>
+const void* tile2d_kind(TileKind kind, int axes_code, int mode) {
+  switch (kind) {
+    case kTileSmall: return tile2d_axes<T, S, false>(axes_code, mode);
+    case kTileBig: return tile2d_axes<T, S, true>(axes_code, mode);
+    case kTilePairs: return axes_code == 10 ? tile2d_pairs<T, S, kTilePairs>(mode) : nullptr;
+    case kTilePairsBig:
+      return axes_code == 10 ? tile2d_pairs<T, S, kTilePairsBig>(mode) : nullptr;
+  }
+  return nullptr;
+}
+
 template <typename T>
-const void* kernel_tile2d(bool strang, bool big, int axes_code, int mode) {
-  if (strang)
-    return big ? tile2d_axes<T, StrangStep, true>(axes_code, mode)
-               : tile2d_axes<T, StrangStep, false>(axes_code, mode);
-  return big ? tile2d_axes<T, LieStep, true>(axes_code, mode)
-             : tile2d_axes<T, LieStep, false>(axes_code, mode);
+const void* kernel_tile2d(bool strang, TileKind kind, int axes_code, int mode) {
+  return strang ? tile2d_kind<T, StrangStep>(kind, axes_code, mode)
+                : tile2d_kind<T, LieStep>(kind, axes_code, mode);
 }
 
 // the instance groups (nullptr for combinations that are not built)
-const void* kernel_tile2d_f32(bool strang, bool big, int axes_code, int mode);
-const void* kernel_tile2d_f64(bool strang, bool big, int axes_code, int mode);
+const void* kernel_tile2d_f32(bool strang, TileKind kind, int axes_code, int mode);
+const void* kernel_tile2d_f64(bool strang, TileKind kind, int axes_code, int mode);
 
 }  // namespace dirac
