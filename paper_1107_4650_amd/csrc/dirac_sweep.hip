@@ -32,7 +32,8 @@ namespace dirac {
 // ---------------------------------------------------------------------------
 // 1-D resident kernel: a whole 1-D instance lives in one workgroup's
 // registers for all its steps; neighbour movers cross thread boundaries
-// through LDS.  Thread t holds cells [t*SPT, (t+1)*SPT).  The per-cell
+// through LDS.  Thread t holds cells [t*SPT, (t+1)*SPT); on a periodic line n is
+// a multiple of SPT.  The per-cell
 // arithmetic is the same as in k_sweep2d, so results are bit-identical.
 // ---------------------------------------------------------------------------
 template <typename T, int AX, int SPT, int NC>
@@ -44,6 +45,7 @@ __global__ __launch_bounds__(1024) void k_resident1d(T* __restrict__ psi,
   const int t = threadIdx.x;
   const int nthr = blockDim.x;
   const int64_t n = a.n;
+  const int last = static_cast<int>((n - 1) / SPT);  // periodic: n - 1 is its last cell
   Site<T> s[SPT];
   typename Stored<T>::type f[SPT];  // as the tiled passes keep them, for the same bits
 #pragma unroll
@@ -69,15 +71,15 @@ __global__ __launch_bounds__(1024) void k_resident1d(T* __restrict__ psi,
     __syncthreads();
     Mov<T> rprev, lnext, scratch;
     if (t > 0) rprev = lds_r[buf][t - 1];
-    else if (a.periodic) rprev = lds_r[buf][nthr - 1];
+    else if (a.periodic) rprev = lds_r[buf][last];
     else zero(rprev);
 #pragma unroll
     for (int k = 0; k < SPT; ++k) {
       if (k < SPT - 1) {
         Axis<AX, T>::movers(s[k + 1], scratch, lnext);
       } else {
-        if (t < nthr - 1) lnext = lds_l[buf][t + 1];
-        else if (a.periodic) lnext = lds_l[buf][0];
+        if (a.periodic && t == last) lnext = lds_l[buf][0];
+        else if (t < nthr - 1) lnext = lds_l[buf][t + 1];
         else zero(lnext);
       }
       Mov<T> rcur;
@@ -207,7 +209,6 @@ static hipError_t launch_res_spt(void* psi, const double* V, const ResidentArgs&
                                  int threads, hipStream_t st) {
   switch (spt) {
     case 1: return launch_res_t<T, AX, 1>(psi, V, a, threads, st);
-    case 2: return launch_res_t<T, AX, 2>(psi, V, a, threads, st);
     case 4: return launch_res_t<T, AX, 4>(psi, V, a, threads, st);
     default: return hipErrorInvalidValue;
   }
