@@ -932,9 +932,12 @@ extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* cons
   (void)hipEventCreate(&e0);
   (void)hipEventCreate(&e1);
   int rc = DL_OK;
-  // time per step of `trials` passes at the current settings
+  // time per step of `trials` passes at the current settings (with register tiles
+  // of twice as many full ones: their pass count is even, and fewer steps would
+  // make shallower passes)
   auto score = [&](double* ms_per_step) -> int {
-    std::vector<int64_t> ns(B.count, int64_t(trials) * B.depth);
+    const int64_t steps = B.tiles ? 2 * int64_t(trials) * B.tile_depth : int64_t(trials) * B.depth;
+    std::vector<int64_t> ns(B.count, steps);
     int r = upload_layout(B);
     if (!r) r = prepare(B, cp.data(), V, ns.data(), st);
     if (!r) r = run(B, ns.data(), st);  // warm-up
@@ -945,7 +948,7 @@ extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* cons
     (void)hipEventSynchronize(e1);
     float ms = 0.f;
     (void)hipEventElapsedTime(&ms, e0, e1);
-    *ms_per_step = ms / (double(trials) * B.depth);
+    *ms_per_step = ms / static_cast<double>(steps);
     return DL_OK;
   };
   // 0. register tiles; the steps below tune the marching passes
