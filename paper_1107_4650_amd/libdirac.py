@@ -151,7 +151,7 @@ def make_grid(shape, axes=None, xmin=None, dx=None) -> Grid:
 
 def _stream_handle():
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 class Plan:
@@ -167,6 +167,7 @@ class Plan:
         self.lib = load()
         self.shape = tuple(int(s) for s in shape)           # x first
         self.tshape = tuple(reversed(self.shape)) + (2 if bispinor else 4,)  # tensor shape
+        self.cshape = self.tshape[:-1]  # shape of one value per cell
         self.dtype_code = _dtype_code(dtype)
         self.dx, self.dt, self.c, self.m = float(dx), float(dt), float(c), float(m)
         self.bc = bc
@@ -178,17 +179,18 @@ class Plan:
                                       self.c, self.m, self.dtype_code, _bc_code(bc), flags))
         self.handle = h
 
-    # -- tensor checks --------------------------------------------------------
+    # -- tensor checks (device pointers as plain integers: the argument types
+    # convert them, and a call of a few steps is bound by this side) ------------
     def _state(self, t, name="psi"):
         import torch
         want = torch.complex64 if self.dtype_code == DL_C64 else torch.complex128
-        if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+        if not isinstance(t, torch.Tensor) or not t.is_cuda:
             raise TypeError(f"{name} must be a CUDA (HIP) tensor")
         if t.dtype != want:
             raise TypeError(f"{name} must be {want}, got {t.dtype}")
-        if tuple(t.shape) != self.tshape or not t.is_contiguous():
+        if t.shape != self.tshape or not t.is_contiguous():
             raise ValueError(f"{name} must be contiguous with shape {self.tshape}")
-        return ctypes.c_void_p(t.data_ptr())
+        return t.data_ptr()
 
     def _cells(self, t, name, allow_none=True):
         import torch
@@ -196,11 +198,11 @@ class Plan:
             if allow_none:
                 return None
             raise ValueError(f"{name} is required")
-        if not isinstance(t, torch.Tensor) or t.device.type != "cuda" or t.dtype != torch.float64:
+        if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != torch.float64:
             raise TypeError(f"{name} must be a float64 CUDA tensor")
-        if tuple(t.shape) != self.tshape[:-1] or not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous with shape {self.tshape[:-1]}")
-        return ctypes.c_void_p(t.data_ptr())
+        if t.shape != self.cshape or not t.is_contiguous():
+            raise ValueError(f"{name} must be contiguous with shape {self.cshape}")
+        return t.data_ptr()
 
     # -- operations -------------------------------------------------------------
     def step(self, psi, V=None, nsteps=1):
