@@ -44,30 +44,34 @@ def log(msg):
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("dirac_device.h", "dirac_sweep_impl.h", "dirac_sweep2d_kernels.h",
-              "dirac_sweep2d_f32_hi.hip", "dirac_launch.h"):
+    for f in ("dirac_device.h", "dirac_sweep_impl.h", "dirac_tile2d_kernels.h",
+              "dirac_tile2d_f32.hip", "dirac_launch.h"):
         with open(os.path.join(ROOT, "paper_1107_4650_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
 
 def timed_sweep(plan, psi, V, steps, warmup, fused=1):
-    """Advance psi by `steps` time steps (rounded down to whole passes of
-    `fused` steps) and time it.  The steps run as one dl_step call, which
-    enqueues the passes back to back in the library (ping-ponging psi and the
-    plan's buffer, ending in psi for an even pass count); HIP events are
-    recorded on the launch stream before and after the call (the pass count
-    is rounded down to an even number).  Returns
-    (wall seconds, mean per-launch ms from the events, final tensor, steps
-    timed)."""
+    """Advance psi by `steps` time steps (rounded down to an even number of
+    groups of `fused` steps) and time it.  The steps run as one dl_step call,
+    which enqueues its passes back to back in the library and ends in psi; HIP
+    events are recorded on the launch stream before and after the call.
+    Returns (wall seconds, mean per-launch ms from the events, final tensor,
+    steps timed, passes of the call)."""
     import torch
     nl, nw = max(1, steps // fused), max(0, warmup // fused)
     if nl > 1 and nl % 2:
-        nl -= 1  # an even pass count ends in psi: no copy back inside the timed region
+        nl -= 1  # an even count of marching passes ends in psi: no copy back in the timed region
     if fused > 1 and plan.info()["depth"] != fused:
         plan.set_depth(fused)
+    tile = plan.info()["tile_2d_depth"]  # register-tile passes of at most that many steps
+    passes = -(-nl * fused // tile) if tile else nl
     if nw:
         plan.step(psi, V, nw * fused)
+    if tile and passes > 2 and passes % 2:
+        # the plan allocates its third state buffer at the first call of an odd
+        # number of passes: not in the timed region
+        plan.step(psi.clone(), V, 3 * tile)
     torch.cuda.synchronize()
     start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     t0 = time.perf_counter()
@@ -76,8 +80,7 @@ def timed_sweep(plan, psi, V, steps, warmup, fused=1):
     end.record()
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
-    per = start.elapsed_time(end) / nl
-    return wall, per, psi, nl * fused
+    return wall, start.elapsed_time(end) / passes, psi, nl * fused, passes
 
 
 def to_dev(x, dtype=None):
@@ -160,11 +163,12 @@ def bench_main(args):
     with L.Plan(w.shape, w.dx, w.dt, w.c, w.m, dtype="c64", xmin=w.xmin) as p32:
         d32 = p32.info()["depth"]
         psi32 = to_dev(w.psi0, torch.complex64)
-        wall32, per32, out32, n32 = timed_sweep(p32, psi32, V, args.steps, args.warmup, d32)
+        wall32, per32, out32, n32, np32 = timed_sweep(p32, psi32, V, args.steps, args.warmup, d32)
         info = p32.info()
         obs32 = p32.observables(out32, 0.0)
     res["fp32"] = dict(wall=wall32, per_launch_ms=per32)
-    log(f"fp32: {wall32 * 1e3 / n32:.4f} ms/step wall, {per32:.4f} ms per {d32}-step launch")
+    log(f"fp32: {wall32 * 1e3 / n32:.4f} ms/step wall, {per32:.4f} ms per launch "
+        f"({np32} launches for {n32} steps)")
     if args.only == "sweep":
         return None
 
@@ -172,8 +176,8 @@ def bench_main(args):
     with L.Plan(w.shape, w.dx, w.dt, w.c, w.m, dtype="c128", xmin=w.xmin) as p64:
         d64 = p64.info()["depth"]
         psi64 = to_dev(w.psi0)
-        wall64, per64, out64, n64 = timed_sweep(p64, psi64, V, n32, args.warmup - args.warmup % d32,
-                                                d64)
+        wall64, per64, out64, n64, np64 = timed_sweep(p64, psi64, V, n32,
+                                                      args.warmup - args.warmup % d32, d64)
         obs64 = p64.observables(out64, 0.0)
     # both runs advanced the same number of steps from the same initial state
     assert n64 == n32, (n64, n32)
@@ -186,10 +190,12 @@ def bench_main(args):
         log(f"vs stored oracle state after {gold['steps']} steps: fp32 rel-L2 "
             f"{gold['fp32_rel_l2']:.3e}, fp64 {gold['fp64_rel_l2']:.3e}")
 
-    # one launch advances every cell d32 steps, reading psi and V once and
-    # writing psi once: 72 B per cell per launch, 72 / d32 B per site-update
+    # one launch advances every cell s32 steps (the mean of the call), reading psi
+    # and V once and writing psi once: 72 B per cell per launch, 72 / s32 B per
+    # site-update
+    s32 = n32 / np32
     achieved = BYTES_F32 * sites / (per32 * 1e-3) / 1e9
-    kname = f"sweep2d_d{d32}_f32_2048"
+    kname = "tile2d_f32_2048"
     prof = load_profile(kname)
     traffic = prof.get("bytes_per_launch") if prof else None
     line = {
@@ -208,18 +214,18 @@ def bench_main(args):
         "config": {"workload": "2-D Dirac, 2048x2048 cells, tanh step V0*tanh(x/0.1), "
                                "Gaussian packet sigma 1.5 p0=(40,0), complex64 state, FP64 V "
                                "and phases, dx=0.01, c*dt=dx, zero walls",
-                   "grid": [2048, 2048], "steps_per_launch": d32,
+                   "grid": [2048, 2048], "steps_per_launch": s32,
                    "tiling": info},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic,
-                     "kernel": f"k_sweep2d<float, LieStep, {d32}, 0, 1, 2, 4>",
+                     "kernel": "k_tile2d<float, LieStep, 8, 6, 0, 1, 2>",
                      "bytes_per_launch_per_cell": BYTES_F32,
-                     "bytes_per_site_update": BYTES_F32 / d32,
-                     "per_launch_ms": per32, "site_updates_per_launch": d32 * sites,
+                     "bytes_per_site_update": BYTES_F32 / s32,
+                     "per_launch_ms": per32, "site_updates_per_launch": s32 * sites,
                      # the fused pass recomputes halo cells and converts to FP64 for the
                      # phase; rocprofv3 counters (SQ_INSTS_VALU) show the SIMDs' VALU
-                     # issue as the limiter of the five-step pass
+                     # issue as the limiter of the pass
                      "valu_busy": prof.get("valu_busy") if prof else None,
                      "profile": prof.get("summary") if prof else None,
                      # a sweep that reads and writes psi (and reads V) once per step
@@ -230,7 +236,7 @@ def bench_main(args):
                                                 / (HBM_PEAK_GBS * 1e9 / BYTES_F32)},
         "fp64": {"value": sites * n64 / wall64, "unit": "site-updates/s",
                  "ms_per_step": wall64 * 1e3 / n64, "per_launch_ms": per64,
-                 "steps_per_launch": d64,
+                 "steps_per_launch": n64 / np64,
                  "roofline_frac": BYTES_F64 * sites / (per64 * 1e-3) / 1e9 / HBM_PEAK_GBS},
         "fp32_vs_fp64_rel_l2": err,
         "fp32_vs_fp64_steps": n32 + args.warmup - args.warmup % d32,
@@ -246,8 +252,8 @@ def bench_extras(args, line):
     from paper_1107_4650_amd import libdirac as L
     from paper_1107_4650_amd.inputs import config_1d_step
     ex = {}
-    # 1-D N = 4096, 2000 steps, complex128 (passes of 24 steps, then 5 and 3); the
-    # warm-up takes the same passes, so the plan's buffers exist before the timing
+    # 1-D N = 4096, 2000 steps, complex128; the warm-up takes the same passes, so the
+    # plan's buffers exist before the timing
     w = config_1d_step()
     with L.Plan(w.shape, w.dx, w.dt, w.c, w.m, dtype="c128", xmin=w.xmin) as p:
         psi = to_dev(w.psi0)
@@ -293,7 +299,7 @@ def bench_extras(args, line):
 def bench_long_line(n=1 << 22, steps=400):
     """A long 1-D line (4M cells, the 1-D workload's packet and step potential
     stretched over a 41.9 a.u. box), complex64: the four-component state vs
-    the two-component one, passes of 5 steps each."""
+    the two-component one, at the plan's depth."""
     import torch
     from paper_1107_4650_amd import libdirac as L
     from paper_1107_4650_amd.inputs import packet, potential_step, C_LIGHT, M_E
@@ -314,7 +320,7 @@ def bench_long_line(n=1 << 22, steps=400):
             e.record()
             torch.cuda.synchronize()
             ms = s.elapsed_time(e)
-            depth = p.info()["depth"]
+            depth = p.info()["line_1d_depth"]
         out[name] = {"ms_per_step": ms / steps, "site_updates_per_s": n * steps / (ms * 1e-3),
                      "steps_per_pass": depth, "bytes_per_cell_per_pass": 8 * 2 * nc + 8}
         del t
@@ -392,7 +398,7 @@ def bench_klein2d(args):
         wall = time.perf_counter() - t0
         ms = s.elapsed_time(e)
         obs = p.observables(psi, 0.0)
-        depth = p.info()["depth"]
+        depth = p.info()["tile_2d_depth"]
     del psi, V
     torch.cuda.empty_cache()
     sites = nx * nz
@@ -489,7 +495,7 @@ def bench_3d(args):
             # the time per step
             with L.Plan((n, n, n), dx, 4 * dx / c, c, m, dtype="complex64", scheme="strang") as p:
                 K = p.info()["depth"]
-                wall, per, _, done = timed_sweep(p, psi, V, max(K, min(steps, 20)), K, fused=K)
+                wall, per, _, done, _ = timed_sweep(p, psi, V, max(K, min(steps, 20)), K, fused=K)
             out[dt_name] = {"steps": done, "ms_per_step": wall * 1e3 / done,
                             "steps_per_call": done, "passes_per_call": done + 1,
                             "dt_over_lowest_order_dt": 4,
@@ -502,7 +508,7 @@ def bench_3d(args):
             if depth is not None:
                 p.set_depth(depth)
             K = p.info()["depth"]
-            wall, per, _, done = timed_sweep(p, psi, V, steps, 2 * K, fused=K)
+            wall, per, _, done, _ = timed_sweep(p, psi, V, steps, 2 * K, fused=K)
         sites = n ** 3
         # every launch reads and writes psi once and reads V once, whatever its depth
         out[dt_name] = {"steps": done, "steps_per_launch": K, "ms_per_step": wall * 1e3 / done,

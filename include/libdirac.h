@@ -136,9 +136,10 @@ int dl_plan_destroy(dl_plan p);
  * nsteps = 0 is a no-op. */
 int dl_step(dl_plan p, void *psi, const double *V, int64_t nsteps, void *stream);
 /* (Several steps are fused into one pass over memory: up to 5 on 1-D and
- * 2-D grids (1-D lines of at most 65536 cells without a vector potential
- * first run passes of 24 steps, each wave writing 16 cells, unless the depth
- * is capped; 2-D planes with FP32 state, and with FP64 state up to 600
+ * 2-D grids (unless the depth is capped, 1-D lines run passes of up to 96
+ * lowest-order or 48 second-order steps in registers, and calls of at most 10
+ * steps, 5 with complex128, on up to 1024 cells in place in one workgroup
+ * (allow_resident, dl_plan_set_tiling); 2-D planes with FP32 state, and with FP64 state up to 600
  * thousand cells, run passes of up to 12 lowest-order or 6 second-order steps
  * in register tiles, unless the depth is capped or the plan retiled), fewer on
  * periodic 2-D boxes of fewer than twice that many rows,
@@ -276,7 +277,8 @@ int dl_seed_adjoint(dl_plan p, const void *psi, double x_b, void *lam, double *Q
  * exactly with DL_BC_PERIODIC (with zero walls it holds only while nothing has
  * left the box).  After N steps from (psi_N, lam_N = M psi_N, Q = 0), Q is
  * dL/dV and psi is the reconstructed psi_0.  Up to 3 reverse steps (2 with
- * complex128 state) are fused into one pass over psi, lam, V and Q, with the
+ * complex128 state; more in the register tiles of 2-D planes without a cap on
+ * the depth) are fused into one pass over psi, lam, V and Q, with the
  * bits of single reverse steps (the terms of Q added in the same order).
  * 3-D grids: one pass per reverse step (Q, D^H, T_z^H, T_y^H, T_x^H) through
  * the plan's scratch states, the result copied back to psi and lam after an
@@ -329,7 +331,8 @@ int dl_batch_step(dl_plan b, void *const *psi, const double *const *V,
  * waves), otherwise that many waves per compute unit; seg_len >= 0: rows (or
  * z planes) per march segment, 0 derives it from the grid size; allow_resident
  * (0/1): let 1-D lines of up to 4096 cells run in one workgroup for all steps
- * when the plan fuses at most 2 steps per pass (dl_plan_set_depth); graph_pairs
+ * when the plan fuses at most 2 steps per pass (dl_plan_set_depth), and short
+ * calls on lines of up to 1024 cells (dl_step); graph_pairs
  * >= 1: a captured graph (DL_GRAPH) holds 2 * graph_pairs steps.  Drops the
  * plan's captured graphs.  The bits of every result are independent of these
  * settings.  DL_ERR_ARG on values out of range. */
