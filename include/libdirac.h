@@ -353,16 +353,23 @@ int dl_plan_set_depth(dl_plan p, int depth);
  * HOST array info: [0] workgroups, [1] rows per march segment, [2] segments,
  * [3] x strips, [4] wave tiles, [5] resident 1-D path (0/1), [6] its threads,
  * [7] waves_per_cu setting, [8] XCD-contiguous block order (0/1),
- * [9] graph_pairs, [10] fused steps per pass, [11] workgroups of a
- * single-step pass, [12] reverse steps per pass of dl_grad_step, [13] steps
- * per pass of dl_step_field, [14] 24 on lowest-order lines of at most 65536
- * cells without a cap on the depth, where the passes of a long run have at least
- * that many steps (0: other plans), [15] steps per register-tile pass
- * of 2-D planes (0: marching passes), [16] steps per register pass of 1-D
- * lines (0: marching passes).  Works on DL_DRY plans.  On a batch handle every
- * value is 0 but [10], the steps fused per pass of the batch, [14] the
- * instances run whole by the lines kernel, [15] its workgroups (0 on a dry
- * batch) and [16] their threads. */
+ * [9] graph_pairs, [10] fused steps per marching pass, [11] workgroups of a
+ * single-step pass, [12] steps per marching pass of dl_grad_step, [13] steps
+ * per marching pass of dl_step_field, [14] obsolete (names no pass: 24 on
+ * lowest-order lines of at most 65536 cells without a cap on the depth, else 0;
+ * read [16]), [15] most steps per register-tile pass of 2-D planes (0: no such
+ * passes), [16] most steps per register pass of 1-D lines (0: no such passes),
+ * [17] the register tiles of a 2-D plane (0 none, 1 small, 2 big; 3 small and 4
+ * big with the two pairs of a spinor in workgroups of their own), [18] most steps
+ * per register-tile pass with a vector potential (0: marching passes), [19] the
+ * same of a long dl_grad_step call.  [0] to [13] describe the marching passes also
+ * where others run; [20] to [23] say what the last call that stepped ran (0
+ * before the first): its marching passes, register-tile passes, register passes
+ * over a line, and launches that carry a line through the whole call.  Works on
+ * DL_DRY plans.  On a batch handle every value is 0 but [10], the steps fused per
+ * marching pass (also by the lines kernel), [14] the instances run whole by the
+ * lines kernel, [15] its workgroups (0 on a dry batch), [16] their threads and
+ * [17] the most steps per register-tile pass (0: marching passes). */
 int dl_plan_info(dl_plan p, int64_t *info, int n);
 
 /* Batch tiling: marching passes with seg_len >= 1 rows per 2-D march segment of

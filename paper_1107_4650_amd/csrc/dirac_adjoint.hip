@@ -993,6 +993,14 @@ static bool rev_tile_choice(dl_plan p, int64_t nsteps, bool* big, int64_t* passe
   return true;
 }
 
+int dirac::reverse_tile_depth(dl_plan p) {
+  const int64_t steps = 1000000;
+  bool big = false;
+  int64_t passes = 0;
+  if (p->strang || p->nc != 4 || !rev_tile_choice(p, steps, &big, &passes)) return 0;
+  return static_cast<int>((steps + passes - 1) / passes);
+}
+
 static int check_adjoint_plan(dl_plan p) {
   int rc = check_live(p);
   if (rc) return rc;
@@ -1045,6 +1053,7 @@ extern "C" int dl_grad_step(dl_plan p, void* psi, void* lam, const double* V, do
     }
   }
   const PhaseK ph = make_phase(p->g.ndim, p->dt, p->c, p->m, phase_mode(p->m, V), p->fp64);
+  p->ran = PassCount{};
   if (p->g.ndim == 3) {  // one pass per reverse step, alternating buffers, ending in psi and lam
     Rev3Args a{};
     a.nx = p->g.n[0];
@@ -1063,6 +1072,7 @@ extern "C" int dl_grad_step(dl_plan p, void* psi, void* lam, const double* V, do
       std::swap(pa, pb);
       std::swap(la, lb);
     }
+    p->ran.of[PassRun::kMarch] = nsteps;
     if (pa != psi) {  // odd step count: the result sits in the plan's buffers
       hipError_t e = hipMemcpyAsync(psi, pa, p->state_bytes, hipMemcpyDeviceToDevice, st);
       if (e == hipSuccess)
@@ -1092,6 +1102,7 @@ extern "C" int dl_grad_step(dl_plan p, void* psi, void* lam, const double* V, do
       std::swap(la, lb);
     }
     left = 0;
+    p->ran.of[PassRun::kTile] = passes;
   }
   for (int d = dmax; d >= 1; --d) {
     if (left < d) continue;
@@ -1102,6 +1113,7 @@ extern "C" int dl_grad_step(dl_plan p, void* psi, void* lam, const double* V, do
     for (; left >= d; left -= d) {
       hipError_t e = launch_rev(p->fp64, d, pb, lb, pa, la, V, Q, a, blocks, st);
       if (e != hipSuccess) return set_hip_error(e, "reverse sweep launch");
+      ++p->ran.of[PassRun::kMarch];
       void* t = pa; pa = pb; pb = t;
       t = la; la = lb; lb = t;
     }

@@ -765,8 +765,8 @@ void destroy_batch(dl_plan p) {
   p->batch = nullptr;
 }
 
-// [10] steps per pass, [14] instances run whole by the lines kernel,
-// [15] its workgroups, [16] their threads
+// [10] steps per marching pass, [14] instances run whole by the lines kernel,
+// [15] its workgroups, [16] their threads, [17] steps per register-tile pass
 void batch_info(dl_plan b, int64_t* info, int n) {
   const Batch& B = *as_batch(b);
   for (int i = 0; i < n; ++i) {
@@ -775,6 +775,7 @@ void batch_info(dl_plan b, int64_t* info, int n) {
     if (i == 14) v = B.nlines;
     if (i == 15) v = B.nbins;
     if (i == 16) v = B.line_threads;
+    if (i == 17) v = B.tiles ? B.tile_depth : 0;
     info[i] = v;
   }
 }
@@ -833,6 +834,7 @@ extern "C" int dl_batch_create(dl_plan* out, const dl_grid* grids, const double*
   apply_cache(*B);
   if (p->dry) {
     choose_lines(*B);
+    if (B->tiles) choose_register_tiles(*B);
     *out = p;
     return DL_OK;
   }

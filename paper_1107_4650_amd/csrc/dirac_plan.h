@@ -22,6 +22,11 @@ struct PassRun {
   int depth;
   int64_t count;
 };
+// passes by kind, of the last call that stepped (dl_plan_info)
+struct PassCount {
+  int64_t of[3] = {};  // by PassRun::Kind
+  int64_t whole = 0;   // launches that carry a 1-D line through all steps of the call
+};
 struct PassList {
   PassRun run[kMaxDepth + 4];
   int n = 0;
@@ -31,6 +36,9 @@ struct PassList {
     if (count <= 0) return;
     run[n++] = PassRun{kind, depth, count};
     passes += count;
+  }
+  void count(PassCount& c, int64_t times) const {
+    for (int r = 0; r < n; ++r) c.of[run[r].kind] += times * run[r].count;
   }
 };
 
@@ -72,6 +80,7 @@ struct dl_plan_s {
   dirac::TileKind tile_kind = dirac::kTileSmall;  // ... and their tiles
   int tile_depth_field = 0;    // the same with a vector potential
   dirac::TileKind tile_kind_field = dirac::kTileSmall;
+  dirac::PassCount ran;        // passes of the last call that stepped
   dirac::PlanTiling tiling[5];  // per phase mode (3: a vector potential, 4: a pulse)
   int depth_field = 1;          // fused steps per pass with a vector potential
   const double* field = nullptr;  // field integrals (mode 3) or profile (mode 4) of the call
@@ -127,6 +136,8 @@ int check_f64_ptr(const void* ptr, const char* name, bool nullable);
 void destroy_batch(dl_plan p);
 // reverse steps fused per pass of dl_grad_step (1 where the adjoint is refused)
 int reverse_depth(dl_plan p);
+// steps of a register-tile pass in a long dl_grad_step call (0: marching passes)
+int reverse_tile_depth(dl_plan p);
 // steps fused per pass of a batch
 int batch_depth(dl_plan b);
 // dl_plan_info of a batch handle

@@ -779,10 +779,12 @@ hipError_t enqueue_steps(dl_plan p, void* psi, const double* V, int64_t nsteps, 
                                    p->pulse_on ? &p->pulse : nullptr, nsteps, st);
     if (e != hipSuccess) return e;
     p->pulse.n0 += nsteps;
+    p->ran.of[PassRun::kMarch] += nsteps + 1;
     *result = psi;
     return hipSuccess;
   }
   const PassList list = pass_list(p, nsteps, obs != nullptr);
+  list.count(p->ran, 1);
   want_alt(p, list.passes, st);
   void* third = (list.passes >= 3 && list.passes % 2 == 1) ? p->alt : nullptr;
   void* in = psi;
@@ -822,14 +824,20 @@ __global__ __launch_bounds__(256) void k_copy16(const uint4* __restrict__ src,
     dst[i] = src[i];
 }
 
+// `replays`: how often the call will launch it (for the plan's pass counts)
 static hipError_t graph_for(dl_plan p, void* psi, const double* V, int64_t pairs,
-                            hipGraphExec_t* exec) {
+                            int64_t replays, hipGraphExec_t* exec) {
+  if (p->g.ndim == 3 && p->strang && p->depth_limit >= kMaxDepth)
+    p->ran.of[PassRun::kMarch] += replays * (2 * pairs + 1);
+  else
+    pass_list(p, 2 * pairs, false).count(p->ran, replays);
   for (auto& ge : p->graphs) {
     if (ge.psi == psi && ge.V == V && ge.pairs == pairs && ge.mode == p->ph.mode) {
       *exec = ge.exec;
       return hipSuccess;
     }
   }
+  const PassCount ran = p->ran;  // the capture itself runs nothing
   if (!p->cap_stream) {
     hipError_t e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking);
     if (e != hipSuccess) return e;
@@ -840,6 +848,7 @@ static hipError_t graph_for(dl_plan p, void* psi, const double* V, int64_t pairs
   if (e != hipSuccess) return e;
   void* res = nullptr;
   hipError_t e2 = enqueue_steps(p, psi, V, 2 * pairs, p->cap_stream, &res);
+  p->ran = ran;
   if (e2 == hipSuccess && res != psi) {
     // an odd number of passes ends in the plan's buffer: every replay must
     // leave the state in psi, where the next one starts
@@ -886,6 +895,7 @@ extern "C" int dl_step(dl_plan p, void* psi, const double* V, int64_t nsteps, vo
   if ((rc = check_f64_ptr(V, "V", true))) return rc;
   if (nsteps < 0) return fail(DL_ERR_ARG, "nsteps = %lld < 0", static_cast<long long>(nsteps));
   if (nsteps == 0) return DL_OK;
+  p->ran = PassCount{};
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int mode = phase_mode(p->m, V);
   p->ph = make_phase(transports_per_step(p), p->dt, p->c, p->m, mode, p->fp64);
@@ -903,14 +913,15 @@ extern "C" int dl_step(dl_plan p, void* psi, const double* V, int64_t nsteps, vo
                                      one ? static_cast<int>((p->g.n[0] + 63) / 64 * 64)
                                          : p->res_threads,
                                      st);
+    p->ran.whole = 1;
     return e == hipSuccess ? DL_OK : hip_fail(e, "resident 1-D sweep launch");
   }
   int64_t done = 0;
   if (p->use_graph && nsteps >= 2 * p->graph_pairs) {
     hipGraphExec_t ex = nullptr;
-    hipError_t e = graph_for(p, psi, V, p->graph_pairs, &ex);
-    if (e != hipSuccess) return hip_fail(e, "graph capture");
     const int64_t reps = nsteps / (2 * p->graph_pairs);
+    hipError_t e = graph_for(p, psi, V, p->graph_pairs, reps, &ex);
+    if (e != hipSuccess) return hip_fail(e, "graph capture");
     for (int64_t r = 0; r < reps; ++r) {
       e = hipGraphLaunch(ex, st);
       if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
@@ -940,6 +951,7 @@ extern "C" int dl_step_field(dl_plan p, void* psi, const double* V, const double
   if (nsteps < 0) return fail(DL_ERR_ARG, "nsteps = %lld < 0", static_cast<long long>(nsteps));
   if (nsteps == 0) return DL_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  p->ran = PassCount{};
   p->ph = make_phase(transports_per_step(p), p->dt, p->c, p->m, 3, p->fp64);
   p->field = A;
   select_tiling(p, 3);
@@ -976,6 +988,7 @@ extern "C" int dl_step_pulse(dl_plan p, void* psi, const double* V, const double
   // 1-D / 2-D: phase mode 4 forms each step's field integral in the pass; 3-D
   // passes run the static-field kernels with At = F P, F of each step
   const int mode = (p->g.ndim == 3) ? 3 : 4;
+  p->ran = PassCount{};
   p->ph = make_phase(transports_per_step(p), p->dt, p->c, p->m, mode, p->fp64);
   p->field = P;
   p->pulse = PulseK{pulse->omega, pulse->phase, pulse->t_on, pulse->t_flat, pulse->t_off,
@@ -1010,6 +1023,8 @@ extern "C" int dl_step_out(dl_plan p, const void* src, void* dst, const double* 
   p->ph = make_phase(transports_per_step(p), p->dt, p->c, p->m, phase_mode(p->m, V), p->fp64);
   p->field = nullptr;
   select_tiling(p, p->ph.mode);
+  p->ran = PassCount{};
+  p->ran.of[PassRun::kMarch] = 1;
   hipError_t e = launch_pass(p, 1, src, dst, V, st);
   return e == hipSuccess ? DL_OK : hip_fail(e, "sweep launch");
 }
@@ -1041,6 +1056,8 @@ extern "C" int dl_step_fused_out(dl_plan p, const void* src, void* dst, const do
       left %= d;
     }
   }
+  p->ran = PassCount{};
+  p->ran.of[PassRun::kMarch] = passes;
   const void* in = src;
   int64_t i = 0, left = nsteps;
   for (int d = p->depth; d >= 1; --d) {
@@ -1160,15 +1177,16 @@ extern "C" int dl_step_observables(dl_plan p, void* psi, const double* V, int64_
     }
     p->tile_partials_n = need;
   }
+  p->ran = PassCount{};
   // whole graphs for all but the steps of the fused pass (at least one step,
   // two on 3-D grids)
   int64_t done = 0;
   const int64_t keep = fused3 ? 2 : 1;
   if (p->use_graph && nsteps - keep >= 2 * p->graph_pairs) {
     hipGraphExec_t ex = nullptr;
-    hipError_t e = graph_for(p, psi, V, p->graph_pairs, &ex);
-    if (e != hipSuccess) return hip_fail(e, "graph capture");
     const int64_t reps = (nsteps - keep) / (2 * p->graph_pairs);
+    hipError_t e = graph_for(p, psi, V, p->graph_pairs, reps, &ex);
+    if (e != hipSuccess) return hip_fail(e, "graph capture");
     for (int64_t r = 0; r < reps; ++r) {
       e = hipGraphLaunch(ex, st);
       if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
@@ -1237,7 +1255,11 @@ extern "C" int dl_plan_info(dl_plan p, int64_t* info, int n) {
                           reverse_depth(p),    p->depth_field,
                           (p->line_depth > 0 && !p->strang && p->g.n[0] <= kDeep1DMaxCells)
                               ? kDeep1D : 0,
-                          p->tile_depth, p->line_depth};
+                          p->tile_depth, p->line_depth,
+                          p->tile_depth > 0 ? p->tile_kind + 1 : 0,
+                          p->tile_depth_field, reverse_tile_depth(p),
+                          p->ran.of[PassRun::kMarch], p->ran.of[PassRun::kTile],
+                          p->ran.of[PassRun::kLine], p->ran.whole};
   const int nv = static_cast<int>(sizeof vals / sizeof vals[0]);
   for (int i = 0; i < n && i < nv; ++i) info[i] = vals[i];
   return DL_OK;

@@ -329,11 +329,15 @@ class Plan:
                                           int(bool(allow_resident)), int(graph_pairs)))
 
     def info(self) -> dict:
-        buf = (ctypes.c_int64 * 17)()
-        check(self.lib.dl_plan_info(self.handle, buf, 17))
+        """What dl_plan_info reports: the marching tiling, the steps per pass of each
+        kind of pass, and under "ran_*" the passes of the last call that stepped."""
+        buf = (ctypes.c_int64 * 24)()
+        check(self.lib.dl_plan_info(self.handle, buf, 24))
         keys = ("blocks", "seg_len", "nseg", "nstrips", "ntiles", "resident", "res_threads",
                 "waves_per_cu", "xcd_remap", "graph_pairs", "depth", "blocks_1", "reverse_depth",
-                "field_depth", "deep_1d_depth", "tile_2d_depth", "line_1d_depth")
+                "field_depth", "deep_1d_depth", "tile_2d_depth", "line_1d_depth",
+                "tile_2d_kind", "tile_field_depth", "tile_reverse_depth", "ran_marching",
+                "ran_tiles", "ran_lines", "ran_whole")
         return dict(zip(keys, buf[:]))
 
     def close(self):
@@ -422,13 +426,14 @@ class Batch:
                                     int(self.depth() if depth is None else depth)))
 
     def info(self) -> dict:
-        buf = (ctypes.c_int64 * 17)()
-        check(self.lib.dl_plan_info(self.handle, buf, 17))
+        buf = (ctypes.c_int64 * 18)()
+        check(self.lib.dl_plan_info(self.handle, buf, 18))
         return {"depth": int(buf[10]), "lines": int(buf[14]), "line_bins": int(buf[15]),
-                "line_threads": int(buf[16])}
+                "line_threads": int(buf[16]), "tile_depth": int(buf[17])}
 
     def depth(self) -> int:
-        """Steps fused per pass of the batch."""
+        """Steps fused per marching pass of the batch (info()["tile_depth"]: per
+        register-tile pass, 0 where it marches)."""
         return self.info()["depth"]
 
     def close(self):
