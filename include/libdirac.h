@@ -141,7 +141,8 @@ int dl_step(dl_plan p, void *psi, const double *V, int64_t nsteps, void *stream)
  * steps, 5 with complex128, on up to 1024 cells in place in one workgroup
  * (allow_resident, dl_plan_set_tiling); 2-D planes with FP32 state, and with FP64 state up to 600
  * thousand cells, run passes of up to 12 lowest-order or 6 second-order steps
- * in register tiles, unless the depth is capped or the plan retiled), fewer on
+ * in register tiles where those are the faster (planes of a few rows and single
+ * steps mostly march), unless the depth is capped or the plan retiled), fewer on
  * periodic 2-D boxes of fewer than twice that many rows,
  * and 2 on 3-D grids with rows of fewer than 2^28 cells; the remainder of
  * nsteps runs in shallower passes.  Second-order steps on 3-D grids take one

@@ -32,6 +32,7 @@ struct PassList {
   int n = 0;
   int64_t passes = 0;
   int line_steps = 0;  // kLine: the most steps of a pass, which set the split of the line
+  LineKind line_kind = kLineSmall;
   void add(PassRun::Kind kind, int depth, int64_t count) {
     if (count <= 0) return;
     run[n++] = PassRun{kind, depth, count};
@@ -81,6 +82,11 @@ struct dl_plan_s {
   int tile_depth_field = 0;    // the same with a vector potential
   dirac::TileKind tile_kind_field = dirac::kTileSmall;
   dirac::PassCount ran;        // passes of the last call that stepped
+  // the passes of the last (phase mode, steps, observables) asked for
+  dirac::PassList list;
+  int list_mode = -1;
+  int64_t list_steps = -1;
+  bool list_obs = false;
   dirac::PlanTiling tiling[5];  // per phase mode (3: a vector potential, 4: a pulse)
   int depth_field = 1;          // fused steps per pass with a vector potential
   const double* field = nullptr;  // field integrals (mode 3) or profile (mode 4) of the call

@@ -13,6 +13,7 @@
 
 #include "../../include/libdirac.h"
 #include "dirac_launch.h"
+#include "dirac_pass_cost.h"
 #include "dirac_trace.h"
 #include "dirac_plan.h"
 
@@ -290,19 +291,16 @@ static double tile_cost(dl_plan p, bool field, TileKind kind, int steps) {
                    p->cu_count);
 }
 
-// 2-D plans whose passes are not capped or retiled by the caller run in
-// register tiles where those beat the marching passes: with FP32 state on
-// every plane (per step, Lie: 1.2 against 4.1 us at 256^2, 4.6 against 6.7 us
-// at 1024^2, 14.0 against 17.0 us at 2048^2, 49 against 57 us at 4096^2), with
-// FP64 state up to 600 thousand cells (768^2: 5.5 against 6.4 us, second order
-// 600^2 7.9 against 9.2, 680^2 10.6 against 10.2, 760^2 10.8 against 11.3 us;
-// 1024^2: 9.1 against 8.7 and 18.4 against 15.5 us).  The tile and the depth are
-// those of the least fitted time per step; small planes of alpha_x and alpha_y
-// run the two pairs of a spinor apart (per step,
-// Lie: 128^2 FP32 1.15 -> 0.81 us, FP64 1.57 -> 1.06; 512^2 FP64 3.5 -> 2.8).
-// With a vector potential: up to 600 thousand cells (768^2 lowest order, pulse:
-// FP32 9.0 against 11.1 us, FP64 14.1 against 14.8; 1024^2: 15.6 against 13.7
-// and 24.2 against 18.7).
+// The register tiles of 2-D plans whose passes are not capped or retiled by the
+// caller; a call takes them where they are predicted to beat the marching passes
+// (pass_list).  With FP32 state on planes of any size (per step, Lie, potential: 1.2
+// against 4.1 us at 256^2, 4.6 against 6.7 us at 1024^2, 14.0 against 17.0 us at
+// 2048^2), with FP64 state or a vector potential up to 600 thousand cells (768^2 FP64
+// 5.5 against 6.4 us; 1024^2 9.1 against 8.7, second order 18.4 against 15.5; pulse,
+// 768^2: FP32 9.0 against 11.1 us, FP64 14.1 against 14.8; 1024^2: 15.6 against 13.7
+// and 24.2 against 18.7).  The tile and the depth are those of the least fitted time
+// per step; small planes of alpha_x and alpha_y run the two pairs of a spinor apart
+// (per step, Lie: 128^2 FP32 1.15 -> 0.81 us, FP64 1.57 -> 1.06; 512^2 FP64 3.5 -> 2.8).
 constexpr int64_t kTileMaxCells = 600000;
 
 static void choose_tile(dl_plan p) {
@@ -408,6 +406,7 @@ static void choose_line(dl_plan p) {
 }
 
 static int plan_tiling(dl_plan p) {
+  p->list_mode = -1;
   // fused steps per pass.  A periodic 2-D pass reaches one row per stage (one
   // per lowest-order step, two per second-order step) beyond a segment on each
   // side and wraps once, so the box needs at least twice that many rows.  A
@@ -647,11 +646,11 @@ static hipError_t launch_pass_obs(dl_plan p, int depth, const void* src, void* d
 
 // one register pass of `steps` steps src -> dst over a 1-D line split for
 // passes of up to `most` steps
-static hipError_t launch_pass_line(dl_plan p, int steps, int most, const void* src, void* dst,
-                                   const double* V, hipStream_t st) {
-  LineKind kind = kLineSmall;
+static hipError_t launch_pass_line(dl_plan p, LineKind kind, int steps, int most,
+                                   const void* src, void* dst, const double* V,
+                                   hipStream_t st) {
   LineArgs a{};
-  if (steps > most || line_best(p, most, &kind) < 0.0) return hipErrorInvalidValue;
+  if (steps > most) return hipErrorInvalidValue;
   const int64_t blocks = line_blocks(p, kind, most, a);
   a.nx = p->g.n[0];
   a.periodic = (p->bc == DL_BC_PERIODIC);
@@ -674,24 +673,63 @@ static hipError_t launch_pass_tile(dl_plan p, int depth, const void* src, void* 
   return launch_tile2d(p->fp64, p->strang, kind, src, dst, V, a, st);
 }
 
+// copying the state back from the plan's buffer: 9 us up to 25 MB, then 5.4 TB/s
+static double copy_us(dl_plan p) {
+  return std::max(9.0, 2.0 * static_cast<double>(p->state_bytes) / 5.4e6);
+}
+
 // passes for n steps where a pass has at most `depth`: a single one ends in the
-// plan's buffer, so two shallower ones, unless copying the state back (9 us up
-// to 25 MB, then 5.4 TB/s) is cheaper.  time(steps): of a pass
+// plan's buffer, so two shallower ones, unless copying the state back is cheaper.
+// time(steps): of a pass
 template <class F>
 static int64_t even_passes(dl_plan p, int64_t n, int depth, F time) {
   const int64_t passes = (n + depth - 1) / depth;
   if (passes != 1 || n == 1) return passes;
-  const double copy = std::max(9.0, 2.0 * static_cast<double>(p->state_bytes) / 5.4e6);
   const int k = static_cast<int>(n);
-  return time(k - k / 2) + time(k / 2) < time(k) + copy ? 2 : 1;
+  return time(k - k / 2) + time(k / 2) < time(k) + copy_us(p) ? 2 : 1;
+}
+
+// predicted time of a 2-D call's passes (dirac_pass_cost.h)
+static double list_us(dl_plan p, const PassList& l) {
+  const int mode = p->ph.mode;
+  const TileKind kind = mode >= 3 ? p->tile_kind_field : p->tile_kind;
+  const double cells = static_cast<double>(p->cells);
+  double us = l.passes == 1 ? copy_us(p) : 0.0;
+  for (int r = 0; r < l.n; ++r) {
+    const int d = l.run[r].depth;
+    double t = 0.0;
+    if (l.run[r].kind == PassRun::kTile) {
+      TileArgs a{};
+      if (tile_args(p, mode >= 3, kind, d, a))
+        t = tile_pass_us(p->fp64, p->strang, mode, kind, a.halo, static_cast<double>(a.ntiles),
+                         cells, p->cu_count);
+    } else {
+      const SweepArgs& a = p->sw[d - 1];
+      t = march_pass_us(p->fp64, p->strang, mode, d,
+                        mode >= 3 ? field_max_depth(p->fp64, p->strang)
+                                  : max_depth(p->fp64, p->strang),
+                        a.H, static_cast<double>(a.ny) / static_cast<double>(a.nseg),
+                        p->bl[d - 1], cells, p->cu_count);
+    }
+    us += t * static_cast<double>(l.run[r].count);
+  }
+  return us;
+}
+
+// `left` steps in marching passes, deepest first, appended to l
+static void add_marching(PassList& l, int64_t left, int dmax) {
+  for (int d = dmax; d >= 1; --d) {
+    l.add(PassRun::kMarch, d, left / d);
+    left %= d;
+  }
 }
 
 // The passes of a call of `nsteps` steps with the current phase: register
-// passes (1-D) or register tiles (2-D) where the plan uses them, marching passes for
-// the rest, deepest first.  obs: the last pass is the marching pass that sums
-// the observables (on 3-D plans a two-step one, after the single step of an
-// odd count).
-static PassList pass_list(dl_plan p, int64_t nsteps, bool obs) {
+// passes (1-D) or register tiles (2-D) where the plan uses them and, in 2-D, they are
+// predicted to be the faster, marching passes for the rest, deepest first.  obs: the
+// last pass is the marching pass that sums the observables (on 3-D plans a two-step
+// one, after the single step of an odd count).
+static PassList make_pass_list(dl_plan p, int64_t nsteps, bool obs) {
   PassList l;
   int64_t left = nsteps;
   const int dmax = (p->ph.mode >= 3) ? p->depth_field : p->depth;
@@ -706,6 +744,7 @@ static PassList pass_list(dl_plan p, int64_t nsteps, bool obs) {
     });
     const int d = static_cast<int>(left / passes);  // passes of d + 1 and d steps
     l.line_steps = static_cast<int>((left + passes - 1) / passes);
+    (void)line_best(p, l.line_steps, &l.line_kind);
     l.add(PassRun::kLine, d + 1, left % passes);
     l.add(PassRun::kLine, d, passes - left % passes);
     return l;
@@ -713,27 +752,36 @@ static PassList pass_list(dl_plan p, int64_t nsteps, bool obs) {
   const bool field = p->ph.mode >= 3;
   const int tile = field ? p->tile_depth_field : p->tile_depth;
   const TileKind tkind = field ? p->tile_kind_field : p->tile_kind;
-  if (tile > 0) {
-    const int64_t n = obs ? left - std::min<int64_t>(left, dmax) : left;
-    if (n > 0) {
-      const int64_t passes =
-          left == n ? even_passes(p, n, tile, [&](int k) { return tile_cost(p, field, tkind, k); })
-                    : (n + tile - 1) / tile;
-      const int d = static_cast<int>(n / passes);  // passes of d + 1 and d steps
-      l.add(PassRun::kTile, d + 1, n % passes);
-      l.add(PassRun::kTile, d, passes - n % passes);
-      left -= n;
-    }
+  const int64_t n = obs ? left - std::min<int64_t>(left, dmax) : left;  // steps tiles may take
+  if (tile > 0 && n > 0) {
+    const int64_t passes =
+        left == n ? even_passes(p, n, tile, [&](int k) { return tile_cost(p, field, tkind, k); })
+                  : (n + tile - 1) / tile;
+    const int d = static_cast<int>(n / passes);  // passes of d + 1 and d steps
+    l.add(PassRun::kTile, d + 1, n % passes);
+    l.add(PassRun::kTile, d, passes - n % passes);
+    add_marching(l, left - n, dmax);
+    PassList m;
+    add_marching(m, left, dmax);
+    return list_us(p, m) < (l.passes == 1 ? 1.0 : 0.95) * list_us(p, l) ? m : l;
   }
   if (obs && p->g.ndim == 3 && p->depth == 2 && left % 2 == 1 && left > 1) {
     l.add(PassRun::kMarch, 1, 1);
     --left;
   }
-  for (int d = dmax; d >= 1; --d) {
-    l.add(PassRun::kMarch, d, left / d);
-    left %= d;
-  }
+  add_marching(l, left, dmax);
   return l;
+}
+
+// ... kept for the next call of the same kind (the choice takes the host 0.3 us)
+static const PassList& pass_list(dl_plan p, int64_t nsteps, bool obs) {
+  if (p->list_mode != p->ph.mode || p->list_steps != nsteps || p->list_obs != obs) {
+    p->list = make_pass_list(p, nsteps, obs);
+    p->list_mode = p->ph.mode;
+    p->list_steps = nsteps;
+    p->list_obs = obs;
+  }
+  return p->list;
 }
 
 // The plan's third state buffer: with it, an odd number (>= 3) of passes
@@ -797,7 +845,7 @@ hipError_t enqueue_steps(dl_plan p, void* psi, const double* V, int64_t nsteps, 
                         : (in == psi ? p->tmp : psi);
       hipError_t e;
       if (run.kind == PassRun::kLine)
-        e = launch_pass_line(p, run.depth, list.line_steps, in, out, V, st);
+        e = launch_pass_line(p, list.line_kind, run.depth, list.line_steps, in, out, V, st);
       else if (run.kind == PassRun::kTile)
         e = launch_pass_tile(p, run.depth, in, out, V, st);
       else if (obs && last)

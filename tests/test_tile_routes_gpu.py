@@ -1,0 +1,53 @@
+"""2-D calls run in register tiles only where those are the faster: planes a few rows
+thin, which fill a small part of a tile, march, also for single steps; small and
+ordinary planes stay in the tiles.  The bits are those of single marching steps."""
+import numpy as np
+import pytest
+
+from paper_1107_4650_amd import libdirac as L
+from paper_1107_4650_amd.inputs import random_spinor
+from tests.gpu_util import announce, gpu_step, same_bits
+
+pytestmark = pytest.mark.gpu
+
+C = 137.036
+DX = 0.01
+
+# measured, us, tiles against marching passes: 2^20 x 2 1542 / 534 (20 steps), 262144 x 8
+# 357 / 235, 300000 x 3 407 / 197; one step 172 / 46, 62 / 47, 55 / 23; FP64 30000 x 3, 5
+# steps 34 / 24
+THIN = [((1 << 20, 2), "c64", 20), ((1 << 20, 2), "c64", 1), ((262144, 8), "c64", 20),
+        ((300000, 3), "c64", 20), ((300000, 3), "c64", 1), ((30000, 3), "c128", 5)]
+TILED = [((256, 256), "c64", 20), ((4000, 4), "c64", 20), ((3000, 60), "c64", 20),
+         ((2048, 2048), "c64", 20), ((512, 512), "c128", 20)]
+
+
+@pytest.mark.parametrize("scheme", ["lie", "strang"])
+@pytest.mark.parametrize("shape,dtype,nsteps,tiles", [c + (False,) for c in THIN] +
+                         [c + (True,) for c in TILED])
+def test_route_of_a_call(shape, dtype, nsteps, tiles, scheme):
+    import torch
+    announce(f"route {shape} {dtype} n={nsteps} {scheme}")
+    dt = (1 if scheme == "lie" else 2) * DX / C
+    t = torch.ones(shape[::-1] + (4,), dtype=torch.complex64 if dtype == "c64" else
+                   torch.complex128, device="cuda")
+    V = torch.zeros(shape[::-1], dtype=torch.float64, device="cuda")
+    with L.Plan(shape, DX, dt, C, 1.0, dtype=dtype, scheme=scheme) as p:
+        p.step(t, V, nsteps)
+        torch.cuda.synchronize()
+        i = p.info()
+    assert (i["ran_tiles"] > 0, i["ran_marching"] > 0) == (tiles, not tiles), i
+
+
+@pytest.mark.parametrize("scheme", ["lie", "strang"])
+@pytest.mark.parametrize("shape,bc", [((30000, 3), "zero"), ((30000, 4), "periodic"),
+                                      ((40000, 5), "periodic"), ((40000, 8), "zero")])
+def test_thin_planes_keep_single_step_bits(shape, bc, scheme):
+    announce(f"thin plane {shape} {bc} {scheme}")
+    psi = random_spinor(shape[::-1], seed=shape[1])
+    V = np.random.default_rng(shape[1]).uniform(-3, 3, size=shape[::-1]) * C * C
+    kw = dict(dx=DX, dt=(1 if scheme == "lie" else 2) * DX / C, c=C, bc=bc, scheme=scheme)
+    for dtype in ("c64", "c128"):
+        for nsteps in (1, 2, 5, 13):
+            single = gpu_step(psi, V, m=1.0, nsteps=nsteps, depth=1, dtype=dtype, **kw)
+            assert same_bits(gpu_step(psi, V, m=1.0, nsteps=nsteps, dtype=dtype, **kw), single)
