@@ -763,7 +763,8 @@ static PassList make_pass_list(dl_plan p, int64_t nsteps, bool obs) {
     add_marching(l, left - n, dmax);
     PassList m;
     add_marching(m, left, dmax);
-    return list_us(p, m) < (l.passes == 1 ? 1.0 : 0.95) * list_us(p, l) ? m : l;
+    const double margin = l.passes == 1 || (p->fp64 && p->strang) ? 1.0 : 0.95;
+    return list_us(p, m) < margin * list_us(p, l) ? m : l;
   }
   if (obs && p->g.ndim == 3 && p->depth == 2 && left % 2 == 1 && left > 1) {
     l.add(PassRun::kMarch, 1, 1);

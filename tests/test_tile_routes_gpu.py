@@ -39,6 +39,21 @@ def test_route_of_a_call(shape, dtype, nsteps, tiles, scheme):
     assert (i["ran_tiles"] > 0, i["ran_marching"] > 0) == (tiles, not tiles), i
 
 
+@pytest.mark.parametrize("n,tiles", [(600, True), (660, False), (680, False), (700, False),
+                                     (720, False), (774, False)])
+def test_second_order_fp64_planes_around_the_crossing(n, tiles):
+    # measured, us per 36 steps, tiles / marching: 600^2 283 / 327, 660^2 366 / 343, 680^2
+    # 376 / 363, 700^2 389 / 361, 720^2 397 / 364, 774^2 469 / 396
+    import torch
+    announce(f"route FP64 second order {n}^2")
+    t = torch.ones((n, n, 4), dtype=torch.complex128, device="cuda")
+    V = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+    with L.Plan((n, n), DX, 2 * DX / C, C, 1.0, dtype="c128", scheme="strang") as p:
+        p.step(t, V, 36)
+        torch.cuda.synchronize()
+        assert (p.info()["ran_tiles"] > 0) == tiles
+
+
 @pytest.mark.parametrize("scheme", ["lie", "strang"])
 @pytest.mark.parametrize("shape,bc", [((30000, 3), "zero"), ((30000, 4), "periodic"),
                                       ((40000, 5), "periodic"), ((40000, 8), "zero")])
