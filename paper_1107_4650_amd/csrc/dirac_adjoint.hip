@@ -21,6 +21,7 @@
 // transport of a reverse step, narrows the valid lanes by one on each side),
 // and marches along y as the forward passes do.
 #include "dirac_device.h"
+#include "dirac_pass_cost.h"
 #include "dirac_plan.h"
 #include "dirac_sweep_impl.h"
 #include "dirac_tile2d_kernels.h"
@@ -898,7 +899,7 @@ static void rev_tiling(dl_plan p, int depth, RevArgs& a, int& blocks) {
   if (p->waves_per_cu > 0) {
     target = int64_t(p->cu_count) * p->waves_per_cu;
   } else {
-    int occ = rev_occ(p->fp64, depth, a.axes_code);
+    int occ = p->dry ? rev_min_blocks(p->fp64, depth) : rev_occ(p->fp64, depth, a.axes_code);
     if (occ <= 0) occ = 2;
     target = int64_t(occ) * 4 * p->cu_count;
   }
@@ -959,14 +960,14 @@ static double rev_tile_cost(dl_plan p, bool big, int steps) {
   return f.t0 + f.t1 * steps + more * (f.n0 + f.n1 * steps);
 }
 
-// 2-D plans whose passes are not capped or retiled by the caller run their
-// reverse steps in register tiles, which beat the marching reverse passes on
-// every plane and both state types (per step, FP32: 1.8 against 7.9 us at
+// The register tiles of the reverse steps of 2-D plans whose passes are not capped or
+// retiled by the caller (per step, FP32: 1.8 against 7.9 us in marching passes at
 // 128^2, 11.5 against 15.0 at 1024^2, 38.8 against 50.6 at 2048^2; FP64: 2.2
-// against 11.1, 25.9 against 37.9, 101 against 136).
-static bool rev_tile_choice(dl_plan p, int64_t nsteps, bool* big, int64_t* passes) {
+// against 11.1, 25.9 against 37.9, 101 against 136): the most steps of a pass, and
+// their shape.  rev_route says which calls take them.
+static int rev_tile_choice(dl_plan p, int64_t nsteps, bool* big) {
   if (p->g.ndim != 2 || p->depth_limit < kMaxDepth || p->waves_per_cu > 0 || p->seg_override > 0)
-    return false;
+    return 0;
   int depth = 0;
   double best = 0.0;
   for (int b = 0; b < 2; ++b)
@@ -978,27 +979,69 @@ static bool rev_tile_choice(dl_plan p, int64_t nsteps, bool* big, int64_t* passe
         *big = b != 0;
       }
     }
-  if (depth == 0) return false;
-  // an odd number of passes ends in the plan's buffers: one pass more, unless
-  // copying both states back (about 4 us, then 4.5 TB/s each) is cheaper
-  auto cost = [&](int64_t n) -> double {
-    const int d = static_cast<int>(nsteps / n);
-    const double more = static_cast<double>(nsteps % n);
-    const double t = (more > 0.0 ? more * rev_tile_cost(p, *big, d + 1) : 0.0) +
-                     (static_cast<double>(n) - more) * rev_tile_cost(p, *big, d);
-    return n % 2 == 0 ? t : t + 2.0 * (4.0 + 2.0 * static_cast<double>(p->state_bytes) / 4.5e6);
+  return depth;
+}
+
+// Register tiles (their passes, *big) or marching passes (0) for a call of nsteps
+// reverse steps of a 2-D plane: the less predicted time (dirac_pass_cost.h), an odd
+// count of passes with the copy of both states back.
+static int64_t rev_choose(dl_plan p, int mode, int64_t nsteps, bool* big) {
+  const int depth = rev_tile_choice(p, nsteps, big);
+  if (depth == 0) return 0;
+  const double cells = static_cast<double>(p->cells);
+  // both states: 9 us up to 25 MB, then 5.6 TB/s each (2048^2, FP32: 91 us)
+  const double copy = 2.0 * std::max(9.0, 2.0 * static_cast<double>(p->state_bytes) / 5.6e6);
+  auto tile = [&](int64_t d) {
+    TileArgs a{};
+    rev_tile_args(p, *big, static_cast<int>(d), a);
+    return rev_tile_pass_us(p->fp64, mode, *big, static_cast<int>(d),
+                            static_cast<double>(a.ntiles), cells, p->cu_count);
   };
-  const int64_t n = (nsteps + depth - 1) / depth;
-  *passes = (n < nsteps && cost(n + 1) < cost(n)) ? n + 1 : n;
-  return true;
+  auto tiles_us = [&](int64_t passes) {
+    const double more = static_cast<double>(nsteps % passes);
+    double t = (static_cast<double>(passes) - more) * tile(nsteps / passes);
+    if (more > 0.0) t += more * tile(nsteps / passes + 1);
+    return passes % 2 == 1 ? t + copy : t;
+  };
+  int64_t passes = (nsteps + depth - 1) / depth;
+  double t = tiles_us(passes);
+  if (passes < nsteps && tiles_us(passes + 1) < t) t = tiles_us(++passes);
+  double m = 0.0;
+  int64_t left = nsteps, marching = 0;
+  for (int d = reverse_depth(p); d >= 1; --d) {
+    if (left < d) continue;
+    RevArgs a{};
+    int blocks = 0;
+    rev_tiling(p, d, a, blocks);
+    m += static_cast<double>(left / d) *
+         rev_march_pass_us(p->fp64, mode, d, p->fp64 ? kMaxRevDepthF64 : kMaxRevDepthF32, a.H,
+                           static_cast<double>(a.ny) / static_cast<double>(a.nseg), blocks, cells,
+                           p->cu_count);
+    marching += left / d;
+    left %= d;
+  }
+  if (marching % 2 == 1) m += copy;
+  return m < 0.97 * t ? 0 : passes;
+}
+
+// ... kept for the next call of as many steps (a marching tiling asks the runtime for
+// occupancies)
+static int64_t rev_route(dl_plan p, int mode, int64_t nsteps, bool* big) {
+  if (p->rev_steps != nsteps || p->rev_mode != mode) {
+    p->rev_passes = rev_choose(p, mode, nsteps, &p->rev_big);
+    p->rev_steps = nsteps;
+    p->rev_mode = mode;
+  }
+  *big = p->rev_big;
+  return p->rev_passes;
 }
 
 int dirac::reverse_tile_depth(dl_plan p) {
   const int64_t steps = 1000000;
   bool big = false;
-  int64_t passes = 0;
-  if (p->strang || p->nc != 4 || !rev_tile_choice(p, steps, &big, &passes)) return 0;
-  return static_cast<int>((steps + passes - 1) / passes);
+  if (p->strang || p->nc != 4 || p->g.ndim != 2) return 0;
+  const int64_t passes = rev_choose(p, 2, steps, &big);
+  return passes > 0 ? static_cast<int>((steps + passes - 1) / passes) : 0;
 }
 
 static int check_adjoint_plan(dl_plan p) {
@@ -1088,8 +1131,8 @@ extern "C" int dl_grad_step(dl_plan p, void* psi, void* lam, const double* V, do
   void* lb = p->tmp2;
   int64_t left = nsteps;
   bool big = false;
-  int64_t passes = 0;
-  if (rev_tile_choice(p, nsteps, &big, &passes)) {  // passes of d + 1 steps, then of d
+  const int64_t passes = rev_route(p, ph.mode, nsteps, &big);
+  if (passes > 0) {  // register tiles: passes of d + 1 steps, then of d
     for (int64_t i = 0; i < passes; ++i) {
       TileArgs a{};
       const int d = static_cast<int>(nsteps / passes + (i < nsteps % passes ? 1 : 0));

@@ -131,4 +131,44 @@ inline double march_pass_us(bool fp64, bool strang, int mode, int depth, int dee
                   rows_mean, blocks, pass_bytes(forward_mb(cells, fp64, mode)), cu_count);
 }
 
+// The reverse passes of a 2-D plane (phase modes 0 to 2), fitted to the same planes; a
+// tile pass hides part of its bytes behind its steps (1.5-norm of both).  A tile holds 16
+// (small) or 24 rows, so planes a few rows thin lose here too (2^20 x 2, a pass of one
+// reverse step: FP32 152 against 75 us, FP64 362 against 172).  Errors 5 to 7 %; a call
+// marches where that is predicted to be 3 % faster.  Of 2800 measured calls of 1 to 120
+// reverse steps 457 ran over 3 % slower than marching, at worst 1.7 times; by this rule
+// 66 do, at worst 1.2 times.
+inline PassBytes reverse_bytes(double cells, bool fp64, int mode) {
+  return pass_bytes(cells * ((fp64 ? 256 : 128) + 16 + (mode == 2 ? 8 : 0)) / 1e6);
+}
+inline double rev_tile_pass_us(bool fp64, int mode, bool big, int steps, double tiles,
+                               double cells, int cu_count) {
+  static const TileFit fits[2][3][2] = {  // [fp64][phase mode][big]
+    {{{3.13, 1.03, 0.371, 0.723, 0.137, 0.0719}, {3.54, 1.49, 0.589, 1.05, 0.128, 0.07}},
+     {{3.06, 1.32, 0.482, 0.866, 0.134, 0.0636}, {3.53, 1.84, 0.576, 1.3, 0.123, 0.0683}},
+     {{3.57, 1.29, 0.801, 0.888, 0.136, 0.0587}, {4.45, 1.85, 1.16, 1.3, 0.121, 0.0743}}},
+    {{{4.78, 1.24, 2.65, 1.25, 0.238, 0.0259}, {6.09, 1.76, 3.67, 1.73, 0.233, 0.0518}},
+     {{4.6, 1.39, 2.67, 1.36, 0.239, 0.0192}, {5.89, 1.88, 3.76, 1.81, 0.232, 0.0455}},
+     {{5.37, 1.33, 3.73, 1.26, 0.236, 0.0187}, {6.91, 1.84, 4.98, 1.77, 0.229, 0.0482}}}};
+  const TileFit& f = fits[fp64][mode][big];
+  const PassBytes b = reverse_bytes(cells, fp64, mode);
+  const double more =
+      std::max(0.0, per_unit(tiles, cu_count) - 1.0) * (f.n0 + f.n1 * steps);
+  const double memory = f.m * b.mb + f.o * b.beyond;
+  return f.t0 + f.t1 * steps +
+         std::cbrt(std::pow(more * std::sqrt(more) + memory * std::sqrt(memory), 2.0));
+}
+inline double rev_march_pass_us(bool fp64, int mode, int depth, int deepest, int rows,
+                                double rows_mean, double blocks, double cells, int cu_count) {
+  static const MarchFit fits[2][3][2] = {  // [fp64][phase mode][K = 1, deepest]
+    {{{4.49, 0.339, 0.36, 0.0824, 0.134}, {2.61, 1.38, 1.44, 0.00245, 0.0569}},
+     {{4.7, 0.372, 0.417, 0.0734, 0.137}, {2.4, 1.54, 1.63, 0, 0.0414}},
+     {{4.9, 0.469, 0.498, 0.065, 0.135}, {2.13, 1.65, 1.75, 0.00383, 0.037}}},
+    {{{5.01, 0.882, 1.11, 0.116, 0.0535}, {6.79, 1.06, 1.23, 0.0921, 0.0834}},
+     {{5, 0.894, 1.13, 0.115, 0.0537}, {6.99, 1.09, 1.26, 0.0904, 0.0831}},
+     {{5.63, 1.12, 1.4, 0.102, 0.0515}, {6.85, 1.38, 1.52, 0.0909, 0.0649}}}};
+  return march_us(fits[fp64][mode], depth, deepest, depth, rows, rows_mean, blocks,
+                  reverse_bytes(cells, fp64, mode), cu_count);
+}
+
 }  // namespace dirac

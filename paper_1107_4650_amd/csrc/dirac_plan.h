@@ -87,6 +87,11 @@ struct dl_plan_s {
   int list_mode = -1;
   int64_t list_steps = -1;
   bool list_obs = false;
+  // ... and of the last 2-D dl_grad_step: passes of the register tiles, 0: marching
+  int64_t rev_steps = -1;
+  int rev_mode = -1;
+  int64_t rev_passes = 0;
+  bool rev_big = false;
   dirac::PlanTiling tiling[5];  // per phase mode (3: a vector potential, 4: a pulse)
   int depth_field = 1;          // fused steps per pass with a vector potential
   const double* field = nullptr;  // field integrals (mode 3) or profile (mode 4) of the call

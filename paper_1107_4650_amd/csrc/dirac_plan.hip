@@ -407,6 +407,7 @@ static void choose_line(dl_plan p) {
 
 static int plan_tiling(dl_plan p) {
   p->list_mode = -1;
+  p->rev_steps = -1;
   // fused steps per pass.  A periodic 2-D pass reaches one row per stage (one
   // per lowest-order step, two per second-order step) beyond a segment on each
   // side and wraps once, so the box needs at least twice that many rows.  A
