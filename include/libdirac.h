@@ -318,8 +318,9 @@ int dl_batch_create(dl_plan *out, const dl_grid *grids, const double *dx,
  * (at most 2^20 cells), run whole in a
  * persistent kernel (a workgroup carries a bin of such lines through all of
  * their steps); the others advance by one launch per pass of fused steps over
- * a table of tiles (register tiles, as in dl_step, until dl_batch_set or a
- * tuning chooses marching passes); the two run concurrently (a second stream forked from and
+ * a table of tiles (register tiles, as in dl_step, unless most cells lie in
+ * instances a few rows thin, until dl_batch_set or a tuning chooses marching
+ * passes; dl_plan_info says which); the two run concurrently (a second stream forked from and
  * joined to `stream`).  Synchronises `stream` before it rewrites the
  * descriptors of the previous call. */
 int dl_batch_step(dl_plan b, void *const *psi, const double *const *V,

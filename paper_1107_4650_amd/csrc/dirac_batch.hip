@@ -11,8 +11,9 @@
 //     pass in the register tiles of the single plans (k_batch_tile): one
 //     launch per pass over a flat table of tiles, every instance splitting its
 //     steps evenly over its passes;
-//   * once the caller sets march segments and a depth (dl_batch_set, or a
-//     tuning that found them faster), those instances march instead: one
+//   * in batches mostly of instances a few rows thin, and once the caller sets march
+//     segments and a depth (dl_batch_set, or a tuning that found them faster), those
+//     instances march instead: one
 //     launch per pass of D fused steps over a table of tiles (instance, strip
 //     of 64 - 2D columns, march segment), longest first, so that the in-order
 //     workgroup dispatch is a longest-processing-time list schedule;
@@ -40,6 +41,7 @@
 #include <string>
 #include <vector>
 
+#include "dirac_pass_cost.h"
 #include "dirac_plan.h"
 #include "dirac_sweep_impl.h"
 #include "dirac_tile2d_kernels.h"
@@ -315,6 +317,7 @@ struct Batch {
   int depth = 1;                    // steps fused per pass
   int depth_cap = 5;                // largest depth the instances allow
   bool tiles = true;                // 2-D instances and long lines: register tiles, else march
+  bool tiles_cached = false;        // ... as the tuning cache says
   bool tile_big = false;            // ... their shape and largest depth
   int tile_depth = 1;
   int seg_of[kMaxClass] = {};       // march segment length per 2-D size class
@@ -435,6 +438,43 @@ void choose_register_tiles(Batch& B) {
         B.tile_big = big != 0;
       }
     }
+}
+
+// Instances a few rows thin fill a small part of a register tile: a new batch marches
+// where that is predicted to take under 0.7 of the tiles' time per step (the fits of
+// dirac_pass_cost.h with a potential; marching batches, which read the phase mode and the
+// geometry from tables, measured 1.4 times theirs, tiles 1.1).  100 steps, FP32, tiles
+// against marching passes: 30 instances of 20000 x 4 4820 us / 2245, of 20000 x 12 4400 /
+// 3765, of 20000 x 32 7466 / 7836; 100 of 256^2 3094 / 3130.
+bool marching_beats_tiles(const Batch& B) {
+  double waves = 0.0, rows = 0.0, cells = 0.0;
+  int most = 0;
+  for (int k = 0; k < B.count; ++k) {
+    if (B.h_insts[k].line) continue;
+    const dl_grid& g = B.grids[k];
+    const int64_t ny = g.ndim > 1 ? g.n[1] : 1;
+    const int64_t H = std::max<int64_t>(1, std::min<int64_t>(B.seg_of[size_class(ny)], ny));
+    const double strips =
+        static_cast<double>((g.n[0] + strip_width(B.depth) - 1) / strip_width(B.depth));
+    waves += strips * static_cast<double>((ny + H - 1) / H);
+    rows += strips * static_cast<double>(ny);
+    cells += static_cast<double>(cells_of(g));
+    most = std::max(most, static_cast<int>(H));
+  }
+  if (waves == 0.0) return false;
+  const double march = march_pass_us(B.fp64, false, 2, B.depth, max_depth(B.fp64, false), most,
+                                     rows / waves, std::ceil(waves / 4.0), cells, B.cu_count);
+  const double tile = tile_pass_us(
+      B.fp64, false, 2, B.tile_big ? kTileBig : kTileSmall, B.tile_depth,
+      static_cast<double>(register_tiles(B, B.tile_big, B.tile_depth, nullptr)), cells, B.cu_count);
+  return march / B.depth < 0.7 * tile / B.tile_depth;
+}
+
+// lines and, unless the tuning cache chose, tiles or marching passes of a new batch
+void choose_passes(Batch& B) {
+  choose_lines(B);
+  choose_register_tiles(B);
+  if (!B.tiles_cached) B.tiles = !marching_beats_tiles(B);
 }
 
 // bins of lines: as many as the lines' share of the cells asks for (twice
@@ -733,6 +773,7 @@ void apply_cache(Batch& B) {
       B.depth = std::min(v, B.depth_cap);
     } else if (std::strcmp(key, "2d-march") == 0) {
       B.tiles = v != 1;
+      B.tiles_cached = true;
     } else if (std::strcmp(key, "1d-threads") == 0) {
       if (v % 64 == 0 && v <= 1024) B.line_threads = v;
     } else if (std::sscanf(key, "2d-rows%d-seg", &cls) == 1 && cls >= 0 && cls < kMaxClass) {
@@ -833,8 +874,7 @@ extern "C" int dl_batch_create(dl_plan* out, const dl_grid* grids, const double*
   }
   apply_cache(*B);
   if (p->dry) {
-    choose_lines(*B);
-    if (B->tiles) choose_register_tiles(*B);
+    choose_passes(*B);
     *out = p;
     return DL_OK;
   }
@@ -864,7 +904,7 @@ extern "C" int dl_batch_create(dl_plan* out, const dl_grid* grids, const double*
     I.periodic = (bc == DL_BC_PERIODIC);
     I.axes_code = axes_code(grids[k]);
   }
-  choose_lines(*B);
+  choose_passes(*B);
   int rc = upload_layout(*B);
   if (rc) {
     free_batch(B);
