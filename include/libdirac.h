@@ -376,7 +376,8 @@ int dl_plan_info(dl_plan p, int64_t *info, int n);
 
 /* Batch tiling: marching passes with seg_len >= 1 rows per 2-D march segment of
  * every size class, depth in 1 .. the batch's largest (5, less on periodic boxes of few rows)
- * fused steps per pass.  Results stay bit-identical. */
+ * fused steps per pass, in place of register tiles, also those a tuning kept
+ * (dl_batch_autotune can choose them again).  Results stay bit-identical. */
 int dl_batch_set(dl_plan b, int seg_len, int depth);
 
 /* Autotuner of the batch's tile shapes: a coordinate search, timed on a
@@ -386,10 +387,12 @@ int dl_batch_set(dl_plan b, int seg_len, int depth);
  * then the march segment length (16 .. 512 rows) of each 2-D size class
  * present (class = floor(log2(rows))), then the workgroup size of the lines
  * kernel (256 .. 1024 threads, 512 with complex128); the marching passes so
- * tuned are kept only if they beat the register tiles.  Each candidate runs
- * `trials` passes after a warm-up and is scored by its time per step.
- * chosen (HOST, may be NULL) receives 3 ints: the depth, the lines workgroup
- * size and the segment length of the largest size class (0 if none).
+ * tuned are kept only if they beat the register tiles, both timed over the same
+ * steps.  Each candidate of the search runs `trials` passes after a warm-up and is
+ * scored by its time per step.  chosen (HOST, may be NULL) receives 3 ints: the
+ * depth of the marching passes, the lines workgroup size and the march segment
+ * length of the largest size class (0 if none), also where the register tiles won
+ * and those passes do not run: entry [17] of dl_plan_info says which did.
  * Allocates a scratch copy of all states for the call; synchronises
  * `stream`.  When the environment variable LIBDIRAC_TUNE_CACHE names a file,
  * appends one line per setting, "dirac-batch <c64|c128> <key> <value>" with

@@ -37,6 +37,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <numeric>
 #include <new>
 #include <string>
 #include <vector>
@@ -937,12 +938,14 @@ extern "C" int dl_batch_step(dl_plan b, void* const* psi, const double* const* V
   return run(B, nsteps, st);
 }
 
-// Coordinate search over the batch's tile shapes, timed on a scratch copy of
+// Coordinate search over the batch's marching passes, timed on a scratch copy of
 // the states (the caller's arrays are not modified): first the pass depth
 // (steps per pass: the strip width 64 - 2D follows), then the march segment
-// length of each 2-D size class present (largest class first), then the lines
-// kernel's workgroup size.  Each candidate runs `trials` passes after one
-// warm-up run, without graphs, and is scored by its time per step.
+// length of each 2-D size class present (largest class first).  The passes so
+// tuned and the register tiles then run the same number of steps, whole passes and
+// an even count of both (neither copies a state back), and the faster stay; last the
+// lines kernel's workgroup size.  Each candidate of the search runs `trials` passes
+// after one warm-up run, without graphs, and is scored by its time per step.
 extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* const* V, int trials,
                                  int* chosen, void* stream) {
   dirac::TraceRange trace_range("dl_batch_autotune");
@@ -974,11 +977,8 @@ extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* cons
   (void)hipEventCreate(&e0);
   (void)hipEventCreate(&e1);
   int rc = DL_OK;
-  // time per step of `trials` passes at the current settings (with register tiles
-  // of twice as many full ones: their pass count is even, and fewer steps would
-  // make shallower passes)
-  auto score = [&](double* ms_per_step) -> int {
-    const int64_t steps = B.tiles ? 2 * int64_t(trials) * B.tile_depth : int64_t(trials) * B.depth;
+  // time per step of `steps` steps at the current settings
+  auto time_steps = [&](int64_t steps, double* ms_per_step) -> int {
     std::vector<int64_t> ns(B.count, steps);
     int r = upload_layout(B);
     if (!r) r = prepare(B, cp.data(), V, ns.data(), st);
@@ -993,14 +993,16 @@ extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* cons
     *ms_per_step = ms / static_cast<double>(steps);
     return DL_OK;
   };
-  // 0. register tiles; the steps below tune the marching passes
-  double tiles_t = 0;
-  B.tiles = true;
-  rc = score(&tiles_t);
+  // ... of `trials` passes (twice as many of the register tiles: their pass count is
+  // even, and fewer steps would make shallower passes)
+  auto score = [&](double* ms_per_step) {
+    return time_steps(B.tiles ? 2 * int64_t(trials) * B.tile_depth : int64_t(trials) * B.depth,
+                      ms_per_step);
+  };
+  const bool tiles_were = B.tiles;
   B.tiles = false;
-  double march_t = 1e300;
   // 1. the pass depth
-  if (rc == DL_OK) {
+  {
     int best = B.depth;
     double best_t = 1e300;
     for (int d = std::min(3, B.depth_cap); d <= B.depth_cap && rc == DL_OK; ++d) {
@@ -1013,7 +1015,6 @@ extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* cons
       }
     }
     B.depth = best;
-    march_t = std::min(march_t, best_t);
   }
   // 2. the segment length of each 2-D size class, largest class first
   std::vector<int> classes;
@@ -1038,10 +1039,19 @@ extern "C" int dl_batch_autotune(dl_plan b, void* const* psi, const double* cons
       }
     }
     B.seg_of[cls] = best;
-    march_t = std::min(march_t, best_t);
   }
-  B.tiles = tiles_t <= march_t;
-  // 3. the lines kernel's workgroup size
+  // 3. the marching passes so tuned against the register tiles
+  if (rc == DL_OK) {
+    choose_register_tiles(B);
+    const int64_t steps = 2 * int64_t(trials) * std::lcm(B.depth, B.tile_depth);
+    double march_t = 0, tiles_t = 0;
+    rc = time_steps(steps, &march_t);
+    B.tiles = true;
+    if (rc == DL_OK) rc = time_steps(steps, &tiles_t);
+    B.tiles = tiles_t <= march_t;
+  }
+  if (rc != DL_OK) B.tiles = tiles_were;
+  // 4. the lines kernel's workgroup size
   bool any_line = false;
   for (const BatchInst& I : B.h_insts) any_line = any_line || I.line;
   if (any_line && rc == DL_OK) {

@@ -411,17 +411,20 @@ class Batch:
         check(self.lib.dl_batch_step(self.handle, P, Vp, ns, _stream_handle()))
 
     def autotune(self, psis, Vs, trials=4) -> dict:
-        """Tune the tile shapes on a copy of the states; returns the choice
-        (depth, line_threads, seg_len of the largest 2-D size class)."""
+        """Tune the tile shapes on a copy of the states; returns the choice: depth and
+        seg_len of the largest 2-D size class for marching passes, line_threads,
+        and tile_depth, the steps per pass of the register tiles where those won
+        (0: the marching passes did)."""
         P, Vp = self._ptrs(psis, Vs)
         out = (ctypes.c_int * 3)()
         check(self.lib.dl_batch_autotune(self.handle, P, Vp, int(trials), out,
                                          _stream_handle()))
-        return {"depth": out[0], "line_threads": out[1], "seg_len": out[2]}
+        return {"depth": out[0], "line_threads": out[1], "seg_len": out[2],
+                "tile_depth": self.info()["tile_depth"]}
 
     def set(self, seg_len=64, depth=None):
-        """Segment length of every 2-D size class and steps per pass (None:
-        the current depth)."""
+        """Marching passes with this segment length of every 2-D size class and
+        steps per pass (None: the current depth)."""
         check(self.lib.dl_batch_set(self.handle, int(seg_len),
                                     int(self.depth() if depth is None else depth)))
 
