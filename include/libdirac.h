@@ -34,10 +34,11 @@
  *    allocated in dl_plan_create.  Steps run in passes over memory that
  *    alternate between psi and that buffer; a call that takes an odd number
  *    of passes ends in the buffer and copies the result back into psi, except
- *    that for three or more passes the plan allocates (once, on the first
- *    such call outside stream capture) a third state buffer through which
- *    the last pass writes psi directly.  One plan must not be used from two
- *    streams or threads at once.
+ *    that for three or more passes a third state buffer serves, through which
+ *    the last pass writes psi directly: allocated with the plan on 1-D and 2-D
+ *    plans whose passes run in registers (dl_step) and whose state has at most
+ *    256 MiB, else once, on the first such call outside stream capture.  One plan
+ *    must not be used from two streams or threads at once.
  *  - psi and lam must be 16-byte aligned, V, Q and G 8-byte aligned.
  *  - The plan, step, observables, adjoint and batch calls each open a named
  *    roctx range (the call's name) for rocprofv3 --marker-trace, so a trace

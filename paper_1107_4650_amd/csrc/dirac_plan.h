@@ -108,6 +108,7 @@ struct dl_plan_s {
   void* tmp = nullptr;         // second state buffer
   void* tmp2 = nullptr;        // second state buffer for the adjoint field
   void* alt = nullptr;         // third state buffer (odd pass counts end in psi)
+  bool alt_in_tmp = false;     // ... the second half of tmp's allocation
   bool alt_failed = false;     // its allocation failed once: keep copying back
   double* partials = nullptr;  // reduction partials
   double* dres = nullptr;      // device results

@@ -465,6 +465,27 @@ static int plan_tiling(dl_plan p) {
   return DL_OK;
 }
 
+// Plans with register passes, whose calls often take an odd number of passes, get
+// the third state buffer with the second, in one allocation, up to this size (2048^2
+// FP32: 134 MB): allocated by the first such call it cost that call 30 to 300 us.
+// Larger plans prefer an even count (even_passes) and allocate it on demand.
+constexpr size_t kAltWithPlan = size_t(256) << 20;
+
+static hipError_t alloc_states(dl_plan p) {
+  const size_t at = (p->state_bytes + 255) / 256 * 256;
+  if (p->g.ndim < 3 && (p->tile_depth > 0 || p->tile_depth_field > 0 || p->line_depth > 0) &&
+      p->state_bytes <= kAltWithPlan) {
+    if (hipMalloc(&p->tmp, at + p->state_bytes) == hipSuccess) {
+      p->alt = static_cast<char*>(p->tmp) + at;
+      p->alt_in_tmp = true;
+      return hipSuccess;
+    }
+    (void)hipGetLastError();
+    p->tmp = nullptr;
+  }
+  return hipMalloc(&p->tmp, p->state_bytes);
+}
+
 extern "C" int dl_plan_create(dl_plan* out, const dl_grid* g, double dx, double dt, double c,
                               double m, dl_dtype dtype, dl_bc bc, unsigned flags) {
   dirac::TraceRange trace_range("dl_plan_create");
@@ -521,7 +542,7 @@ extern "C" int dl_plan_create(dl_plan* out, const dl_grid* g, double dx, double 
   plan_tiling(p);
   const bool mid = strang && g->ndim == 3;  // the 3-D second-order step runs through a third buffer
   if (mid) dirac::strang3d_prepare(p->fp64);
-  if (hipMalloc(&p->tmp, p->state_bytes) != hipSuccess ||
+  if (alloc_states(p) != hipSuccess ||
       (mid && hipMalloc(&p->tmp2, p->state_bytes) != hipSuccess) ||
       hipMalloc(&p->partials, sizeof(double) * 2 * 8 * kObsBlocks) != hipSuccess ||
       hipMalloc(&p->dres, sizeof(double) * 64) != hipSuccess ||
@@ -562,7 +583,7 @@ extern "C" int dl_plan_destroy(dl_plan p) {
     if (p->dres) (void)hipFree(p->dres);
     if (p->hres) (void)hipHostFree(p->hres);
     if (p->tile_partials) (void)hipFree(p->tile_partials);
-    if (p->alt) (void)hipFree(p->alt);
+    if (p->alt && !p->alt_in_tmp) (void)hipFree(p->alt);
     (void)hipGetLastError();
   }
   delete p;
@@ -679,15 +700,26 @@ static double copy_us(dl_plan p) {
   return std::max(9.0, 2.0 * static_cast<double>(p->state_bytes) / 5.4e6);
 }
 
-// passes for n steps where a pass has at most `depth`: a single one ends in the
-// plan's buffer, so two shallower ones, unless copying the state back is cheaper.
+// passes for n steps where a pass has at most `depth`, `more` passes of the call
+// following: a single one ends in the plan's buffer, so two shallower ones, unless
+// copying the state back is cheaper; an odd count of three or more needs the third
+// state buffer, so one more pass where the plan lacks it and that costs at most 3 %.
 // time(steps): of a pass
 template <class F>
-static int64_t even_passes(dl_plan p, int64_t n, int depth, F time) {
+static int64_t even_passes(dl_plan p, int64_t n, int depth, int more, F time) {
   const int64_t passes = (n + depth - 1) / depth;
-  if (passes != 1 || n == 1) return passes;
-  const int k = static_cast<int>(n);
-  return time(k - k / 2) + time(k / 2) < time(k) + copy_us(p) ? 2 : 1;
+  if (passes == n) return passes;
+  if (passes + more == 1) {
+    const int k = static_cast<int>(n);
+    return time(k - k / 2) + time(k / 2) < time(k) + copy_us(p) ? 2 : 1;
+  }
+  if ((passes + more) % 2 == 0 || p->alt_in_tmp) return passes;
+  auto us = [&](int64_t m) {
+    const int d = static_cast<int>(n / m);
+    const double deep = static_cast<double>(n % m);
+    return (static_cast<double>(m) - deep) * time(d) + (deep > 0.0 ? deep * time(d + 1) : 0.0);
+  };
+  return us(passes + 1) <= 1.03 * us(passes) ? passes + 1 : passes;
 }
 
 // predicted time of a 2-D call's passes (dirac_pass_cost.h)
@@ -739,7 +771,7 @@ static PassList make_pass_list(dl_plan p, int64_t nsteps, bool obs) {
   // bytes; 10 steps: 1e6 cells 63 against 66 us, 4e6 228 against 240)
   const bool few = p->fp64 && p->cells >= kLineFewCells && left <= 2 * dmax;
   if (p->line_depth > 0 && p->ph.mode <= 2 && left > 0 && !few) {
-    const int64_t passes = even_passes(p, left, p->line_depth, [&](int k) {
+    const int64_t passes = even_passes(p, left, p->line_depth, 0, [&](int k) {
       LineKind kind = kLineSmall;
       return line_best(p, k, &kind);
     });
@@ -755,9 +787,9 @@ static PassList make_pass_list(dl_plan p, int64_t nsteps, bool obs) {
   const TileKind tkind = field ? p->tile_kind_field : p->tile_kind;
   const int64_t n = obs ? left - std::min<int64_t>(left, dmax) : left;  // steps tiles may take
   if (tile > 0 && n > 0) {
-    const int64_t passes =
-        left == n ? even_passes(p, n, tile, [&](int k) { return tile_cost(p, field, tkind, k); })
-                  : (n + tile - 1) / tile;
+    const int64_t passes = even_passes(p, n, tile, left > n ? 1 : 0, [&](int k) {
+      return tile_cost(p, field, tkind, k);
+    });
     const int d = static_cast<int>(n / passes);  // passes of d + 1 and d steps
     l.add(PassRun::kTile, d + 1, n % passes);
     l.add(PassRun::kTile, d, passes - n % passes);
