@@ -140,7 +140,8 @@ int dl_step(dl_plan p, void *psi, const double *V, int64_t nsteps, void *stream)
  * 2-D grids (unless the depth is capped, 1-D lines run passes of up to 96
  * lowest-order or 48 second-order steps in registers, and calls of at most 10
  * steps, 5 with complex128, on up to 1024 cells in place in one workgroup
- * (allow_resident, dl_plan_set_tiling); 2-D planes with FP32 state, and with FP64 state up to 600
+ * (allow_resident, dl_plan_set_tiling; under stream capture where that is the faster
+ * on the device); 2-D planes with FP32 state, and with FP64 state up to 600
  * thousand cells, run passes of up to 12 lowest-order or 6 second-order steps
  * in register tiles where those are the faster (planes of a few rows and single
  * steps mostly march), unless the depth is capped or the plan retiled), fewer on

@@ -957,16 +957,40 @@ static hipError_t graph_for(dl_plan p, void* psi, const double* V, int64_t pairs
   return hipSuccess;
 }
 
-// A call of a few lowest-order steps over a line that one workgroup holds, one
-// cell per thread, runs in place in one launch: two register passes cost the host
-// two launches of 2.6 us, while a step in one workgroup takes 0.3 to 0.43 us (FP32)
-// or 0.31 to 0.85 us (FP64).  Per call of 10 steps on 1000 FP32 two-component
-// cells: 10.0 -> 7.5 us where the host bounds it, 6.4 against 5.2 us on the device
-// alone (captured calls), hence the line at 10 steps; FP64, 5 steps: 7.1 against
-// 5.2 us.
-static bool short_line(dl_plan p, int64_t nsteps) {
-  return p->line_depth > 0 && !p->strang && p->allow_resident && p->g.n[0] <= 1024 &&
-         nsteps <= (p->fp64 ? 5 : 10);
+// A call of a few lowest-order steps over a line that one workgroup holds, one cell
+// per thread, runs in place in one launch instead of two register passes.  Enqueued one
+// after the other the second launch bounds such calls: through the Python binding, at
+// every length, width, phase mode and step count up to the limit, 6.2 to 7.0 us in place
+// against 8.5 to 9.1 (FP32), 6.8 to 8.8 against 9.6 to 10.4 (FP64).  On the device alone
+// the steps of one workgroup (0.25 us and 0.009 us per wave with FP32 state, 0.033 with
+// FP64) overtake two passes: 10 steps on 1000 cells with a potential 6.7 against 5.9 us
+// with four components and 6.5 against 5.4 with two, FP64, 5 steps, 8.7 against 6.1 and
+// 7.2 against 5.3.  The limits are where that difference eats the launch (2.6 us).  A
+// call that is being captured costs the host nothing on replay and takes the faster
+// device time (fits to captured calls on 64 to 1024 cells, errors 2 to 4 %).
+static bool short_line(dl_plan p, int64_t nsteps, hipStream_t st) {
+  if (p->line_depth == 0 || p->strang || !p->allow_resident || p->g.n[0] > 1024 ||
+      nsteps > (p->fp64 ? 5 : 10))
+    return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    cs = hipStreamCaptureStatusNone;
+  }
+  if (cs == hipStreamCaptureStatusNone) return true;
+  struct Fit { double t0, wave, v0, v_wave, step, step_wave; };
+  static const Fit whole[2][2] = {  // [fp64][two components]
+      {{1.52, 0.033, 0.23, 0.021, 0.244, 0.009}, {1.50, 0.011, 0.21, 0.024, 0.252, 0.009}},
+      {{1.45, 0.127, 0.50, 0.031, 0.238, 0.033}, {1.47, 0.021, 0.42, 0.048, 0.228, 0.032}}};
+  static const Fit passes[2][2] = {
+      {{3.88, 0.020, 0.67, 0.013, 0.080, 0.0}, {3.80, 0.026, 0.63, 0.004, 0.042, 0.0}},
+      {{4.06, 0.029, 1.01, 0.014, 0.085, 0.0}, {3.87, 0.024, 0.84, 0.007, 0.047, 0.0}}};
+  const double waves = static_cast<double>((p->g.n[0] + 63) / 64);
+  auto us = [&](const Fit& f) {
+    return f.t0 + f.wave * waves + (p->ph.mode == 2 ? f.v0 + f.v_wave * waves : 0.0) +
+           static_cast<double>(nsteps) * (f.step + f.step_wave * waves);
+  };
+  return us(whole[p->fp64][p->nc == 2]) <= us(passes[p->fp64][p->nc == 2]);
 }
 
 extern "C" int dl_step(dl_plan p, void* psi, const double* V, int64_t nsteps, void* stream) {
@@ -983,7 +1007,7 @@ extern "C" int dl_step(dl_plan p, void* psi, const double* V, int64_t nsteps, vo
   p->ph = make_phase(transports_per_step(p), p->dt, p->c, p->m, mode, p->fp64);
   p->field = nullptr;
   select_tiling(p, mode);
-  const bool one = short_line(p, nsteps);
+  const bool one = short_line(p, nsteps, st);
   if (p->resident || one) {
     ResidentArgs ra{};
     ra.n = p->g.n[0];
