@@ -86,7 +86,7 @@ inline double pulse_integral(const PulseK& p, double ta, double tb) {
 
 // F of step n0 + s of the pass (the time of a step is formed from its global
 // index, so a pass of K steps and K passes of one step see the same values)
-inline double pulse_step_integral(const PulseK& p, int s) {
+inline double pulse_step_integral(const PulseK& p, int64_t s) {
   const double n = static_cast<double>(p.n0 + s);
   return pulse_integral(p, std::fma(n, p.dt, p.t0), std::fma(n + 1.0, p.dt, p.t0));
 }

@@ -906,7 +906,7 @@ static hipError_t strang3d_t(const void* src, void* dst, void* mid, void* mid2, 
   // with a second scratch state (mid2) src and dst may be the same buffer.
   auto step_pass = [&](bool first_pass, int64_t step, const T* in, T* out) {
     SweepArgs t = first_pass ? first : next;
-    t.F[0] = pulse ? pulse_step_integral(*pulse, static_cast<int>(step)) : 1.0;
+    t.F[0] = pulse ? pulse_step_integral(*pulse, step) : 1.0;
     const dim3 g(static_cast<unsigned>(first_pass ? bfirst : bnext));
     if (first_pass) {
       switch (mode) {
