@@ -384,6 +384,7 @@ static double line_best(dl_plan p, int steps, LineKind* kind) {
 }
 
 constexpr int64_t kLineFewCells = 200000;
+constexpr int64_t kLineFewCellsPair = int64_t(1) << 20;
 
 // Lines without a vector potential whose passes are not capped by the caller
 // run register passes of the depth of least fitted time per step (whole
@@ -768,8 +769,11 @@ static PassList make_pass_list(dl_plan p, int64_t nsteps, bool obs) {
   const int dmax = (p->ph.mode >= 3) ? p->depth_field : p->depth;
   // (FP64 calls of two marching passes or one on long lines run those: a wave of
   // a register pass reads 64 cells to write 48, and short passes are bound by the
-  // bytes; 10 steps: 1e6 cells 63 against 66 us, 4e6 228 against 240)
-  const bool few = p->fp64 && p->cells >= kLineFewCells && left <= 2 * dmax;
+  // bytes; 10 steps: 1e6 cells 63 against 66 us, 4e6 228 against 240.  FP32 lines of
+  // two components: two full marching passes of long lines only; 10 steps: 2^20 cells
+  // 19.6 against 21.3, 2^22 63.5 against 67.8; 8 steps 20.4 against 19.1)
+  const bool few = p->fp64 ? p->cells >= kLineFewCells && left <= 2 * dmax
+                           : p->nc == 2 && p->cells >= kLineFewCellsPair && left == 2 * dmax;
   if (p->line_depth > 0 && p->ph.mode <= 2 && left > 0 && !few) {
     const int64_t passes = even_passes(p, left, p->line_depth, 0, [&](int k) {
       LineKind kind = kLineSmall;
