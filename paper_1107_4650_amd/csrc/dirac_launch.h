@@ -26,10 +26,6 @@ constexpr int64_t kMaxRow3DFused = int64_t(1) << 28;
 // compiler parking part of the working set in the accumulation registers.
 constexpr int kMaxDepth = 5;
 constexpr int kMaxDepthF64 = 5;
-// the least steps a pass of a long lowest-order run without a vector potential
-// has on lines of at most kDeep1DMaxCells cells (dl_plan_info)
-constexpr int kDeep1D = 24;
-constexpr int64_t kDeep1DMaxCells = 65536;
 __host__ __device__ constexpr int max_depth(bool fp64, bool strang) {
   return strang ? 3 : (fp64 ? kMaxDepthF64 : kMaxDepth);
 }

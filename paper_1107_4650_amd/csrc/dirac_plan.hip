@@ -1363,8 +1363,9 @@ extern "C" int dl_plan_info(dl_plan p, int64_t* info, int n) {
                           t.ntiles,            p->resident,  p->res_threads, p->waves_per_cu,
                           t.xcd_remap,         p->graph_pairs, p->depth,     p->bl[0],
                           reverse_depth(p),    p->depth_field,
-                          (p->line_depth > 0 && !p->strang && p->g.n[0] <= kDeep1DMaxCells)
-                              ? kDeep1D : 0,
+                          // obsolete, for callers that read it: the steps of a kind of pass
+                          // over short lines that the register passes replaced
+                          (p->line_depth > 0 && !p->strang && p->g.n[0] <= 65536) ? 24 : 0,
                           p->tile_depth, p->line_depth,
                           p->tile_depth > 0 ? p->tile_kind + 1 : 0,
                           p->tile_depth_field, reverse_tile_depth(p),
