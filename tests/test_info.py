@@ -30,6 +30,16 @@ def test_register_tiles_are_named(dtype, scheme):
         assert line[k] == 0, k
 
 
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("scheme", ["lie", "strang"])
+@pytest.mark.parametrize("shape,kind", [
+    ((2, 2), 3), ((7, 3), 3), ((41, 9), 3), ((130, 127), 3), ((256, 257), 3), ((21, 1000), 3),
+    ((400, 390), 4), ((511, 513), 4)])
+def test_pairs_apart_on_both_tiles(shape, kind, scheme, dtype):
+    # both tiles of the pairs, at sizes that the comparisons with single steps run
+    assert info(shape, scheme=scheme, dtype=dtype)["tile_2d_kind"] == kind
+
+
 def test_caps_leave_marching_passes():
     with L.Plan((256, 256), DX, DX / C, C, 1.0, dry=True) as p:
         p.set_depth(2)
