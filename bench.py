@@ -44,7 +44,7 @@ def log(msg):
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("dirac_device.h", "dirac_sweep_impl.h", "dirac_tile2d_kernels.h",
+    for f in ("dirac_cos_sinc.h", "dirac_device.h", "dirac_sweep_impl.h", "dirac_tile2d_kernels.h",
               "dirac_tile2d_f32.hip", "dirac_launch.h"):
         with open(os.path.join(ROOT, "paper_1107_4650_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
@@ -64,14 +64,8 @@ def timed_sweep(plan, psi, V, steps, warmup, fused=1):
         nl -= 1  # an even count of marching passes ends in psi: no copy back in the timed region
     if fused > 1 and plan.info()["depth"] != fused:
         plan.set_depth(fused)
-    tile = plan.info()["tile_2d_depth"]  # register-tile passes of at most that many steps
-    passes = -(-nl * fused // tile) if tile else nl
     if nw:
         plan.step(psi, V, nw * fused)
-    if tile and passes > 2 and passes % 2:
-        # the plan allocates its third state buffer at the first call of an odd
-        # number of passes: not in the timed region
-        plan.step(psi.clone(), V, 3 * tile)
     torch.cuda.synchronize()
     start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     t0 = time.perf_counter()
@@ -80,7 +74,14 @@ def timed_sweep(plan, psi, V, steps, warmup, fused=1):
     end.record()
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
+    passes = passes_run(plan)
     return wall, start.elapsed_time(end) / passes, psi, nl * fused, passes
+
+
+def passes_run(plan):
+    """Passes over memory of the plan's last call that stepped."""
+    i = plan.info()
+    return i["ran_marching"] + i["ran_tiles"] + i["ran_lines"] + i["ran_whole"]
 
 
 def to_dev(x, dtype=None):
@@ -320,7 +321,7 @@ def bench_long_line(n=1 << 22, steps=400):
             e.record()
             torch.cuda.synchronize()
             ms = s.elapsed_time(e)
-            depth = p.info()["line_1d_depth"]
+            depth = steps / passes_run(p)
         out[name] = {"ms_per_step": ms / steps, "site_updates_per_s": n * steps / (ms * 1e-3),
                      "steps_per_pass": depth, "bytes_per_cell_per_pass": 8 * 2 * nc + 8}
         del t
@@ -352,8 +353,9 @@ def bench_field(args, steps=400):
         e.record()
         torch.cuda.synchronize()
         ms = s.elapsed_time(e)
+        passes = passes_run(p)
         norm = p.observables(psi, 0.0)[0]
-        K = p.info()["field_depth"]
+        K = steps / passes
     del psi, V, At
     torch.cuda.empty_cache()
     # per pass of K steps: psi read + written (64 B), V (8 B), At (24 B) per cell
@@ -398,7 +400,7 @@ def bench_klein2d(args):
         wall = time.perf_counter() - t0
         ms = s.elapsed_time(e)
         obs = p.observables(psi, 0.0)
-        depth = p.info()["tile_2d_depth"]
+        depth = steps / passes_run(p)
     del psi, V
     torch.cuda.empty_cache()
     sites = nx * nz
@@ -443,7 +445,7 @@ def bench_3d(args):
         psi = (f[..., None] * u).to(tdt).contiguous()
         del f
         if dt_name.endswith("vector_potential"):
-            # a smooth static field integral along y, one step per pass
+            # a smooth static field integral along y
             At = torch.zeros((3, n, n, n), dtype=torch.float64, device="cuda")
             At[1] = (0.05 * torch.sin(2 * np.pi * x / 5.0))[None, None, :]
             with L.Plan((n, n, n), dx, dx / c, c, m, dtype="complex64") as p:
@@ -456,10 +458,11 @@ def bench_3d(args):
                 e_.record()
                 torch.cuda.synchronize()
                 msf = s_.elapsed_time(e_) / nf
-            # psi read + written (64 B), V (8 B), At (24 B) per cell and step
-            out[dt_name] = {"steps": nf, "ms_per_step": msf, "steps_per_pass": 1,
+                K = nf / passes_run(p)
+            # psi read + written (64 B), V (8 B), At (24 B) per cell and pass of K steps
+            out[dt_name] = {"steps": nf, "ms_per_step": msf, "steps_per_pass": K,
                             "site_updates_per_s": n ** 3 / (msf * 1e-3),
-                            "hbm_frac": 96 * n ** 3 / (msf * 1e-3) / 1e9 / HBM_PEAK_GBS}
+                            "hbm_frac": 96 * n ** 3 / (K * msf * 1e-3) / 1e9 / HBM_PEAK_GBS}
             log(f"3-D 512^3 {dt_name}: {msf:.3f} ms/step")
             del psi, At
             torch.cuda.empty_cache()
@@ -639,12 +642,12 @@ def bench_adjoint(args):
         p.grad_step(psi, lam, V, Q, w.nsteps)
         p.project(Q, G, g)
         ev[3].record()
+        K = w.nsteps / passes_run(p)
         torch.cuda.synchronize()
         fwd_ms = ev[0].elapsed_time(ev[1])
         bwd_ms = ev[2].elapsed_time(ev[3])
         rec = rel_l2(psi, psi0)
         gn = float(torch.linalg.vector_norm(g))
-        K = p.info()["reverse_depth"]
     sites = w.sites * w.nsteps
     g32 = g.cpu().numpy()
     check = adjoint_checks(w, G, theta, g32)
@@ -728,7 +731,10 @@ def bench_batch(args):
         out["autotuned"] = b.autotune(psis, Vs, trials=3)
         out["autotune_s"] = time.perf_counter() - t0
         out["layout"] = b.info()
-        K = b.depth()
+        # register tiles: an even count of passes of at most that many steps
+        tile = out["layout"]["tile_depth"]
+        passes = 2 * -(-steps // (2 * tile)) if tile else steps // b.depth() + steps % b.depth()
+        K = steps / passes
         work = [t.clone() for t in psis]
         b.step(work, Vs, [steps] * len(ws))  # captures the call's graph
         del work
@@ -739,7 +745,8 @@ def bench_batch(args):
         tb = time.perf_counter() - t0
     out["batched_s"] = tb
     out["batched_site_updates_per_s"] = sites * steps / tb
-    # one pass of K steps reads and writes each state once and reads V once
+    # one pass of K steps (mean of the call) reads and writes each state once and reads V
+    # once
     out["batched_steps_per_pass"] = K
     out["batched_roofline_frac"] = BYTES_F32 / K * sites * steps / tb / 1e9 / HBM_PEAK_GBS
     # the same instances one plan at a time, from the same initial states
@@ -761,7 +768,7 @@ def bench_batch(args):
     out["one_at_a_time_site_updates_per_s"] = sites * steps / ts
     out["speedup"] = ts / tb
     log(f"batch: {tb:.3f} s batched vs {ts:.3f} s one at a time "
-        f"(depth {K}, {out['layout']['lines']} lines in {out['layout']['line_bins']} workgroups)")
+        f"({K:.2f} steps a pass, {out['layout']['lines']} lines in {out['layout']['line_bins']} workgroups)")
     return out
 
 
