@@ -19,13 +19,13 @@
 // with a potential, marching -> tiles: 256^2 FP32 4.06 -> 1.20 us, 1024^2
 // 6.7 -> 4.6 us, 2048^2 17.0 -> 14.0 us; 256^2 FP64 4.9 -> 1.7 us; second
 // order at 2048^2 FP32 28.4 -> 25.7 us.  Large planes are bound by VALU issue
-// (the halo makes a tile of 48 rows and K = 7 do 1.8 times the work it writes)
-// at 4.5 TB/s of reads and writes; small ones by the launch and the first load
-// (about 5 us) and by the barrier and LDS latency of a step (0.7 us).  With a
-// vector potential a step is bound by some 150 FP64 operations per cell, the
-// halo counts for more and the tiles win on planes of up to 768^2 cells only
-// (pulse, FP32: 256^2 7.3 -> 2.8 us per step, 768^2 11.1 -> 9.0, 1024^2 13.7
-// marching against 15.6).
+// (the halo makes a tile of 48 rows and K = 7 do 1.8 times the work it writes;
+// 71 % of the issue slots at 2.4 GHz and 3.1 TB/s counted at 2048^2); small ones
+// by the launch and the first load (about 5 us) and by the barrier and LDS
+// latency of a step (0.7 us).  With a vector potential a step is bound by some
+// 150 FP64 operations per cell, the halo counts for more and the tiles win on
+// planes of up to 768^2 cells only (pulse, FP32: 256^2 7.3 -> 2.8 us per step,
+// 768^2 11.1 -> 9.0, 1024^2 13.7 marching against 15.6).
 // On a small plane of alpha_x and alpha_y the step is the issue of a unit's
 // sixteen waves while other units idle: the two uncoupled pairs of a spinor
 // go to workgroups of their own (256^2, FP32, 100 steps: 119 -> 97 us).
