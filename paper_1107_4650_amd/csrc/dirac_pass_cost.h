@@ -13,8 +13,8 @@
 // call leaves the tiles only where marching is predicted to be 5 % faster; a call of
 // one pass, which is a copy and little else, goes where the prediction says, and so
 // does FP64 second order, where the two cross flatly and are predicted to 3 % (640^2 to
-// 720^2, 36 steps: marching 343 to 364 us, tiles 349 to 397).  Of 13
-// thousand measured calls of 1 to 100 steps, 2280 ran over 3 % slower than in
+// 720^2, 36 steps: marching 343 to 364 us, tiles 349 to 397).  Of 13 thousand calls of
+// 1 to 100 steps composed from the measured passes, 2280 take over 3 % longer than in
 // marching passes with tiles wherever they fit, at worst 4.3 times; by this rule 236
 // do, at worst 1.3 times.
 #pragma once

@@ -145,7 +145,9 @@ void make_tiling(const dl_grid& g, int64_t target, int seg_override, SweepArgs& 
 
 // Time of a register-tile pass in us, from fits (rms error 4-9 %) to the
 // passes of 1 to 12 steps (8 with a vector potential) on planes of 128^2 to
-// 4096^2 (2048^2) cells: a compute unit's first tile takes t0 + t1 per transport
+// 4096^2 (2048^2) cells, of alpha_x and alpha_y with a potential: it picks a plan's
+// tile and depth (dirac_pass_cost.h, fitted to every phase mode and to thin planes,
+// says whether a call takes them).  A compute unit's first tile takes t0 + t1 per transport
 // pair, every further one n0 + n1 per transport pair.  Without a vector potential
 // and with at most one workgroup per unit (rms error 2-5 %, 64^2 to 640^2), the
 // loads of all workgroups add `load` on a full chip.
@@ -827,8 +829,9 @@ static const PassList& pass_list(dl_plan p, int64_t nsteps, bool obs) {
 
 // The plan's third state buffer: with it, an odd number (>= 3) of passes
 // ends in psi (psi -> tmp -> alt -> tmp ... -> psi) instead of in tmp with a
-// copy back.  Allocated once, by the first call that needs it, and never
-// while the stream is being captured; without it the copy stays.  n: passes
+// copy back.  Where it did not come with the plan (kAltWithPlan), allocated once,
+// by the first call that needs it, and never while the stream is being captured;
+// without it the copy stays.  n: passes
 // of the call.
 static void want_alt(dl_plan p, int64_t n, hipStream_t st) {
   if (p->alt || p->alt_failed) return;
