@@ -470,15 +470,12 @@ static int plan_tiling(dl_plan p) {
 
 // Plans with register passes, whose calls often take an odd number of passes, get
 // the third state buffer with the second, in one allocation, up to this size (2048^2
-// FP32: 134 MB): allocated by the first such call it cost that call 30 to 300 us.  It
-// starts on a 2 MiB boundary, as an allocation of its own does (4096 FP64 cells, 2000
-// steps: 259.2 us, right behind the second 260.8).
+// FP32: 134 MB): allocated by the first such call it cost that call 30 to 300 us.
 // Larger plans prefer an even count (even_passes) and allocate it on demand.
 constexpr size_t kAltWithPlan = size_t(256) << 20;
 
 static hipError_t alloc_states(dl_plan p) {
-  constexpr size_t kPage = size_t(2) << 20;
-  const size_t at = (p->state_bytes + kPage - 1) / kPage * kPage;
+  const size_t at = (p->state_bytes + 255) / 256 * 256;
   if (p->g.ndim < 3 && (p->tile_depth > 0 || p->tile_depth_field > 0 || p->line_depth > 0) &&
       p->state_bytes <= kAltWithPlan) {
     if (hipMalloc(&p->tmp, at + p->state_bytes) == hipSuccess) {
